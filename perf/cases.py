@@ -218,3 +218,117 @@ def tolerance(case):
     if case["op"] != "forward":
         return {"rel": 4e-6, "max": 5e-5}
     return {"rel": 4.4e-6, "max": 3.5e-5} if case["types"] == "vector" else {"rel": 1.3e-6, "max": 1.5e-5}
+
+
+# ---- the same outputs in 64 bits, in plain torch ----
+
+def _philox(b, draw, block):
+    """Philox4x32-10 with key 0: four uniforms of example b (the documented augmentation stream)."""
+    c, k = [b, draw & 0xFFFFFFFF, draw >> 32, block], [0, 0]
+    for _ in range(10):
+        p0, p1 = 0xD2511F53 * c[0], 0xCD9E8D57 * c[2]
+        c = [(p1 >> 32) ^ c[1] ^ k[0], p1 & 0xFFFFFFFF, (p0 >> 32) ^ c[3] ^ k[1], p0 & 0xFFFFFFFF]
+        k = [(k[0] + 0x9E3779B9) & 0xFFFFFFFF, (k[1] + 0xBB67AE85) & 0xFFFFFFFF]
+    return [(w + 0.5) / 2.0 ** 32 for w in c]
+
+
+def _first_poses(B, dev):
+    """The poses a new GridLayer draws for its first pass: uniform rotations, +-2 A."""
+    q, t = [], []
+    for b in range(B):
+        u, v = _philox(b, 0, 0), _philox(b, 0, 1)
+        s1, s2, a1, a2 = math.sqrt(1 - u[0]), math.sqrt(u[0]), 2 * math.pi * u[1], 2 * math.pi * u[2]
+        q.append([s2 * math.cos(a2), s1 * math.sin(a1), s1 * math.cos(a1), s2 * math.sin(a2)])
+        t.append([2.0 * (2.0 * x - 1.0) for x in v[:3]])
+    return torch.tensor(q, device=dev), torch.tensor(t, device=dev)     # float32, as they are applied
+
+
+def _rotations(q):
+    q = q.double()
+    w, x, y, z = (q / q.norm(dim=1, keepdim=True)).unbind(1)
+    return torch.stack([1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y),
+                        2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x),
+                        2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)], 1).view(-1, 3, 3)
+
+
+def _density(x):
+    """rho(x) and rho'(x), x = d/r: a Gaussian up to 1, a quadratic from there to 3/2."""
+    e, A = torch.exp(-2 * x * x), 4 * math.exp(-2.0)
+    u = (1.5 - x).clamp(min=0.0)
+    return torch.where(x <= 1, e, A * u * u), torch.where(x <= 1, -4 * x * e, -2 * A * u)
+
+
+def exact(case, seed):
+    """Atoms placed in 64 bits and rounded to float (positions are float by definition), every
+    voxel in an atom's cutoff box summed in 64 bits.  None for occupancy, which is decided bit
+    for bit by a fixed sequence of float operations and compared exactly."""
+    c = case
+    if c["binary"]:
+        return None
+    s = prepare(case, seed)
+    dev, B, N, T, D, S = s["coords"].device, c["B"], c["N"], c["T"], c["D"], c["S"]
+    side, f64 = D * S, torch.float64
+    quats, trans = _first_poses(B, dev) if c["pose"] == "random" else (s["quats"], s["translations"])
+    cen = s["centers"].double() if s["centers"] is not None else torch.zeros((B, 3), dtype=f64, device=dev)
+    R = _rotations(quats) if quats is not None else torch.eye(3, dtype=f64, device=dev).repeat(B, 1, 1)
+    pos = torch.einsum("bmk,bnk->bnm", R, s["coords"].detach().double() - cen[:, None]) + cen[:, None]
+    if trans is not None:
+        pos = pos + trans.double()[:, None]
+    pos = pos.float().double() - cen[:, None] + 0.5 * (side - 1) * c["res"]      # from the first lattice point
+    alive = torch.ones((B, N), dtype=torch.bool, device=dev)
+    if s["natoms"] is not None:
+        alive &= torch.arange(N, device=dev)[None, :] < s["natoms"][:, None]
+    vector = c["types"] == "vector"
+    w = s["weights"].detach().double() if vector else None
+    grid = torch.zeros(B * T * side ** 3 if c["op"] != "backward" else 0, dtype=f64, device=dev)
+    G = None
+    if c["op"] != "forward":
+        G = s["grad"].double()
+        if S > 1:       # subgrids -> one cube
+            G = G.permute(0, 4, 1, 5, 2, 6, 3, 7).reshape(B, T, side, side, side)
+        G = G.reshape(-1)
+    gpos = torch.zeros((B, N, 3), dtype=f64, device=dev)
+    gw = torch.zeros((B, N, T), dtype=f64, device=dev) if vector else None
+    K = int(2 * CUTOFF * RMAX / c["res"]) + 3
+    o = torch.arange(K, device=dev)
+    box = torch.stack(torch.meshgrid(o, o, o, indexing="ij"), -1).view(1, -1, 3)
+    bi, ni = torch.nonzero(alive, as_tuple=True)
+    step = max(1, 12_000_000 // K ** 3)
+    for a0 in range(0, len(bi), step):
+        b, n = bi[a0:a0 + step], ni[a0:a0 + step]
+        x = pos[b, n]
+        lo = torch.floor((x - CUTOFF * RMAX) / c["res"]).long()
+        p = lo[:, None] + box
+        u = x[:, None] - p * c["res"]                           # atom minus voxel
+        d = u.norm(dim=2)
+        ok = ((p >= 0) & (p < side)).all(2)
+        v = torch.where(ok, (p[..., 0] * side + p[..., 1]) * side + p[..., 2], 0)
+        if vector:
+            chans = [(torch.full_like(n, t), s["radii"][t].double().expand(len(n))) for t in range(T)]
+        else:
+            t = s["types"][b, n].long()
+            chans = [(t, (s["radii"][t] if c["radii"] == "type" else s["radii"][b, n]).double())]
+        for t, r in chans:
+            rho, slope = _density(d / r[:, None])
+            at = ((b * T + t) * side ** 3)[:, None] + v
+            rho = torch.where(ok, rho, 0.0)
+            wt = w[b, n, t] if vector else torch.ones_like(r)
+            if c["op"] != "backward":
+                grid.index_add_(0, at.view(-1), (wt[:, None] * rho).view(-1))
+            if c["op"] != "forward":
+                g = torch.where(ok, G[at], 0.0)
+                f = g * slope / (r[:, None] * d.clamp(min=1e-30))
+                gpos[b, n] += wt[:, None] * (f[..., None] * u).sum(1)
+                if vector:
+                    gw[b, n, t] = (g * rho).sum(1)
+    out = []
+    if c["op"] != "backward":
+        grid = grid.view(B, T, side, side, side)
+        if S > 1:
+            grid = grid.view(B, T, S, D, S, D, S, D).permute(0, 2, 4, 6, 1, 3, 5, 7).contiguous()
+        out.append(grid)
+    if c["op"] != "forward":
+        out.append(torch.einsum("bmk,bnm->bnk", R, gpos))
+        if vector:
+            out.append(gw)
+    return out if c["op"] == "step" else (tuple(out) if len(out) > 1 else out[0])
