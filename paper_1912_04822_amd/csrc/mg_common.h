@@ -65,9 +65,7 @@ __host__ __device__ inline int source_example(int subgrid_count, int e)
 //                         a bin, in atom order.  Slots first+live .. first+all
 //                         hold w = 0.
 //   idx   [B][N] int32    original atom index of each record
-//   meta  [B][T] int4     {first, live, all, sorted}; sorted = 0 means the
-//                         group was too long to bin: its records are in atom
-//                         order, culled ones carry r = 0, and live == all
+//   meta  [B][T] int4     {first, live, all, 1}
 //   range [B][T][D] int2  for x-plane i: the span [r0, r1) of records, counted from
 //                         the example's first record rec[b][0], that can reach
 //                         the plane; r0 and r1 do not decrease with i, so planes
@@ -135,7 +133,6 @@ struct ForwardGeometry {
 };
 ForwardGeometry forward_geometry(int D, int tile_floats);
 
-constexpr int kSortCap = 2048;          // longest group the prep kernel bins by x-plane
 constexpr int kRankCap = 256;           // most channels that are put in order of radius
 
 // Timing events for the main kernel of the current call (null: none).  The launchers pass
