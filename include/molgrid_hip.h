@@ -325,7 +325,9 @@ int mg_last_hip_error(void);
  *                     launch (every tile's wavefront transforms, culls and filters the
  *                     example's atoms itself; no prep kernel, the workspace is not
  *                     touched); 0 = always the prep kernel and its tables.  Binary
- *                     grids are the same to the bit either way, real ones to rounding
+ *                     grids are the same to the bit either way, real ones to rounding.
+ *                     Backward calls without subgrids likewise up to 49152 atoms in
+ *                     all (vector types 8192): gradients are the same to the bit
  *   "tile_order"      0 or 1 (default 0): 0 = all tiles of a channel, then the
  *                     next channel; 1 = tile k of every channel, then tile k+1
  *   "lds_floor"       -1..65536 (default -1 = chosen per call: 6144 for 4 KB

@@ -427,14 +427,17 @@ static int backward_call(const mg_gridmaker *gm, int B, int N, int T, const floa
     const bool sub = gm->sub.count > 1;
     float *gc = (sub && grad_coords) ? ws.gtmp : grad_coords;
     float *gw = (sub && grad_weights) ? ws.wtmp : grad_weights;
-    if (tables != Tables::kUseBuilt) {
+    // few atoms in all: one launch, every atom's wavefront places its atom itself
+    const bool single = tables == Tables::kBuildAndRun && timing_prep_stop() == 0 &&
+                        g_single_launch.load(std::memory_order_relaxed) != 0 && mg::backward_takes_single_launch(bt);
+    if (tables != Tables::kUseBuilt && !single) {
         const int stop = timing_prep_stop();
         rc = hip_status(mg::launch_prep(gm->gs, bt, ws, stop, (hipStream_t)stream));
         if (rc != MG_OK || stop != 0) return rc;    // a prep kernel cut short leaves no tables to read
     }
     const unsigned expect = tables == Tables::kUseBuilt ? mg::workspace_tag(gm->gs, bt) : 0u;
-    rc = hip_status(mg::launch_backward(gm->gs, bt, ws, grad_out, grad_is_double, gc, gw, expect,
-                                        take_events(), (hipStream_t)stream));
+    rc = hip_status(mg::launch_backward(gm->gs, bt, ws, grad_out, grad_is_double, gc, gw, single,
+                                        expect, take_events(), (hipStream_t)stream));
     if (rc != MG_OK || !sub) return rc;
     if (grad_coords)
         rc = hip_status(mg::launch_sum_subgrids(gm->sub.count, B, (size_t)N * 3, gc, grad_coords,

@@ -39,6 +39,7 @@
 
 #include "mg_common.h"
 #include "mg_wave.h"
+#include "mg_xform.h"
 
 namespace mg {
 
@@ -46,6 +47,7 @@ namespace {
 
 struct BwdParams {
     GridSpec gs;
+    RawInputs raw;
     const float4 *rec;
     const int *idx;
     const int4 *meta;
@@ -480,7 +482,7 @@ __device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kC
     });
 }
 
-template <bool VECTOR, bool ALIGNED, typename GT>
+template <bool VECTOR, bool ALIGNED, typename GT, bool FUSED = false>
 __global__ __launch_bounds__(256) void backward_kernel(BwdParams p)
 {
     const GridSpec &gs = p.gs;
@@ -497,7 +499,7 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdParams p)
     // Workgroup ids go round the 8 XCDs (id % 8), each with its own L2.  XCD k takes the k-th
     // eighth of the (example, record) list, so the gradient volume of an example -- and the
     // lines of it that neighbouring records share -- is read through one L2 only.
-    if (p.expect_tag != 0u && *p.tag != p.expect_tag) return;      // not the tables this call expects
+    if (!FUSED && p.expect_tag != 0u && *p.tag != p.expect_tag) return;      // not the tables this call expects
     const unsigned lin = blockIdx.x + zero;
     const unsigned v = (lin & 7u) * p.share + (lin >> 3);
     if (v >= p.units || (lin >> 3) >= p.share) return;
@@ -511,34 +513,81 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdParams p)
     static_assert(kSlotCap == 64 * 16, "one 16-byte store per lane clears the marks");
     reinterpret_cast<int4 *>(marks)[lane] = make_int4(0, 0, 0, 0);
     lds_sync();
-    // Everything the wavefront needs first is requested in one go (one trip to memory, not
-    // four in a row): the group table's last entry, the record and its atom index (slot
-    // clamped into the array; whether the slot is live is decided afterwards), the grid
-    // centre and the rotation.
-    const int cslot = min(slot, N - 1);
-    const unsigned char atom_alive = p.alive[(size_t)b * N + cslot];    // of ATOM number `slot`, see below
-    const int4 last = p.meta[(size_t)b * T + (VECTOR ? 0 : T - 1)];
-    const float4 a = p.rec[(size_t)b * N + cslot];
-    const int ai = p.idx[(size_t)b * N + cslot];
-    const int t_rec = VECTOR ? 0 : p.rchan[(size_t)b * N + cslot];
-    const float4 gc = *reinterpret_cast<const float4 *>(p.gcen + 4 * b);
-    const float *Rp = p.rot + b * 12;
-    const float4 Ra = *reinterpret_cast<const float4 *>(Rp);
-    const float4 Rb = *reinterpret_cast<const float4 *>(Rp + 4);
-    const float Rc = Rp[8];
-    asm volatile("" ::"s"(last.x), "s"(last.z), "s"(gc.x), "s"(gc.y), "s"(gc.z), "s"(Ra.x), "s"(Ra.y),
-                 "s"(Ra.z), "s"(Ra.w), "s"(Rb.x), "s"(Rb.y), "s"(Rb.z), "s"(Rb.w), "s"(Rc));
-    // Every output element is written by someone: the wavefront of record slot s also looks
-    // after ATOM s -- if that atom has no live record (culled, past natoms, type out of range)
-    // nobody else writes its gradient, so its zeros are stored here.
-    if (slot < N && atom_alive == 0) {
-        const size_t atom = (size_t)b * N + slot;
-        if (p.grad_coords && lane < 3) p.grad_coords[atom * 3 + lane] = 0.0f;
-        if (VECTOR && p.grad_weights)
-            for (int k = lane; k < T; k += 64) p.grad_weights[atom * T + k] = 0.0f;
+    float4 a, gc, Ra, Rb;       // record, grid centre, rotation (rows, 9 values)
+    float Rc;
+    int ai, t_rec;
+    if (FUSED) {
+        // No tables: the wavefront of atom `slot` places it itself, with the arithmetic and the
+        // tests of the prep kernel (every value here is the same in all lanes).
+        if (slot >= N) return;
+        const int at = __builtin_amdgcn_readfirstlane(slot);
+        ai = at;
+        const size_t k = (size_t)b * N + at;
+        t_rec = VECTOR ? 0 : p.raw.types[k];
+        float pos[3] = {p.raw.coords[3 * k], p.raw.coords[3 * k + 1], p.raw.coords[3 * k + 2]};
+        const int n = p.raw.natoms ? p.raw.natoms[b] : N;
+        float r_in = 0.0f;
+        if (!VECTOR && !gs.radius_type_indexed) r_in = p.raw.radii[k];
+        Xform X;
+        load_xform(X, b, p.raw.centers, p.raw.quats, p.raw.translations);
+        const bool member = at < n && t_rec >= 0 && t_rec < T;
+        if (!VECTOR && gs.radius_type_indexed && member) r_in = p.raw.radii[t_rec];
+        float r = gs.radius_scale * r_in, reach = r * gs.c;
+        if (VECTOR) {
+            r = 1.0f;
+            float widest = 0.0f;        // of all channels
+            for (int c = lane; c < T; c += 64) widest = fmaxf(widest, gs.radius_scale * p.radii[c]);
+#pragma unroll
+            for (int m = 32; m > 0; m >>= 1) widest = fmaxf(widest, __shfl_xor(widest, m));
+            reach = widest * gs.c;
+        }
+        apply_xform(X, pos, pos);
+        gc = make_float4((float)X.c[0], (float)X.c[1], (float)X.c[2], 0.0f);
+        const float org[3] = {gc.x - gs.half, gc.y - gs.half, gc.z - gs.half};
+        const float span = (float)(D - 1) * gs.res, pad = 1.0e-3f * gs.res;
+        bool live = member && (r > 0.0f) && (reach < 1.0e30f);
+        for (int m = 0; m < 3; ++m)     // also false for NaN / infinite coordinates
+            live = live && (pos[m] >= org[m] - reach - pad) && (pos[m] <= org[m] + span + reach + pad);
+        if (!live) {
+            if (p.grad_coords && lane < 3) p.grad_coords[k * 3 + lane] = 0.0f;
+            if (VECTOR && p.grad_weights)
+                for (int c = lane; c < T; c += 64) p.grad_weights[k * T + c] = 0.0f;
+            return;
+        }
+        a = make_float4(pos[0], pos[1], pos[2], r);
+        Ra = make_float4((float)X.R[0], (float)X.R[1], (float)X.R[2], (float)X.R[3]);
+        Rb = make_float4((float)X.R[4], (float)X.R[5], (float)X.R[6], (float)X.R[7]);
+        Rc = (float)X.R[8];
+    } else {
+        // Everything the wavefront needs first is requested in one go (one trip to memory, not
+        // four in a row): the group table's last entry, the record and its atom index (slot
+        // clamped into the array; whether the slot is live is decided afterwards), the grid
+        // centre and the rotation.
+        const int cslot = min(slot, N - 1);
+        const unsigned char atom_alive = p.alive[(size_t)b * N + cslot];    // of ATOM number `slot`, see below
+        const int4 last = p.meta[(size_t)b * T + (VECTOR ? 0 : T - 1)];
+        a = p.rec[(size_t)b * N + cslot];
+        ai = p.idx[(size_t)b * N + cslot];
+        t_rec = VECTOR ? 0 : p.rchan[(size_t)b * N + cslot];
+        gc = *reinterpret_cast<const float4 *>(p.gcen + 4 * b);
+        const float *Rp = p.rot + b * 12;
+        Ra = *reinterpret_cast<const float4 *>(Rp);
+        Rb = *reinterpret_cast<const float4 *>(Rp + 4);
+        Rc = Rp[8];
+        asm volatile("" ::"s"(last.x), "s"(last.z), "s"(gc.x), "s"(gc.y), "s"(gc.z), "s"(Ra.x), "s"(Ra.y),
+                     "s"(Ra.z), "s"(Ra.w), "s"(Rb.x), "s"(Rb.y), "s"(Rb.z), "s"(Rb.w), "s"(Rc));
+        // Every output element is written by someone: the wavefront of record slot s also looks
+        // after ATOM s -- if that atom has no live record (culled, past natoms, type out of range)
+        // nobody else writes its gradient, so its zeros are stored here.
+        if (slot < N && atom_alive == 0) {
+            const size_t atom = (size_t)b * N + slot;
+            if (p.grad_coords && lane < 3) p.grad_coords[atom * 3 + lane] = 0.0f;
+            if (VECTOR && p.grad_weights)
+                for (int k = lane; k < T; k += 64) p.grad_weights[atom * T + k] = 0.0f;
+        }
+        if (slot >= last.x + last.z) return;            // past the last group's slots (per wavefront)
+        if (!(a.w > 0.0f)) return;                      // dead record: its atom's zeros are written above, by slot
     }
-    if (slot >= last.x + last.z) return;            // past the last group's slots (per wavefront)
-    if (!(a.w > 0.0f)) return;                      // dead record: its atom's zeros are written above, by slot
     const size_t D3 = (size_t)D * D * D;
     const int bs = source_example(p.subgrids, b);          // types and weights are the source example's
     const float ox = gc.x - gs.half;
@@ -660,10 +709,24 @@ hipError_t launch_sum_subgrids(int subgrid_count, int B_source, size_t per_examp
     return hipGetLastError();
 }
 
+// Few atoms: no prep kernel, every atom's wavefront places its atom itself, in the caller's order.
+// What is lost is the order by channel and plane (neighbouring wavefronts then share fewer lines of
+// the gradient grid) and, per atom, the transform worked out by a whole wavefront; what is saved is
+// the prep kernel's 10 us and more.  Whole calls, one launch / prep kernel and backward kernel:
+// 2040 atoms and 28 channels of 48^3 per example, us: index types 10.4 / 17.1 for 1 example, 34.7 / 38.2
+// for 16, 47.1 / 50.2 for 24, 61.5 / 61.3 for 32, 92.1 / 87.7 for 50; vector types, where every atom
+// reads every channel, 55 / 70 for 1, 130 / 144 for 4, 242 / 190 for 8.
+constexpr long long kSingleAtoms = 49152;           // index types
+constexpr long long kSingleAtomsVector = 8192;      // vector types
+bool backward_takes_single_launch(const Batch &bt)
+{
+    return bt.sub.count == 1 && (long long)bt.B * bt.N <= (bt.vec ? kSingleAtomsVector : kSingleAtoms);
+}
+
 hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace &ws,
                            const void *grad_out, bool grad_is_double, float *grad_coords,
-                           float *grad_weights, unsigned expect_tag, KernelEvents ev,
-                           hipStream_t stream)
+                           float *grad_weights, bool single_launch, unsigned expect_tag,
+                           KernelEvents ev, hipStream_t stream)
 {
     BwdParams p;
     p.gs = gs;
@@ -672,6 +735,7 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
     p.alive = ws.alive; p.tag = ws.tag; p.expect_tag = expect_tag;
     p.G = grad_out; p.grad_coords = grad_coords; p.grad_weights = grad_weights;
     p.subgrids = bt.sub.count; p.N = bt.N; p.T = bt.T;
+    p.raw = raw_inputs(bt);
     {
         const double k = 2.8853900817779268;    // 2 / ln 2
         p.sk = (float)std::sqrt(k);
@@ -689,18 +753,19 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
     p.share = (p.units + 7u) / 8u;
     p.wg_magic = p.wgs_per_example <= 1u ? 0ull : (~0ull / p.wgs_per_example) + 1ull;
     const dim3 grd(p.share * 8u), blk(256);
-#define MG_BWD(V, Al, Gt) \
-    hipExtLaunchKernelGGL((backward_kernel<V, Al, Gt>), grd, blk, 0, stream, ev.start, ev.stop, 0, p)
-#define MG_BWD_TYPE(Gt)                                      \
-    if (bt.vec) {                                        \
-        if (aligned) MG_BWD(true, true, Gt);                 \
-        else MG_BWD(true, false, Gt);                        \
-    } else {                                                 \
-        if (aligned) MG_BWD(false, true, Gt);                \
-        else MG_BWD(false, false, Gt);                       \
+#define MG_BWD(V, Al, Gt, Fu) \
+    hipExtLaunchKernelGGL((backward_kernel<V, Al, Gt, Fu>), grd, blk, 0, stream, ev.start, ev.stop, 0, p)
+#define MG_BWD_FUSED(V, Al, Gt) \
+    if (single_launch) MG_BWD(V, Al, Gt, true); else MG_BWD(V, Al, Gt, false)
+#define MG_BWD_TYPE(Gt)                                                             \
+    if (bt.vec) {                                                                   \
+        if (aligned) { MG_BWD_FUSED(true, true, Gt); } else { MG_BWD_FUSED(true, false, Gt); }   \
+    } else {                                                                        \
+        if (aligned) { MG_BWD_FUSED(false, true, Gt); } else { MG_BWD_FUSED(false, false, Gt); } \
     }
     if (grad_is_double) { MG_BWD_TYPE(double) } else { MG_BWD_TYPE(float) }
 #undef MG_BWD_TYPE
+#undef MG_BWD_FUSED
 #undef MG_BWD
     return hipGetLastError();
 }

@@ -124,6 +124,20 @@ struct Batch {
     const float   *translations;  // [B][3] or null
 };
 
+// The caller's arrays, for the single-launch paths of small problems (no prep kernel, no tables).
+struct RawInputs {
+    const float *coords;
+    const int32_t *types;
+    const float *radii;
+    const int32_t *natoms;
+    const float *centers, *quats, *translations;
+};
+
+inline RawInputs raw_inputs(const Batch &bt)
+{
+    return RawInputs{bt.coords, bt.types, bt.radii, bt.natoms, bt.centers, bt.quats, bt.translations};
+}
+
 // Geometry of the forward kernel: every wavefront owns one flat tile of
 // `tile_floats` consecutive floats of one channel (the last tile of a channel
 // may be shorter).
@@ -177,8 +191,9 @@ hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &
                           int keep_alive_stride = 1);
 hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace &ws,
                            const void *grad_out, bool grad_is_double, float *grad_coords,
-                           float *grad_weights, unsigned expect_tag, KernelEvents ev,
-                           hipStream_t stream);
+                           float *grad_weights, bool single_launch, unsigned expect_tag,
+                           KernelEvents ev, hipStream_t stream);
+bool backward_takes_single_launch(const Batch &bt);
 // grad[b] = sum over the sub3 virtual examples of b, in order (subgrids only)
 hipError_t launch_sum_subgrids(int subgrid_count, int B_source, size_t per_example,
                                const float *tmp, float *grad, hipStream_t stream);

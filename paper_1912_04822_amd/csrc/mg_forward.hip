@@ -74,15 +74,6 @@ constexpr unsigned kKeepAliveBytes = 256;       // what every wavefront re-reads
 constexpr float kFixedOne = 16777216.0f;        // 2^24
 constexpr float kFixedLimit = 120.0f;           // largest |sum| trusted to fixed point
 
-// The caller's arrays, for the single-launch path of small problems (no prep kernel, no tables).
-struct RawInputs {
-    const float *coords;
-    const int32_t *types;
-    const float *radii;
-    const int32_t *natoms;
-    const float *centers, *quats, *translations;
-};
-
 struct FwdParams {
     GridSpec gs;
     RawInputs raw;
@@ -1345,8 +1336,7 @@ hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &
     p.tag = ws.tag;
     p.expect_tag = single_launch ? 0u : expect_tag;
     p.groups = 0;
-    p.raw.coords = bt.coords; p.raw.types = bt.types; p.raw.radii = bt.radii; p.raw.natoms = bt.natoms;
-    p.raw.centers = bt.centers; p.raw.quats = bt.quats; p.raw.translations = bt.translations;
+    p.raw = raw_inputs(bt);
     p.out = out;
     p.subgrids = bt.sub.count; p.N = bt.N; p.T = bt.T;
     p.tile_floats = fg.tile_floats;
