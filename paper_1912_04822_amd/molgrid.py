@@ -123,21 +123,28 @@ def mg_time_next_kernel(start_event: Optional[int], stop_event: Optional[int]) -
 
 
 def _ptr(t: Optional[torch.Tensor], dtype, name: str, shape=None):
+    """Address of a device tensor after its checks (an int, or None for a missing array)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(t.shape)))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# torch's own short way to the current stream's handle, without building a Stream object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream() -> int:
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def mg_transform_forward(coords, centers=None, quats=None, translations=None, out=None):
@@ -214,6 +221,7 @@ class GridMaker:
         # workspaces the binding allocated, one per (device, stream): calls on different
         # streams may run at the same time and must not share tables
         self._ws = {}
+        self._need = (None, 0)      # the last (B, N, T) asked for and its workspace size
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -233,11 +241,17 @@ class GridMaker:
         D, S = self.D, self.S
         return (B, T, D, D, D) if S == 1 else (B, S, S, S, T, D, D, D)
 
-    def _workspace(self, B, N, T, device, workspace):
-        need = self.workspace_bytes(B, N, T)
+    def _workspace(self, B, N, T, device, workspace, stream):
+        """The caller's workspace or this GridMaker's for the stream (the caller of this holds the
+        tensor until its kernels are enqueued: another thread may put a larger one in its place)."""
         if workspace is not None:
+            self.workspace_bytes(B, N, T)       # raises for shapes no call takes
             return workspace, workspace.numel() * workspace.element_size()
-        key = (str(device), torch.cuda.current_stream().cuda_stream)    # the stream the call uses
+        last, need = self._need
+        if last != (B, N, T):
+            need = self.workspace_bytes(B, N, T)
+            self._need = ((B, N, T), need)
+        key = (device, stream)
         ws = self._ws.get(key)
         if ws is None or ws.numel() < need:
             ws = torch.empty(need, dtype=torch.uint8, device=device)
@@ -246,6 +260,8 @@ class GridMaker:
 
     def _common(self, coords, natoms, centers, quats, translations):
         B, N, _ = coords.shape
+        if centers is None and quats is None and translations is None and natoms is None:
+            return B, N, _ptr(coords, torch.float32, "coords", (B, N, 3)), None, None, None, None
         return (B, N, _ptr(coords, torch.float32, "coords", (B, N, 3)),
                 _ptr(natoms, torch.int32, "natoms", (B,)),
                 _ptr(centers, torch.float32, "centers", (B, 3)),
@@ -256,17 +272,16 @@ class GridMaker:
                          translations=None, out=None, workspace=None, dtype=torch.float32):
         """``dtype`` (or ``out.dtype``) torch.float64 calls ``mg_forward_index_f64``."""
         B, N, pc, pn, pce, pq, pt = self._common(coords, natoms, centers, quats, translations)
-        D = self.D
         if out is None:
             out = torch.empty(self.grid_shape(B, T), dtype=dtype, device=coords.device)
-        ws, wsb = self._workspace(B, N, T, coords.device, workspace)
+        st = _stream()
+        ws, wsb = self._workspace(B, N, T, coords.device, workspace, st)
         rshape = (T,) if self.radius_type_indexed else (B, N)
         fn = lib().mg_forward_index_f64 if out.dtype == torch.float64 else lib().mg_forward_index
         rc = fn(
             self._h, B, N, T, pc, _ptr(types, torch.int32, "types", (B, N)),
             _ptr(radii, torch.float32, "radii", rshape), pn, pce, pq, pt,
-            _ptr(out, out.dtype, "out", self.grid_shape(B, T)), ctypes.c_void_p(ws.data_ptr()), wsb,
-            _stream())
+            _ptr(out, out.dtype, "out", self.grid_shape(B, T)), ws.data_ptr(), wsb, st)
         if rc != MG_OK:
             raise MolgridError(rc, "mg_forward_index")
         return out
@@ -289,16 +304,15 @@ class GridMaker:
                           translations=None, out=None, workspace=None, dtype=torch.float32):
         B, N, pc, pn, pce, pq, pt = self._common(coords, natoms, centers, quats, translations)
         T = weights.shape[2]
-        D = self.D
         if out is None:
             out = torch.empty(self.grid_shape(B, T), dtype=dtype, device=coords.device)
-        ws, wsb = self._workspace(B, N, T, coords.device, workspace)
+        st = _stream()
+        ws, wsb = self._workspace(B, N, T, coords.device, workspace, st)
         fn = lib().mg_forward_vector_f64 if out.dtype == torch.float64 else lib().mg_forward_vector
         rc = fn(
             self._h, B, N, T, pc, _ptr(weights, torch.float32, "weights", (B, N, T)),
             _ptr(radii, torch.float32, "radii", (T,)), pn, pce, pq, pt,
-            _ptr(out, out.dtype, "out", self.grid_shape(B, T)), ctypes.c_void_p(ws.data_ptr()), wsb,
-            _stream())
+            _ptr(out, out.dtype, "out", self.grid_shape(B, T)), ws.data_ptr(), wsb, st)
         if rc != MG_OK:
             raise MolgridError(rc, "mg_forward_vector")
         return out
@@ -306,10 +320,10 @@ class GridMaker:
     def mg_backward_index(self, coords, types, radii, T, grad_out, natoms=None, centers=None,
                           quats=None, translations=None, grad_coords=None, workspace=None):
         B, N, pc, pn, pce, pq, pt = self._common(coords, natoms, centers, quats, translations)
-        D = self.D
         if grad_coords is None:
             grad_coords = torch.empty((B, N, 3), dtype=torch.float32, device=coords.device)
-        ws, wsb = self._workspace(B, N, T, coords.device, workspace)
+        st = _stream()
+        ws, wsb = self._workspace(B, N, T, coords.device, workspace, st)
         rshape = (T,) if self.radius_type_indexed else (B, N)
         fn = (lib().mg_backward_index_f64 if grad_out.dtype == torch.float64
               else lib().mg_backward_index)
@@ -318,7 +332,7 @@ class GridMaker:
             _ptr(radii, torch.float32, "radii", rshape), pn, pce, pq, pt,
             _ptr(grad_out, grad_out.dtype, "grad_out", self.grid_shape(B, T)),
             _ptr(grad_coords, torch.float32, "grad_coords", (B, N, 3)),
-            ctypes.c_void_p(ws.data_ptr()), wsb, _stream())
+            ws.data_ptr(), wsb, st)
         if rc != MG_OK:
             raise MolgridError(rc, "mg_backward_index")
         return grad_coords
@@ -328,12 +342,12 @@ class GridMaker:
                            want_coords=True, want_weights=True, workspace=None):
         B, N, pc, pn, pce, pq, pt = self._common(coords, natoms, centers, quats, translations)
         T = weights.shape[2]
-        D = self.D
         if grad_coords is None and want_coords:
             grad_coords = torch.empty((B, N, 3), dtype=torch.float32, device=coords.device)
         if grad_weights is None and want_weights:
             grad_weights = torch.empty((B, N, T), dtype=torch.float32, device=coords.device)
-        ws, wsb = self._workspace(B, N, T, coords.device, workspace)
+        st = _stream()
+        ws, wsb = self._workspace(B, N, T, coords.device, workspace, st)
         fn = (lib().mg_backward_vector_f64 if grad_out.dtype == torch.float64
               else lib().mg_backward_vector)
         rc = fn(
@@ -342,7 +356,7 @@ class GridMaker:
             _ptr(grad_out, grad_out.dtype, "grad_out", self.grid_shape(B, T)),
             _ptr(grad_coords, torch.float32, "grad_coords", (B, N, 3)),
             _ptr(grad_weights, torch.float32, "grad_weights", (B, N, T)),
-            ctypes.c_void_p(ws.data_ptr()), wsb, _stream())
+            ws.data_ptr(), wsb, st)
         if rc != MG_OK:
             raise MolgridError(rc, "mg_backward_vector")
         return grad_coords, grad_weights
@@ -361,7 +375,7 @@ class GridMaker:
         rc = lib().mg_prepare(
             self._h, B, N, T, pc, _ptr(types, torch.int32, "types", (B, N)),
             _ptr(radii, torch.float32, "radii", rshape), pn, pce, pq, pt,
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _stream())
         if rc != MG_OK:
             raise MolgridError(rc, "mg_prepare")
@@ -372,7 +386,7 @@ class GridMaker:
             out = torch.empty(self.grid_shape(B, T), dtype=torch.float32, device=workspace.device)
         rc = lib().mg_forward_index_prepared(
             self._h, B, N, T, _ptr(out, torch.float32, "out", self.grid_shape(B, T)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _stream())
         if rc != MG_OK:
             raise MolgridError(rc, "mg_forward_index_prepared")
@@ -386,7 +400,7 @@ class GridMaker:
             self._h, B, N, T, _ptr(weights, torch.float32, "weights", (B, N, T)),
             _ptr(radii, torch.float32, "radii", (T,)),
             _ptr(out, torch.float32, "out", self.grid_shape(B, T)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _stream())
         if rc != MG_OK:
             raise MolgridError(rc, "mg_forward_vector_prepared")
@@ -399,7 +413,7 @@ class GridMaker:
             self._h, B, N, T,
             _ptr(grad_out, torch.float32, "grad_out", self.grid_shape(B, T)),
             _ptr(grad_coords, torch.float32, "grad_coords", (B, N, 3)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _stream())
         if rc != MG_OK:
             raise MolgridError(rc, "mg_backward_index_prepared")
@@ -418,7 +432,7 @@ class GridMaker:
             _ptr(grad_out, torch.float32, "grad_out", self.grid_shape(B, T)),
             _ptr(grad_coords, torch.float32, "grad_coords", (B, N, 3)),
             _ptr(grad_weights, torch.float32, "grad_weights", (B, N, T)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
             _stream())
         if rc != MG_OK:
             raise MolgridError(rc, "mg_backward_vector_prepared")
