@@ -320,13 +320,15 @@ int mg_last_hip_error(void);
  *                     the grid is streamed out
  *   "keep_alive_stride" 1, 2, 4 or 8 (default 1): only one wavefront in that many
  *                     does the keep-alive read
- *   "single_launch"   0 or 1 (default 1): index types into a float grid with at most
- *                     256 atoms per example and 2048 in the batch run as ONE kernel
- *                     launch (every tile's wavefront transforms, culls and filters the
- *                     example's atoms itself; no prep kernel, the workspace is not
- *                     touched); 0 = always the prep kernel and its tables.  Binary
- *                     grids are the same to the bit either way, real ones to rounding.
- *                     Backward calls without subgrids likewise up to 49152 atoms in
+ *   "single_launch"   0 or 1 (default 1): small problems run as ONE kernel launch
+ *                     (no prep kernel, the workspace is not touched).  Forward, index
+ *                     types into a float grid without subgrids: at most 2048 atoms per
+ *                     example and 4 to 8 million voxels, or 256 atoms per example and
+ *                     2048 in the batch, and neither "tile_floats" nor "waves_per_tile"
+ *                     set: every tile's workgroup places the example's atoms itself.
+ *                     0 = always the prep kernel and its tables.  Binary grids are the
+ *                     same to the bit either way, real ones to rounding.  Backward
+ *                     calls without subgrids likewise up to 49152 atoms in
  *                     all (vector types 8192): gradients are the same to the bit
  *   "tile_order"      0 or 1 (default 0): 0 = all tiles of a channel, then the
  *                     next channel; 1 = tile k of every channel, then tile k+1

@@ -288,9 +288,9 @@ static int forward_call(const mg_gridmaker *gm, int B, int N, int T, const float
     const mg::Workspace ws = mg::carve_workspace(gm->gs, gm->sub.count, workspace, bt.B, N, T);
     const auto knob = [](const std::atomic<int> &k) { return k.load(std::memory_order_relaxed); };
     const int stop = timing_prep_stop();
-    // a few hundred atoms in all: one launch, every tile looks at the atoms itself
+    // small problems: one launch, every tile looks at the atoms itself (its tile shapes are fixed)
     const bool single = tables == Tables::kBuildAndRun && knob(g_single_launch) != 0 && stop == 0 &&
-                        timing_debug() == 0 && mg::forward_takes_single_launch(bt, out_is_double);
+                        timing_debug() == 0 && knob(g_tile_floats) == 0 && knob(g_waves_per_tile) == 0 && mg::forward_takes_single_launch(gm->gs, bt, out_is_double);
     if (tables != Tables::kUseBuilt && !single) {
         rc = hip_status(mg::launch_prep(gm->gs, bt, ws, stop, (hipStream_t)stream));
         if (rc != MG_OK || stop != 0) return rc;    // a prep kernel cut short leaves no tables to read

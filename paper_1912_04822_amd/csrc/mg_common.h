@@ -178,10 +178,10 @@ unsigned workspace_tag(const GridSpec &gs, const Batch &bt);
 hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws, int stop,
                        hipStream_t stream);
 // Small problems (index types, float grid): the forward kernel alone, no prep kernel -- every
-// tile's wavefront transforms, culls and filters the example's atoms itself.
-constexpr int kSmallAtoms = 256;        // most atoms per example
-constexpr int kSmallTotal = 2048;       // most atoms in the batch
-bool forward_takes_single_launch(const Batch &bt, bool out_is_double);
+// tile's workgroup transforms, culls and filters the example's atoms itself.
+constexpr int kSmallAtoms = 256;        // one wavefront looking at all of them: most atoms per example
+constexpr int kSmallTotal = 2048;       // ... and in the batch
+bool forward_takes_single_launch(const GridSpec &gs, const Batch &bt, bool out_is_double);
 // expect_tag != 0 (a *_prepared call): the kernel returns at once, writing nothing, unless the
 // workspace's tag equals it
 hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &ws,

@@ -70,6 +70,7 @@ namespace mg {
 namespace {
 
 constexpr int kTaskCap = 256;                   // (atom, row) tasks staged per round
+constexpr int kFusedAtoms = 2048;               // single launch: most atoms a workgroup of several wavefronts looks through
 constexpr unsigned kKeepAliveBytes = 256;       // what every wavefront re-reads of the tables by default
 constexpr float kFixedOne = 16777216.0f;        // 2^24
 constexpr float kFixedLimit = 120.0f;           // largest |sum| trusted to fixed point
@@ -474,9 +475,11 @@ __device__ inline TileGeom tile_geom(const FwdParams &p, int D, unsigned tile_in
 // FUSED (small problems, index types): there are no records; the "records" [r0, r1) are the
 // example's atoms themselves, and a lane transforms, culls and filters by type the atom it takes,
 // with the arithmetic and the tests of the prep kernel.
+// With more than one wavefront `list` names the atoms of type t (find_atoms).
 template <bool BINARY, bool ALIGNED, int ITERS, int NW, typename OUT, bool FUSED = false>
 __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b, int t,
-                                          const TileGeom &tg, int r0, int r1, const float4 &cen)
+                                          const TileGeom &tg, int r0, int r1, const float4 &cen,
+                                          const unsigned short *list = nullptr)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const GridSpec &gs = p.gs;
@@ -539,7 +542,8 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
     };
     auto fetch_raw = [&](int base) {
         RawAtom ra;
-        const int ec = min(base + lane * nsplit + sub, count - 1);      // count >= 1 here
+        int ec = min(base + lane * nsplit + sub, count - 1);            // count >= 1 here
+        if (NW > 1) ec = list[ec];
         ra.te = p.raw.types[(size_t)b * N + ec];
         const float *c3 = p.raw.coords + ((size_t)b * N + ec) * 3;
         ra.cc[0] = c3[0]; ra.cc[1] = c3[1]; ra.cc[2] = c3[2];
@@ -676,6 +680,43 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
 }
 
 
+// The atoms of type t among the first n (at most kFusedAtoms) of an example, in order, into `list`
+// (LDS); every wavefront looks at its own run of them.  Returns how many there are.
+template <int NW>
+__device__ inline int find_atoms(const int32_t *types, int n, int t, unsigned short *list, unsigned short *counts)
+{
+    constexpr int kPer = kFusedAtoms / (64 * NW);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int first = wave * (64 * kPer);
+    int v[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int a = first + k * 64 + lane;
+        v[k] = a < n ? types[a] : -1;           // t >= 0
+    }
+    int mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) mine += (int)__builtin_popcountll(__ballot(v[k] == t));
+    if (lane == 0) counts[wave] = (unsigned short)mine;
+    __syncthreads();
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int c = counts[w];
+        if (w < wave) at += c;
+        total += c;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const unsigned long long m = __ballot(v[k] == t);
+        if (v[k] == t)
+            list[at + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = (unsigned short)(first + k * 64 + lane);
+        at += (int)__builtin_popcountll(m);
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(total);
+}
+
 // One workgroup per tile.  OUT: float, or double for a grid of doubles.
 template <bool BINARY, bool ALIGNED, int ITERS, int NW, typename OUT, bool FUSED = false>
 __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
@@ -737,7 +778,13 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
             n = p.raw.natoms[b];
             n = n < 0 ? 0 : (n > N ? N : n);
         }
-        tile_body<BINARY, ALIGNED, ITERS, NW, OUT, true>(p, lds, b, t, tgf, 0, n, cenf);
+        const unsigned short *list = nullptr;
+        if (NW > 1) {
+            unsigned short *out = reinterpret_cast<unsigned short *>(lds + ITERS * 512 + NW * (kTaskCap / 4) + 4);
+            n = find_atoms<NW>(p.raw.types + (size_t)b * N, n, t, out, out + kFusedAtoms);
+            list = out;
+        }
+        tile_body<BINARY, ALIGNED, ITERS, NW, OUT, true>(p, lds, b, t, tgf, 0, n, cenf, list);
         return;
     }
     const size_t group = (size_t)b * T + t;
@@ -1280,12 +1327,35 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
     return hipGetLastError();
 }
 
-bool forward_takes_single_launch(const Batch &bt, bool out_is_double)
+// Small problems (index types into a float grid, no subgrids) in one launch: floats per
+// tile (negative: its type's atoms are listed first), 0 where the prep kernel and its tables are quicker.
+//   * up to 64 atoms: 1024, one wavefront that looks at all of them in one round;
+//   * else, up to 2048 atoms: several wavefronts that first list the tile's type (find_atoms).
+//     Tiles of about two x-planes, so that the atoms found need one round: 1024 (two wavefronts)
+//     below 37 points a side, else 4096 (four); 2048 where that leaves less than three workgroups
+//     per CU and a tile more than one plane.
+//     Listing and placing the atoms per tile costs 7 us per 3.1 M voxels at 2040 atoms against the
+//     10 us and more of the prep kernel: up to 8 M voxels (4 M with the small tiles).
+// Whole calls, one launch / prep kernel and tables, us: 100 atoms, 4 x 24^3: 9.6 / 16 (one wavefront
+// that looks at all atoms: 13); 2040 atoms, 28 x 48^3: 12.5 / 18.3 (with 4096: 13.5), two of them 18.0 /
+// 20.2 (with 2048: 19.1), three 22.8 / 22.7; 1000 atoms, 14 x 64^3: 11.1 / 16.6; 20 x 200 atoms, 12 x
+// 24^3: 16.3 / 18.9; 40 x 600 atoms, 12 x 16^3: 14.7 / 21.2 (with 4096: 22).
+static int single_launch_tile(const GridSpec &gs, const Batch &bt, bool out_is_double)
 {
-    // index types into a float grid, no subgrids, at most kSmallAtoms atoms per example and
-    // kSmallTotal in all: every tile's wavefront can afford to look at all of them itself
-    return !bt.vec && !out_is_double && bt.sub.count == 1 && bt.N <= kSmallAtoms &&
-           (long long)bt.B * bt.N <= kSmallTotal;
+    if (bt.vec || out_is_double || bt.sub.count != 1 || bt.N > kFusedAtoms) return 0;
+    const long long voxels = (long long)bt.B * bt.T * gs.D * gs.D * gs.D;
+    const bool large = gs.D >= 37;
+    if (bt.N > 64 && voxels <= (large ? 8LL << 20 : 4LL << 20)) {
+        if (!large) return -1024;
+        const long long wgs = (long long)bt.B * bt.T * forward_geometry(gs.D, 4096).tiles;
+        return wgs < 768 && gs.D < 64 ? -2048 : -4096;
+    }
+    return bt.N <= kSmallAtoms && (long long)bt.B * bt.N <= kSmallTotal ? 1024 : 0;
+}
+
+bool forward_takes_single_launch(const GridSpec &gs, const Batch &bt, bool out_is_double)
+{
+    return single_launch_tile(gs, bt, out_is_double) != 0;
 }
 
 hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &ws, void *out,
@@ -1298,9 +1368,12 @@ hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &
                                      stream);
     if (tile_floats == 512) tile_floats = 1024;     // the smallest tile of these kernels
     if (waves_per_tile == 0) waves_per_tile = 1;
-    if (single_launch) {        // one shape only: 4 KB tiles, one wavefront, ids in order
-        tile_floats = 1024;
-        waves_per_tile = 1;
+    bool find = false;          // single launch with find_atoms
+    if (single_launch) {        // ids in order
+        tile_floats = single_launch_tile(gs, bt, out_is_double);
+        find = tile_floats < 0;
+        if (find) tile_floats = -tile_floats;
+        waves_per_tile = !find ? 1 : (tile_floats == 1024 ? 2 : 4);
         xcd_run = 0;
         tile_order = 0;
         keep_alive = 0;
@@ -1382,6 +1455,7 @@ hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &
     // tile | marks of each wavefront | shared words; lds_floor raises the request to cap how
     // many tiles are resident on a CU
     size_t lds_bytes = (size_t)tile_floats * sizeof(float) + (size_t)nw * kTaskCap + 16;
+    if (find) lds_bytes += (kFusedAtoms + 8) * sizeof(unsigned short);
     // 4 KB tiles, one wavefront each: 26 per CU (104 KB of stores in flight) instead of all 32
     // slots measured 98.2 us against 102.4 us on the 48^3 batch (22 to 30 per CU alike)
     if (lds_floor < 0) lds_floor = (tile_floats == 1024 && nw == 1 && !out_is_double && !bt.vec) ? 6144 : 0;
@@ -1406,12 +1480,20 @@ hipError_t launch_forward(const GridSpec &gs, const Batch &bt, const Workspace &
     default: return hipErrorInvalidValue;                                       \
     }
     if (single_launch) {
-#define MG_FUSED(Bn, Al) \
-    hipExtLaunchKernelGGL((forward_kernel<Bn, Al, 2, 1, float, true>), grd, blk, (uint32_t)lds_bytes, \
-                          stream, ev.start, ev.stop, 0, p)
+#define MG_FUSED1(Bn, Al, It, Nw)                                                             \
+    hipExtLaunchKernelGGL((forward_kernel<Bn, Al, It, Nw, float, true>), grd, blk,            \
+                          (uint32_t)lds_bytes, stream, ev.start, ev.stop, 0, p)
+#define MG_FUSED(Bn, Al)                                                                      \
+    do {                                                                                      \
+        if (nw == 1) MG_FUSED1(Bn, Al, 2, 1);                                                 \
+        else if (nw == 2) MG_FUSED1(Bn, Al, 2, 2);                                            \
+        else if (iters == 4) MG_FUSED1(Bn, Al, 4, 4);                                         \
+        else MG_FUSED1(Bn, Al, 8, 4);                                                         \
+    } while (0)
         if (gs.binary) { if (aligned) MG_FUSED(true, true); else MG_FUSED(true, false); }
         else           { if (aligned) MG_FUSED(false, true); else MG_FUSED(false, false); }
 #undef MG_FUSED
+#undef MG_FUSED1
     } else {
         if (gs.binary) { if (aligned) MG_LAUNCH(true, true) else MG_LAUNCH(true, false) }
         else           { if (aligned) MG_LAUNCH(false, true) else MG_LAUNCH(false, false) }
