@@ -74,6 +74,9 @@ constexpr int kFusedAtoms = 2048;               // single launch: most atoms a w
 constexpr unsigned kKeepAliveBytes = 256;       // what every wavefront re-reads of the tables by default
 constexpr float kFixedOne = 16777216.0f;        // 2^24
 constexpr float kFixedLimit = 120.0f;           // largest |sum| trusted to fixed point
+// Vector types: steps of 2^-25 -- as unsigned numbers up to 128 where no weight of the tile is
+// negative, as signed ones up to 64 otherwise.
+constexpr int kVecFixedBits = 25;
 
 struct FwdParams {
     GridSpec gs;
@@ -106,6 +109,7 @@ struct FwdParams {
     float inv_sk;
     float g2k, c2k;     // g^2 k, c^2 k
     float sA, cA;       // tail coefficients
+    float vg2k, tk, tc; // vector types: g^2 k, 2g/sqrt(k), 2g c
 };
 
 // what a wavefront keeps for the tile it is working on (all wave-uniform)
@@ -142,7 +146,6 @@ __device__ inline unsigned div_u32(unsigned x, unsigned long long magic)
 // One atom of the current batch as its lane holds it.
 struct Atom {
     float4 a;           // x', y', z', r
-    float w;            // weight (vector types), else 1
     bool valid;
 };
 
@@ -318,15 +321,9 @@ __device__ inline PairHit pair_test(const TileCtx &cx, const FwdParams &p, const
 }
 
 // What the hits of this wavefront can add to one voxel at most (rho <= 1), in 1/256.
-template <bool VECTOR>
-__device__ inline int pair_bound(const PairHit &h, const Atom &at)
+__device__ inline int pair_bound(const PairHit &h)
 {
-    const bool hit = h.nA + h.nB > 0;
-    if (VECTOR) {       // each weight rounded up to 1/256, summed exactly by DPP adds (no LDS traffic)
-        const int mine = hit ? (int)ceilf(fminf(fabsf(at.w), 4096.0f) * 256.0f) : 0;
-        return bcast(wave_inclusive_scan(mine), 63);
-    }
-    return 256 * (int)__builtin_popcountll(__ballot(hit));
+    return 256 * (int)__builtin_popcountll(__ballot(h.nA + h.nB > 0));
 }
 
 // Stage the tasks of the hits (rows of plane A, then rows of plane B, atom after atom)
@@ -363,9 +360,15 @@ __device__ inline bool pair_run(const TileCtx &cx, PairHit &h, bool fixed)
 
 // Stream the finished tile to HBM (zeros if no atom touched it).  ITERS = tile_floats / 512
 // chunks of 2 KB; wavefront w of NW takes chunks w, w + NW, ...
-template <bool ALIGNED, int ITERS, int NW, typename OUT>
-__device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed)
+// VECTOR: fixed point is unsigned unless `neg`, in steps of 2^-kVecFixedBits.
+template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false>
+__device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed, bool neg = true)
 {
+    const auto value = [&](float bits) {
+        const int i = __float_as_int(bits);
+        if (VECTOR) return (neg ? (float)i : (float)(unsigned)i) * (1.0f / (float)(1 << kVecFixedBits));
+        return (float)i * (1.0f / kFixedOne);
+    };
     constexpr bool kWide = sizeof(OUT) == 8;        // a grid of doubles: the same values, widened
     if (ALIGNED && kWide) {
         // Doubles: every store instruction writes 1 KB in one piece (lane l its 16 bytes at
@@ -383,9 +386,7 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
                 const int o = ((it * NW + cx.wave) * 4 + k) * 64 + cx.lane;
                 v[k] = touched ? src2[o] : make_float2(0.0f, 0.0f);
                 if (convert) {
-                    const float sc = 1.0f / kFixedOne;
-                    v[k] = make_float2((float)__float_as_int(v[k].x) * sc,
-                                       (float)__float_as_int(v[k].y) * sc);
+                    v[k] = make_float2(value(v[k].x), value(v[k].y));
                 }
             }
 #pragma unroll
@@ -420,11 +421,8 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
         for (int it = 0; it < MINE; ++it) {
             float4 a = v[2 * it], b = v[2 * it + 1];
             if (convert) {
-                const float sc = 1.0f / kFixedOne;
-                a = make_float4((float)__float_as_int(a.x) * sc, (float)__float_as_int(a.y) * sc,
-                                (float)__float_as_int(a.z) * sc, (float)__float_as_int(a.w) * sc);
-                b = make_float4((float)__float_as_int(b.x) * sc, (float)__float_as_int(b.y) * sc,
-                                (float)__float_as_int(b.z) * sc, (float)__float_as_int(b.w) * sc);
+                a = make_float4(value(a.x), value(a.y), value(a.z), value(a.w));
+                b = make_float4(value(b.x), value(b.y), value(b.z), value(b.w));
             }
             const int o = (it * NW + cx.wave) * 128 + cx.lane * 2;
             if (o < n4) {
@@ -443,8 +441,7 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
         for (int o = cx.wave * 64 + cx.lane; o < cx.n; o += 64 * NW) {
             float v = 0.0f;
             if (touched)
-                v = fixed ? (float)reinterpret_cast<const int *>(cx.tile)[o] * (1.0f / kFixedOne)
-                          : cx.tile[o];
+                v = fixed ? value(cx.tile[o]) : cx.tile[o];
             dst[o] = (OUT)v;
         }
     }
@@ -553,7 +550,6 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
     auto finish_raw = [&](const RawAtom &ra, int e) {
         Atom at;
         at.a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        at.w = 1.0f;
         if (e < count && ra.te == t) {
             float pp[3];
             apply_xform(X, ra.cc, pp);
@@ -573,7 +569,6 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
         const int e = base + lane * nsplit + sub;
         Atom at;
         at.a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        at.w = 1.0f;
         if (FUSED) return finish_raw(fetch_raw(base), e);
         if (e < count) at.a = rec[e];
         at.valid = (e < count) && (at.a.w > 0.0f);
@@ -620,7 +615,7 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
             for (int iA = pA0; iA <= pA1; iA += 2) {
                 PairHit h = test_pair(at, iA);
                 if (!BINARY && fixed) {
-                    bound += min(pair_bound<false>(h, at), 1 << 24);
+                    bound += min(pair_bound(h), 1 << 24);
                     if (bound > limit) {
                         fixed = false;
                         for (int o = lane; o < ITERS * 512; o += 64)
@@ -642,13 +637,13 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
         int bound = 0;
         if (single) {
             h0 = test_pair(at0, pA0);
-            if (!BINARY && !short_span) bound = pair_bound<false>(h0, at0);
+            if (!BINARY && !short_span) bound = pair_bound(h0);
         } else if (!BINARY && !short_span) {
             for (int base = 0; base < count && bound <= limit; base += 64 * nsplit) {
                 const Atom at = base == 0 ? at0 : load_atom(base);
                 for (int iA = pA0; iA <= pA1; iA += 2) {
                     const PairHit h = test_pair(at, iA);
-                    bound += min(pair_bound<false>(h, at), 1 << 24);   // past the limit the value does not matter
+                    bound += min(pair_bound(h), 1 << 24);   // past the limit the value does not matter
                 }
             }
         }
@@ -819,10 +814,13 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
 // formula, so the voxels of the widest sphere that a narrower one does not reach add nothing.
 // The channels are taken in order of radius (chan_order, written by the prep kernel), so the
 // spheres of a group are nearly the same size.
-//   Gaussian  w exp2(-x'^2_q)          = sgn exp2(log2|w| - ratio2_q x'^2)
-//   tail      w (sqrt(x'^2_q) sA - cA)^2 = sgn (s sqrt|w| sA ratio_q - sqrt|w| cA)^2,  s = sqrt(x'^2)
-// log2|w|, sqrt|w| sA ratio_q and sqrt|w| cA are worked out once per atom (in the lane that
-// holds the atom) and fetched by the lanes that walk its chords.
+// The Gaussian and the quadratic tail are taken as a product, without a select between them:
+//   rho(x) = exp(-2 min(x, g)^2) clamp(2g (c - x), 0, 1)^2
+// (2g (c - g) = 1 and A = 4 g^2 exp(-2 g^2), so the second factor is 1 up to g and the tail's
+// A (x - c)^2 over exp(-2 g^2) beyond), the weight as an exponent:
+//   |w| rho_q = exp2(max(log2|w| - ratio2_q x'^2, log2|w| - g^2 k)) clamp(2gc - s tq_q, 0, 1)^2,
+// s = sqrt(x'^2).  log2|w| is worked out once per atom (in the lane that holds the atom) and
+// fetched by the lanes that walk its chords; it is all a chord needs per channel.
 // ---------------------------------------------------------------------------
 constexpr int kVecGroup = 4;
 
@@ -830,23 +828,14 @@ struct VecGroup {           // wave-uniform: the channels of this workgroup
     int chan[kVecGroup];        // channel index (for dead slots: any valid channel)
     bool live[kVecGroup];       // slot q holds a channel with a positive radius
     float ratio2[kVecGroup];    // (rmax / r_q)^2
-    float sAq[kVecGroup];       // sA rmax / r_q
-    float thq[kVecGroup];       // Gaussian region of channel q: x'^2 <= g^2 k / ratio2_q
+    float tq[kVecGroup];        // 2g/sqrt(k) rmax / r_q
     float r2[kVecGroup];        // binary mode: r_q * r_q (float, as the predicate's right-hand side)
     float rmax;
+    float g2k, tc;              // g^2 k; 2g c
 };
 
-// Fixed-point tiles: sqrt(|w| rho) of a tail is at most sqrt(kFixedLimit) < 11 wherever the tail is
-// used, so divided by kVecTailScale it lies in [0, 1] and the multiply-add's clamp (to [0, 1], free)
-// replaces the min that cuts the tail off at the cutoff; the Gaussian's exponent carries the same
-// factor (squared), and the conversion to fixed point multiplies it back.
-constexpr float kVecTailScale = 16.0f;
-static_assert(kVecTailScale * kVecTailScale >= kFixedLimit, "the scaled tail root must stay in [0, 1]");
-
-struct VecAtom {            // per atom, per channel of the group (fixed point: see kVecTailScale)
-    float lw[kVecGroup];        // log2 |w_q|  (-inf for w_q = 0: the Gaussian is then 0); fixed: - 8
-    float su[kVecGroup];        // sqrt|w_q| sA ratio_q; fixed: / 16
-    float sc[kVecGroup];        // sqrt|w_q| cA; fixed: / 16
+struct VecAtom {            // per atom, per channel of the group
+    float lw[kVecGroup];        // log2 |w_q|  (-inf for w_q = 0: the value is then 0); fixed point: + kVecFixedBits
     int neg;                    // bit q: w_q < 0  (binary mode: bit q: w_q > 0, the atom marks channel q)
 };
 
@@ -868,12 +857,11 @@ __device__ inline void run_tasks_group(const TileCtx &cx, const VecGroup &vg, co
         const float pxA = fetch(src, cd.pxA), pxB = fetch(src, cd.pxB);
         const int pack = __builtin_amdgcn_ds_bpermute(src, cd.pack);
         const int k = tau - __builtin_amdgcn_ds_bpermute(src, cd.start);   // row number within the atom
-        float lw[kVecGroup], su[kVecGroup], sc[kVecGroup];
+        float lw[kVecGroup], lwg[kVecGroup];
 #pragma unroll
         for (int q = 0; q < kVecGroup; ++q) {
             lw[q] = fetch(src, va.lw[q]);
-            su[q] = fetch(src, va.su[q]);
-            sc[q] = fetch(src, va.sc[q]);
+            lwg[q] = lw[q] - vg.g2k;
         }
         int sb[kVecGroup];
         if (SIGNED) {
@@ -901,27 +889,27 @@ __device__ inline void run_tasks_group(const TileCtx &cx, const VecGroup &vg, co
         const float z0 = (((float)klo - cx.hD) - fz) * stepk;
         const float fnz = (float)nz;
         float *q0 = rowp + klo;
+        float tc = vg.tc;
+        asm volatile("" : "+v"(tc));        // keep it in a VGPR across the loop
         for (float fi = 0.0f; fi < fnz; fi += 1.0f, ++q0) {
             const float zs = fmaf(fi, stepk, z0);
             const float x2 = fmaf(zs, zs, x2b);
             const float sx = __builtin_amdgcn_sqrtf(x2);
 #pragma unroll
             for (int q = 0; q < kVecGroup; ++q) {
-                const float e = __builtin_amdgcn_exp2f(fmaf(-vg.ratio2[q], x2, lw[q]));
-                // FIXED: the atom's constants carry 1/kVecTailScale (see VecAtom), so that the tail's
-                // root stays below 1 and the clamp of the multiply-add cuts it off at the cutoff
-                const float u = FIXED ? __builtin_amdgcn_fmed3f(fmaf(-sx, su[q], sc[q]), 0.0f, 1.0f)
-                                      : fminf(fmaf(sx, su[q], -sc[q]), 0.0f);
-                float val = x2 <= vg.thq[q] ? e : u * u;                    // |w_q| rho_q, 0 beyond the cutoff
-                if (SIGNED) val = __int_as_float(__float_as_int(val) | sb[q]);
+                const float e = __builtin_amdgcn_exp2f(__builtin_amdgcn_fmed3f(fmaf(-vg.ratio2[q], x2, lw[q]), lwg[q], lw[q]));
+                const float u = __builtin_amdgcn_fmed3f(fmaf(-sx, vg.tq[q], tc), 0.0f, 1.0f);
+                float u2 = u * u;                                           // 0 beyond the cutoff
+                if (SIGNED) u2 = __int_as_float(__float_as_int(u2) | sb[q]);
                 if (FIXED) {
-                    // |val| 2^24 + 1/2, truncated: rounded to the nearest fixed-point step
+                    // |w| rho 2^kVecFixedBits + 1/2, truncated: rounded to the nearest fixed-point step
                     const float half = SIGNED ? __int_as_float(0x3f000000 | sb[q]) : 0.5f;
-                    __hip_atomic_fetch_add(reinterpret_cast<int *>(q0) + q * stride,
-                                           (int)fmaf(val, kFixedOne * kVecTailScale * kVecTailScale, half),
+                    const float v = fmaf(e, u2, half);
+                    __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(q0) + q * stride, SIGNED ? (unsigned)(int)v : (unsigned)v,
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 } else {
-                    __hip_atomic_fetch_add(q0 + q * stride, val, __ATOMIC_RELAXED,
+                    // (a weight may be infinite here; beyond the cutoff it adds nothing all the same)
+                    __hip_atomic_fetch_add(q0 + q * stride, u > 0.0f ? e * u2 : 0.0f, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
@@ -1038,6 +1026,8 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     // the channels of this group and what depends on their radii only
     VecGroup vg;
     vg.rmax = 0.0f;
+    vg.g2k = p.vg2k;
+    vg.tc = p.tc;
     float rq[kVecGroup];
 #pragma unroll
     for (int q = 0; q < kVecGroup; ++q) {
@@ -1049,10 +1039,9 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     }
 #pragma unroll
     for (int q = 0; q < kVecGroup; ++q) {
-        const float ratio = vg.live[q] ? vg.rmax * __builtin_amdgcn_rcpf(rq[q]) : 1.0f;
+        const float ratio = vg.live[q] ? vg.rmax / rq[q] : 1.0f;
         vg.ratio2[q] = ratio * ratio;
-        vg.sAq[q] = p.sA * ratio;
-        vg.thq[q] = p.g2k * __builtin_amdgcn_rcpf(vg.ratio2[q]);
+        vg.tq[q] = p.tk * ratio;
         vg.r2[q] = vg.live[q] ? rq[q] * rq[q] : -1.0f;     // (nothing is within a dead channel's radius)
     }
 
@@ -1081,6 +1070,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 
     const size_t total = (size_t)D * D * D;
     OUT *out = reinterpret_cast<OUT *>(p.out);
+    bool negs = false;          // some weight of the tiles is negative
     auto store_all = [&](bool touched, bool fixed) {
 #pragma unroll
         for (int q = 0; q < kVecGroup; ++q) {
@@ -1088,7 +1078,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
             TileCtx cq = cx;
             cq.tile = lds + q * kTile;
             OUT *dst = out + ((size_t)b * T + vg.chan[q]) * total + tg.f0;
-            store_tile<ALIGNED, ITERS, NW, OUT>(cq, dst, touched && vg.live[q], fixed);
+            store_tile<ALIGNED, ITERS, NW, OUT, true>(cq, dst, touched && vg.live[q], fixed, negs);
         }
     };
     const int count = r1 - r0;
@@ -1152,35 +1142,40 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
             // this round's atom: what its chords will need, per channel
             Atom at;
             at.a = rc.a;
-            float wmax = 0.0f;
             VecAtom va;
+            int wb[kVecGroup];      // |w_q| rounded up to 1/256
             va.neg = 0;
+            bool wany = false;
 #pragma unroll
             for (int q = 0; q < kVecGroup; ++q) {
                 if (BINARY) {       // the atom marks the channels where its weight is positive
-                    va.lw[q] = 0.0f; va.su[q] = 0.0f; va.sc[q] = 0.0f;
+                    va.lw[q] = 0.0f;
                     va.neg |= (wc.w[q] > 0.0f ? 1 : 0) << q;
                     continue;
                 }
                 const float aw = fabsf(wc.w[q]);
-                wmax = fmaxf(wmax, aw);
-                const float sw = __builtin_amdgcn_sqrtf(aw) * (fixed ? 1.0f / kVecTailScale : 1.0f);
-                va.lw[q] = __builtin_amdgcn_logf(aw) - (fixed ? 8.0f : 0.0f);       // log2; 8 = log2 of the scale squared
-                va.su[q] = sw * vg.sAq[q];
-                va.sc[q] = sw * cx.cA;
+                wb[q] = aw > 0.0f ? (int)ceilf(fminf(aw, 4096.0f) * 256.0f) : 0;
+                wany = wany || aw > 0.0f;
+                va.lw[q] = __builtin_amdgcn_logf(aw) + (fixed ? (float)kVecFixedBits : 0.0f);       // log2
                 va.neg |= (wc.w[q] < 0.0f ? 1 : 0) << q;
             }
-            at.w = wmax;
-            at.valid = (rc.a.w > 0.0f) && (BINARY ? va.neg != 0 : wmax > 0.0f);
+            at.valid = (rc.a.w > 0.0f) && (BINARY ? va.neg != 0 : wany);
             at.a.w = vg.rmax;
             const bool any_neg = !BINARY && __ballot(at.valid && va.neg != 0) != 0ull;
+            negs = negs || any_neg;
             for (int iA = tg.i_lo; iA <= tg.i_hi; iA += 2) {
                 cx.rowA = iA * D - tg.R0;
                 cx.rowB = cx.rowA + D;
                 const int jaA = max(-cx.rowA, 0), jbA = min(tg.R1 - tg.R0 - cx.rowA, D);
                 const int jaB = max(-cx.rowB, 0), jbB = iA < tg.i_hi ? min(tg.R1 - tg.R0 - cx.rowB, D) : 0;
                 PairHit h = pair_test<BINARY>(cx, p, at, ox, iA, jaA, jbA, jaB, jbB);
-                if (!BINARY) bound = min(bound + min(pair_bound<true>(h, at), 1 << 24), 1 << 26);
+                if (!BINARY) {      // what these atoms can add to one voxel of the channel they add most to
+                    int most = 0;
+#pragma unroll
+                    for (int q = 0; q < kVecGroup; ++q)     // (summed exactly by DPP adds, no LDS traffic)
+                        most = max(most, bcast(wave_inclusive_scan(h.nA + h.nB > 0 ? wb[q] : 0), 63));
+                    bound = min(bound + min(most, 1 << 24), 1 << 26);
+                }
                 const bool ran = any_neg ? pair_run_group<BINARY, true>(cx, vg, h, va, kTile, fixed)
                                          : pair_run_group<BINARY, false>(cx, vg, h, va, kTile, fixed);
                 any = ran || any;
@@ -1200,13 +1195,14 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     if (NW > 1) {
         if (lane == 0) {
             atomicAdd(&cx.shared[0], bound);
-            if (any) cx.shared[1] = 1;
+            if (any) atomicOr(&cx.shared[1], negs ? 3 : 1);
         }
         __syncthreads();                    // every wavefront's additions are in the tiles
         bound = cx.shared[0];
         any = cx.shared[1] != 0;
+        negs = (cx.shared[1] & 2) != 0;
     }
-    if (!BINARY && bound > limit) {         // uniform over the workgroup: the sums may not fit; again, in floats
+    if (!BINARY && bound > (negs ? limit >> 1 : limit)) {       // uniform over the workgroup: the sums may not fit; again, in floats
         if (NW > 1) __syncthreads();        // shared[] has been read by all
         fixed = false;
         clear_tiles();
@@ -1289,6 +1285,11 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
     p.c2k = (float)((double)gs.c * (double)gs.c * k);
     p.sA = (float)std::sqrt((double)gs.A / k);
     p.cA = (float)((double)gs.c * std::sqrt((double)gs.A));
+    // (beyond x = 100 the density is 0 in float whatever the branch: larger g need no larger constants)
+    const double g2 = std::fmax(std::fmin((double)gs.g2, 1.0e4), 1.0e-30), gr = std::sqrt(g2);
+    p.vg2k = (float)(g2 * k);
+    p.tk = (float)(2.0 * gr / std::sqrt(k));
+    p.tc = (float)(2.0 * g2 + 1.0);
     const unsigned long long wgs = (unsigned long long)bt.B * p.groups * fg.tiles;
     if (wgs > 0x7fffffffULL) return hipErrorInvalidValue;
     // four wavefronts per workgroup by default: they share the tiles, so four times as many
