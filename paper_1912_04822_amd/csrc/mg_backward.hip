@@ -169,6 +169,15 @@ __device__ inline void load_slot(const BwdParams &p, const GT *Gc, unsigned row_
             const Float4E g4 = STREAM ? __builtin_nontemporal_load(s4) : *s4;
             d.gv[0] = g4.x; d.gv[1] = g4.y; d.gv[2] = g4.z; d.gv[3] = g4.w;
         }
+    } else if (p.gs.D >= 4) {
+        // Rows of any length: a slot that reaches past the row's end is read from the row's last four
+        // voxels, and those of them that belong to the slot before count as 0.
+        // (Four loads of a voxel each before: 178 instead of 85 us a call on 50 x 28 x 47^3.)
+        const int back = max(k4 - (p.gs.D - 4), 0);
+        load_slot<true, STREAM>(p, Gc, row_off, k4 - back, ux, uy, d);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) d.gv[u] = u < back ? 0.0f : d.gv[u];
+        return;
     } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -467,7 +476,8 @@ __device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kC
         for (int q = 0; q < kChanGroup; ++q)
             if (ALL_LIVE || gc.live[q]) load_slot<ALIGNED, false>(p, Gq[q], row_off, k4, ux, uy, d[q]);
         const float b2 = ux * ux + uy * uy;
-        const float uz0 = fmaf(-(float)k4, step, azs);
+        const int k0 = ALIGNED || p.gs.D < 4 ? k4 : min(k4, p.gs.D - 4);    // where load_slot began
+        const float uz0 = fmaf(-(float)k0, step, azs);
         float fsum = 0.0f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

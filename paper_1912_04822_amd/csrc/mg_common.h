@@ -145,7 +145,7 @@ struct ForwardGeometry {
     int tile_floats;    // 1024, 2048 or 4096
     int tiles;          // tiles per channel = ceil(D^3 / tile_floats)
 };
-ForwardGeometry forward_geometry(int D, int tile_floats);
+ForwardGeometry forward_geometry(int D, int tile_floats, bool shifted = false);
 
 constexpr int kRankCap = 256;           // most channels that are put in order of radius
 
