@@ -75,7 +75,9 @@ constexpr unsigned kKeepAliveBytes = 256;       // what every wavefront re-reads
 constexpr float kFixedOne = 16777216.0f;        // 2^24
 constexpr float kFixedLimit = 120.0f;           // largest |sum| trusted to fixed point
 // Vector types: steps of 2^-25 -- as unsigned numbers up to 128 where no weight of the tile is
-// negative, as signed ones up to 64 otherwise.
+// negative, as signed ones up to 64 otherwise.  (The weight's exponent carries the scale, so log2|w|
+// is rounded at its size: with 2^-24 the error against 64 bits was 1.2e-6, with 2^-25 7e-7, 1.1e-6
+// before the scale moved there.)
 constexpr int kVecFixedBits = 25;
 
 struct FwdParams {
@@ -850,6 +852,11 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
 //   |w| rho_q = exp2(max(log2|w| - ratio2_q x'^2, log2|w| - g^2 k)) clamp(2gc - s tq_q, 0, 1)^2,
 // s = sqrt(x'^2).  log2|w| is worked out once per atom (in the lane that holds the atom) and
 // fetched by the lanes that walk its chords; it is all a chord needs per channel.
+// Bound by vector instruction issue: 34 instructions per step of 64 chords and four channels (38 with
+// the two branches selected: 516 instead of 501 us a call on 50 x 2040 atoms, 28 x 48^3).  Measured and
+// slower: chords cut into slots of four voxels and queued in LDS (7 % fewer instructions, 12 instead of
+// 16 wavefronts per CU: 612 us); tasks in order of the row's distance from the atom (523 us); tile rows
+// padded in LDS (half the bank conflicts, 509 us).
 // ---------------------------------------------------------------------------
 constexpr int kVecGroup = 4;
 
@@ -1274,7 +1281,7 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
                                         hipStream_t stream)
 {
     // 2048-float tiles and four wavefronts per workgroup: the four channel tiles of a group take
-    // 33 KB of LDS, so four workgroups (sixteen wavefronts, what 111 registers allow) fit a CU.
+    // 33 KB of LDS, so four workgroups (sixteen wavefronts; 98 registers would allow twenty) fit a CU.
     // Measured on the 48^3 batch of 50 x 2040 atoms x 28 channels: 0.50 ms; relative to it, 1024
     // floats x 2 wavefronts +10 % (each tile tests the atoms in reach anew), 2048 x 2 and 1024 x 1
     // +43 % (too few wavefronts), 512 x 1 +33 %.  A grid of doubles takes 512 voxels per tile.
