@@ -368,7 +368,8 @@ typedef double Double2E __attribute__((ext_vector_type(2), aligned(8)));
 // Stream the finished tile to HBM (zeros if no atom touched it).  ITERS = tile_floats / 512
 // chunks of 2 KB; wavefront w of NW takes chunks w, w + NW, ...
 // VECTOR: fixed point is unsigned unless `neg`, in steps of 2^-kVecFixedBits.
-template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false>
+// LOOSE: the output is only aligned like its elements.
+template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false, bool LOOSE = false>
 __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed, bool neg = true)
 {
     const auto value = [&](float bits) {
@@ -405,8 +406,9 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
     } else if (ALIGNED) {
         constexpr int MINE = ITERS / NW;            // chunks per wavefront
         const int n4 = cx.n >> 2;                   // even: D^3 and the tile size are multiples of 8
-        Float4E *dst4 = reinterpret_cast<Float4E *>(dst);       // float grids
-        Double2E *dst2 = reinterpret_cast<Double2E *>(dst);     // double grids
+        float4 *dst4 = reinterpret_cast<float4 *>(dst);         // float grids
+        Float4E *dst4e = reinterpret_cast<Float4E *>(dst);
+        double2 *dst2 = reinterpret_cast<double2 *>(dst);       // double grids
         const float4 *src4 = reinterpret_cast<const float4 *>(cx.tile);
         // Constant trip count, fully unrolled; the tile comes from LDS into registers
         // under a uniform branch (zeros otherwise), so that the stores below are one
@@ -434,13 +436,18 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
             const int o = (it * NW + cx.wave) * 128 + cx.lane * 2;
             if (o < n4) {
                 if (kWide) {        // the lane's 8 values are 64 contiguous bytes: four 16-byte stores
-                    dst2[2 * o] = Double2E{(double)a.x, (double)a.y};
-                    dst2[2 * o + 1] = Double2E{(double)a.z, (double)a.w};
-                    dst2[2 * o + 2] = Double2E{(double)b.x, (double)b.y};
-                    dst2[2 * o + 3] = Double2E{(double)b.z, (double)b.w};
+                    dst2[2 * o] = make_double2((double)a.x, (double)a.y);
+                    dst2[2 * o + 1] = make_double2((double)a.z, (double)a.w);
+                    dst2[2 * o + 2] = make_double2((double)b.x, (double)b.y);
+                    dst2[2 * o + 3] = make_double2((double)b.z, (double)b.w);
                 } else {
-                    dst4[o] = Float4E{a.x, a.y, a.z, a.w};
-                    dst4[o + 1] = Float4E{b.x, b.y, b.z, b.w};
+                    if (LOOSE) {
+                        dst4e[o] = Float4E{a.x, a.y, a.z, a.w};
+                        dst4e[o + 1] = Float4E{b.x, b.y, b.z, b.w};
+                    } else {
+                        dst4[o] = a;
+                        dst4[o + 1] = b;
+                    }
                 }
             }
         }
@@ -461,7 +468,7 @@ __device__ inline void store_any_tile(const FwdParams &p, const TileCtx &cx, OUT
                                       bool neg = true)
 {
     if (ALIGNED || ((VECTOR || p.shifted) && cx.n == ITERS * 512))
-        store_tile<true, ITERS, NW, OUT, VECTOR>(cx, dst, touched, fixed, neg);
+        store_tile<true, ITERS, NW, OUT, VECTOR, !ALIGNED && VECTOR>(cx, dst, touched, fixed, neg);
     else
         store_tile<false, ITERS, NW, OUT, VECTOR>(cx, dst, touched, fixed, neg);
 }
@@ -1166,6 +1173,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     // round ahead; clear_first: the tiles are cleared while the first loads are in flight.
     auto pass = [&](int first, int stride, bool fixed, bool clear_first, int &bound) {
         bool any = false;
+        int add[kVecGroup] = {0, 0, 0, 0};      // what this lane's atoms can add to one voxel of channel q
         Raw rc = load_raw(64 * first);
         Raw rn = load_raw(64 * (first + stride));
         Wq wc = gather(rc);
@@ -1206,12 +1214,9 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
                 const int jaA = max(-cx.rowA, 0), jbA = min(tg.R1 - tg.R0 - cx.rowA, D);
                 const int jaB = max(-cx.rowB, 0), jbB = iA < tg.i_hi ? min(tg.R1 - tg.R0 - cx.rowB, D) : 0;
                 PairHit h = pair_test<BINARY>(cx, p, at, ox, iA, jaA, jbA, jaB, jbB);
-                if (!BINARY) {      // what these atoms can add to one voxel of the channel they add most to
-                    int most = 0;
+                if (!BINARY) {
 #pragma unroll
-                    for (int q = 0; q < kVecGroup; ++q)     // (summed exactly by DPP adds, no LDS traffic)
-                        most = max(most, bcast(wave_inclusive_scan(h.nA + h.nB > 0 ? wb[q] : 0), 63));
-                    bound = min(bound + min(most, 1 << 24), 1 << 26);
+                    for (int q = 0; q < kVecGroup; ++q) add[q] = min(add[q] + (h.nA + h.nB > 0 ? wb[q] : 0), 1 << 24);
                 }
                 const bool ran = any_neg ? pair_run_group<BINARY, true>(cx, vg, h, va, kTile, fixed)
                                          : pair_run_group<BINARY, false>(cx, vg, h, va, kTile, fixed);
@@ -1221,6 +1226,11 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
             wc = wn;
             rn = rnn;
             wn = gather(rn);
+        }
+        if (!BINARY) {      // the channel they add most to (summed exactly by DPP adds, no LDS traffic)
+#pragma unroll
+            for (int q = 0; q < kVecGroup; ++q)
+                bound = max(bound, min(bcast(wave_inclusive_scan(add[q]), 63), 1 << 26));
         }
         return any;
     };
