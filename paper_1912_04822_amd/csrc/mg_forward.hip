@@ -22,19 +22,19 @@
 //      z-row, clipped to the tile in its first and last row.  It evaluates the
 //      density voxel by voxel and adds it into the tile held in LDS with LDS
 //      atomics (two atoms may hit one voxel in the same instruction).  The tile
-//      accumulates in signed fixed point (2^-24 steps, integer LDS atomics):
+//      accumulates in unsigned fixed point (2^-26 steps, integer LDS atomics):
 //      integer adds run ~40x faster in LDS than float adds on this chip, are
 //      exact and order-independent, and a contribution is rounded by at most
-//      3e-8.  The sum of the magnitudes that can reach a voxel is tracked; if it
-//      could pass 120 (fixed-point range is +-128) the tile switches to float
-//      accumulation;
+//      7.5e-9.  Where more than 63 atoms reach a tile a sum could pass 2^32: the
+//      adds are then watched, and if one comes near a second pass finds the sums'
+//      upper bits, so that a grid never depends on the order of the atoms or on
+//      how they are split over wavefronts;
 //   4. the finished tile is streamed to HBM, each lane writing 32 contiguous
 //      bytes (two adjacent 16-byte stores), every output element exactly once,
 //      zeros included.  Tiles no atom touches skip LDS and store zeros.
 // The tile sits in LDS in output order (LDS index = output index - first index of
 // the tile).  With more than one wavefront there are two barriers per tile: after
-// the zero fill and the decision between fixed point and float (which needs the
-// bound over all wavefronts), and before the tile is read back.  The default is
+// the zero fill, and before the tile is read back.  The default is
 // one wavefront per 4 KB tile (no barrier at all; 8 KB when a tile meets many
 // records).  A grid of doubles takes 512 voxels per workgroup (4 KB of output) and
 // stores 1 KB per instruction.
@@ -72,8 +72,14 @@ namespace {
 constexpr int kTaskCap = 256;                   // (atom, row) tasks staged per round
 constexpr int kFusedAtoms = 2048;               // single launch: most atoms a workgroup of several wavefronts looks through
 constexpr unsigned kKeepAliveBytes = 256;       // what every wavefront re-reads of the tables by default
-constexpr float kFixedOne = 16777216.0f;        // 2^24
-constexpr float kFixedLimit = 120.0f;           // largest |sum| trusted to fixed point
+// Index types: steps of 2^-26.  (With 2^-24, which leaves room for 255 atoms, the error against 64 bits
+// of 2040 atoms in one channel of 48^3 was 2.6e-7, 2.2e-7 for sums in floats; sums past 64 hardly occur.)
+constexpr float kFixedOne = 67108864.0f;        // 2^26
+constexpr float kAlmostHalf = 0.49999997f;       // rounds to the nearest step: 0.5 would push odd whole numbers of 24 bits up
+constexpr int kSafeHits = 63;                   // this many densities of at most 1 stay below 2^32 steps
+constexpr int kDigitBits = 13;                  // ... and fewer than 2^19 of their upper or lower digits
+constexpr int kDigitHits = 1 << 19;
+constexpr float kFixedLimit = 120.0f;           // vector types: largest |sum| trusted to fixed point
 // Vector types: steps of 2^-25 -- as unsigned numbers up to 128 where no weight of the tile is
 // negative, as signed ones up to 64 otherwise.  (The weight's exponent carries the scale, so log2|w|
 // is rounded at its size: with 2^-24 the error against 64 bits was 1.2e-6, with 2^-25 7e-7, 1.1e-6
@@ -119,7 +125,8 @@ struct FwdParams {
 struct TileCtx {
     float *tile;                // LDS: tile_floats floats, in output order
     unsigned char *marks;       // LDS (per wavefront): marks[first task of the atom in lane l] = l + 1
-    int *shared;                // LDS (workgroup): [0] bound on |sum| (1/256 units), [1] any task
+    int *shared;                // LDS (workgroup): [0] bound on |sum| (1/256 units; vector types), [1] bit 0:
+                                // any task, bit 1: sums may have passed 2^32 (vector types: a weight is negative)
     int lane, wave;
     int D, n;                   // points per side; floats in this tile
     int nrows;                  // grid rows the tile touches
@@ -132,8 +139,6 @@ struct TileCtx {
     float g2k, c2k, sA, cA;
     int debug;
 };
-
-enum TileMode { kUntouched = 0, kFixed = 1, kFloat = 2 };
 
 __device__ inline int div_by_d(int x, unsigned long long magic)
 {
@@ -167,9 +172,20 @@ __device__ inline float fetch(int byte_addr, float v)
     return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_addr, __float_as_int(v)));
 }
 
+// How fixed-point densities are added up.
+enum class Sum {
+    kPlain,
+    kWatch,     // and the values found before each add collected in `seen`
+    kDigit      // only `bits` bits of each from bit `shift`
+};
+struct SumArgs {
+    unsigned shift = 0, bits = 0;
+    unsigned seen = 0;
+};
+
 // Run the staged tasks [0, ntasks): one (atom, row) chord per lane.
-template <bool BINARY, bool FIXED>
-__device__ inline void run_tasks(const TileCtx &cx, const Cand &cd, int ntasks)
+template <bool BINARY, Sum SUM>
+__device__ inline void run_tasks(const TileCtx &cx, const Cand &cd, int ntasks, SumArgs &sa)
 {
     int carry = 0;
     for (int base = 0; base < ntasks; base += 64) {
@@ -226,6 +242,7 @@ __device__ inline void run_tasks(const TileCtx &cx, const Cand &cd, int ntasks)
             float cA = cx.cA;
             asm volatile("" : "+v"(cA));        // keep it in a VGPR across the loop
             float fi = 0.0f;
+            unsigned old = 0u;
             for (int i = 0; i < nz; ++i) {
                 const float zs = fmaf(fi, stepk, z0);
                 fi += 1.0f;
@@ -235,15 +252,16 @@ __device__ inline void run_tasks(const TileCtx &cx, const Cand &cd, int ntasks)
                 // clamp to [0, 1] cuts it off at the cutoff
                 const float u = __builtin_amdgcn_fmed3f(fmaf(-__builtin_amdgcn_sqrtf(x2), cx.sA, cA), 0.0f, 1.0f);
                 const float rho = x2 <= cx.g2k ? e : u * u;             // 0 beyond the cutoff
-                if (FIXED) {
-                    __hip_atomic_fetch_add(reinterpret_cast<int *>(rowp) + klo + i,
-                                           (int)fmaf(rho, kFixedOne, 0.5f), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                } else {
-                    __hip_atomic_fetch_add(rowp + klo + i, rho, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                unsigned v = (unsigned)fmaf(rho, kFixedOne, kAlmostHalf);
+                if (SUM == Sum::kDigit) v = __builtin_amdgcn_ubfe(v, sa.shift, sa.bits);
+                if (SUM == Sum::kWatch) {
+                    asm volatile("" : "+v"(old) : "v"(v));      // the answer to the add before is not waited for until here
+                    sa.seen |= old;
                 }
+                old = __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(rowp) + klo + i, v, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
             }
+            if (SUM == Sum::kWatch) sa.seen |= old;
         }
     }
     lds_sync();
@@ -323,17 +341,11 @@ __device__ inline PairHit pair_test(const TileCtx &cx, const FwdParams &p, const
     return h;
 }
 
-// What the hits of this wavefront can add to one voxel at most (rho <= 1), in 1/256.
-__device__ inline int pair_bound(const PairHit &h)
-{
-    return 256 * (int)__builtin_popcountll(__ballot(h.nA + h.nB > 0));
-}
-
 // Stage the tasks of the hits (rows of plane A, then rows of plane B, atom after atom)
 // and run them.
 // Returns whether there was any task.
 template <bool BINARY>
-__device__ inline bool pair_run(const TileCtx &cx, PairHit &h, bool fixed)
+__device__ inline bool pair_run(const TileCtx &cx, PairHit &h, Sum sum, SumArgs &sa)
 {
     int todo = h.nA + h.nB;         // lanes still to be staged have todo > 0
     if (__ballot(todo > 0) == 0ull) return false;
@@ -355,8 +367,9 @@ __device__ inline bool pair_run(const TileCtx &cx, PairHit &h, bool fixed)
             todo = 0;
         }
         lds_sync();
-        if (fixed) run_tasks<BINARY, true>(cx, h.cd, total);
-        else run_tasks<BINARY, false>(cx, h.cd, total);
+        if (BINARY || sum == Sum::kPlain) run_tasks<BINARY, Sum::kPlain>(cx, h.cd, total, sa);
+        else if (sum == Sum::kWatch) run_tasks<BINARY, Sum::kWatch>(cx, h.cd, total, sa);
+        else run_tasks<BINARY, Sum::kDigit>(cx, h.cd, total, sa);
     }
     return true;
 }
@@ -375,7 +388,7 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
     const auto value = [&](float bits) {
         const int i = __float_as_int(bits);
         if (VECTOR) return (neg ? (float)i : (float)(unsigned)i) * (1.0f / (float)(1 << kVecFixedBits));
-        return (float)i * (1.0f / kFixedOne);
+        return (float)(unsigned)i * (1.0f / kFixedOne);
     };
     constexpr bool kWide = sizeof(OUT) == 8;        // a grid of doubles: the same values, widened
     if (ALIGNED && kWide) {
@@ -514,7 +527,7 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
                                           const TileGeom &tg, int r0, int r1, const float4 &cen,
                                           const unsigned short *list = nullptr)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const GridSpec &gs = p.gs;
     const int D = gs.D, T = p.T, N = p.N;
     const int total = D * D * D;
@@ -577,7 +590,7 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
         RawAtom ra;
         int ec = min(base + lane * nsplit + sub, count - 1);            // count >= 1 here
         if (NW > 1) ec = list[ec];
-        ra.te = p.raw.types[(size_t)b * N + ec];
+        ra.te = NW > 1 ? t : p.raw.types[(size_t)b * N + ec];           // (the list has type t only)
         const float *c3 = p.raw.coords + ((size_t)b * N + ec) * 3;
         ra.cc[0] = c3[0]; ra.cc[1] = c3[1]; ra.cc[2] = c3[2];
         ra.rad = p.raw.radii[gs.radius_type_indexed ? (size_t)t : (size_t)b * N + ec];
@@ -635,79 +648,132 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
             reinterpret_cast<float4 *>(lds)[it * 64 * NW + threadIdx.x] = z4;
         if (threadIdx.x < 2) cx.shared[threadIdx.x] = 0;
     }
-    const bool single = count <= 64 * nsplit && pA1 - pA0 <= 1;    // one round, one pair of planes
-    const int limit = (int)(kFixedLimit * 256.0f);
-    bool any = false, fixed = !BINARY;
-    if (NW == 1 && !single) {
-        // One wavefront, several rounds: a single pass.  The tile starts in fixed point and
-        // the bound on what can reach one voxel is kept up round by round; the moment it
-        // passes the limit, the tile is turned into floats and stays so.  The records of
-        // the next round are requested before this round's tasks run.
-        int bound = 0;
-        Atom at = at0;
-        for (int base = 0; base < count; base += 64) {
-            Atom next = at;
-            if (base + 64 < count) next = load_atom(base + 64);
-            for (int iA = pA0; iA <= pA1; iA += 2) {
-                PairHit h = test_pair(at, iA);
-                if (!BINARY && fixed) {
-                    bound += min(pair_bound(h), 1 << 24);
-                    if (bound > limit) {
-                        fixed = false;
-                        for (int o = lane; o < ITERS * 512; o += 64)
-                            lds[o] = (float)reinterpret_cast<int *>(lds)[o] * (1.0f / kFixedOne);
-                        lds_sync();
-                    }
-                }
-                any = pair_run<BINARY>(cx, h, fixed) || any;
-            }
-            at = next;
-        }
+    // What a wavefront may add to a voxel unwatched.  Alone: all that is safe; the add that carries a sum
+    // past 2^32 (64) comes after that and finds one of the two top bits set (16 or more).  Next to others:
+    // a share of 46, so that a sum which passes 64 has more than 17 of watched adds, the last of which
+    // found 16 or more.
+    const int unwatched = NW == 1 ? kSafeHits : 46 / nsplit;
+    constexpr bool kAhead = !FUSED;     // the next round's records are requested before this round's tasks run
+    // single launch: a watched pass places its first atoms again rather than keep them in registers (six
+    // instead of five wavefronts per SIMD: 11.9 instead of 12.7 us for 2040 atoms, 28 x 48^3; small tiles,
+    // which are watched more often, 8.0 instead of 8.4 us for 28 x 24^3 at 1 A)
+    constexpr bool kAgain = FUSED && NW != 2;
+    constexpr int kShare = kDigitHits - 256;        // records of a pass over digits (whole rounds)
+    float *park = reinterpret_cast<float *>(dst);
+    constexpr int kPark = sizeof(OUT) / sizeof(float);
+    auto each = [&](auto body) {
+        for (int o = threadIdx.x; o < cx.n; o += 64 * NW) body(o);
+    };
+    auto sync = [&]() {
+        if (NW > 1) __syncthreads();
+        else lds_sync();
+    };
+    SumArgs sa;
+    bool any = false;
+    const bool short_span = BINARY || count <= kSafeHits;      // nothing needs watching
+    const bool single = count <= 64 * nsplit && pA1 - pA0 <= 1;        // one round, one pair of planes
+    if (single) {
+        PairHit h = test_pair(at0, pA0);
+        const bool safe = short_span || (int)__builtin_popcountll(__ballot(h.nA + h.nB > 0)) <= unwatched;
+        if (NW > 1) __syncthreads();                // the tile and shared[] are clear
+        any = safe ? pair_run<BINARY>(cx, h, Sum::kPlain, sa) : pair_run<BINARY>(cx, h, Sum::kWatch, sa);
     } else {
-        PairHit h0;
-        if (NW > 1) __syncthreads();                // shared[] is clear
-        // pass 1: what can be added to one voxel at most decides fixed point or float (one
-        // wavefront keeps the bound in a register, several add theirs up in LDS)
-        // (index types: every record adds at most 1 to a voxel, so a short span needs no count)
-        const bool short_span = count <= (int)kFixedLimit;
-        int bound = 0;
-        if (single) {
-            h0 = test_pair(at0, pA0);
-            if (!BINARY && !short_span) bound = pair_bound(h0);
-        } else if (!BINARY && !short_span) {
-            for (int base = 0; base < count && bound <= limit; base += 64 * nsplit) {
-                const Atom at = base == 0 ? at0 : load_atom(base);
-                for (int iA = pA0; iA <= pA1; iA += 2) {
-                    const PairHit h = test_pair(at, iA);
-                    bound += min(pair_bound(h), 1 << 24);   // past the limit the value does not matter
-                }
-            }
-        }
-        if (NW > 1) {
-            if (!short_span && lane == 0 && bound > 0) atomicAdd(&cx.shared[0], min(bound, 1 << 24));
-            __syncthreads();                        // tile and shared[0] are ready
-            if (!short_span) bound = cx.shared[0];
-        }
-        fixed = !BINARY && bound <= limit;
-        // pass 2: the tasks
-        if (single) {
-            any = pair_run<BINARY>(cx, h0, fixed);
-        } else {
+        if (NW > 1) __syncthreads();
+        if (short_span) {
+            Atom at = at0;
             for (int base = 0; base < count; base += 64 * nsplit) {
-                const Atom at = base == 0 ? at0 : load_atom(base);
+                if (!kAhead && base != 0) at = load_atom(base);
+                Atom next = at;
+                if (kAhead && base + 64 * nsplit < count) next = load_atom(base + 64 * nsplit);
                 for (int iA = pA0; iA <= pA1; iA += 2) {
                     PairHit h = test_pair(at, iA);
-                    any = pair_run<BINARY>(cx, h, fixed) || any;
+                    any = pair_run<BINARY>(cx, h, Sum::kPlain, sa) || any;
                 }
+                at = next;
             }
         }
+    }
+    if (short_span) {
         if (NW > 1) {
             if (any && lane == 0) cx.shared[1] = 1;
             __syncthreads();                        // every wavefront's additions are in the tile
             any = cx.shared[1] != 0;
         }
+        store_any_tile<ALIGNED, ITERS, NW, OUT>(p, cx, dst, any, !BINARY);
+        return;
     }
-    store_any_tile<ALIGNED, ITERS, NW, OUT>(p, cx, dst, any, fixed);
+    Atom at = {};
+    if (!kAgain) at = at0;
+    Sum sum = Sum::kWatch;
+    for (int s0 = 0, s1 = count; ;) {               // a pass over the records [s0, s1): all of them but in rare cases
+        int hits[2] = {0, 0};       // what this wavefront can have added to a voxel so far (first pair of planes, others)
+        for (int base = single && sum == Sum::kWatch ? s1 : s0; base < s1; base += 64 * nsplit) {
+            if ((!kAhead && (kAgain || base != s0)) || sum == Sum::kDigit) at = load_atom(base);
+            Atom next = at;
+            if (kAhead && sum != Sum::kDigit && base + 64 * nsplit < s1) next = load_atom(base + 64 * nsplit);
+            for (int iA = pA0; iA <= pA1; iA += 2) {
+                PairHit h = test_pair(at, iA);
+                Sum how = sum;
+                if (sum == Sum::kWatch) {
+                    int &n = hits[iA == pA0 ? 0 : 1];
+                    n = min(n + (int)__builtin_popcountll(__ballot(h.nA + h.nB > 0)), kSafeHits + 1);
+                    if (n <= unwatched) how = Sum::kPlain;
+                }
+                any = pair_run<BINARY>(cx, h, how, sa) || any;
+            }
+            at = next;
+        }
+        if (sum != Sum::kDigit) {
+            bool over = __ballot(sa.seen >= 1u << 30) != 0ull;
+            if (NW > 1) {
+                if (lane == 0 && any) atomicOr(&cx.shared[1], over ? 3 : 1);
+                __syncthreads();                    // every wavefront's additions are in the tile
+                any = cx.shared[1] != 0;
+                over = (cx.shared[1] & 2) != 0;
+            }
+            if (!over) break;                       // uniform over the workgroup
+            // Some sum has come to 16 and may have passed 64.  What the tile has is the sums modulo 2^32;
+            // they wait in the output while a second pass adds up the densities without their last
+            // kDigitBits bits.  Fewer than kDigitHits densities of a voxel lose less than 2^32 together,
+            // so the two make the exact sum.
+            // Hundreds of thousands of records in reach of one tile instead: share by share, in order, a
+            // digit at a time, added up in floats.
+            sum = Sum::kDigit;
+            sa.bits = 32 - kDigitBits;
+            sa.shift = kDigitBits;
+            if (count < kDigitHits) {
+                each([&](int o) { park[(size_t)o * kPark] = cx.tile[o]; });
+            } else {
+                s1 = kShare;
+                each([&](int o) { dst[o] = (OUT)0.0f; });
+            }
+        } else if (count < kDigitHits) {
+            sync();
+            each([&](int o) {
+                const unsigned long long least = (unsigned long long)__float_as_uint(cx.tile[o]) << kDigitBits;
+                const unsigned lost = __float_as_uint(park[(size_t)o * kPark]) - (unsigned)least;
+                dst[o] = (OUT)(float)((double)(least + lost) * (1.0 / (double)kFixedOne));
+            });
+            return;
+        } else {
+            sync();
+            const float step = (float)(1u << sa.shift) / kFixedOne;
+            each([&](int o) { dst[o] = (OUT)((float)dst[o] + (float)__float_as_uint(cx.tile[o]) * step); });
+            if (sa.shift != 0) {
+                sa.shift = 0;
+                sa.bits = kDigitBits;
+            } else {
+                if (s1 == count) return;
+                s0 = s1;
+                s1 = min(count, s0 + kShare);
+                sa.shift = kDigitBits;
+                sa.bits = 32 - kDigitBits;
+            }
+        }
+        each([&](int o) { cx.tile[o] = 0.0f; });    // (by the thread that has read the word)
+        sync();
+    }
+    store_any_tile<ALIGNED, ITERS, NW, OUT>(p, cx, dst, any, !BINARY);
 }
 
 
