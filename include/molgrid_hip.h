@@ -235,8 +235,9 @@ int mg_backward_vector(const mg_gridmaker *gm, int B, int N, int T,
  * prep kernel.  Arguments are as in the ordinary calls; types == NULL in
  * mg_prepare makes the tables of vector types.  The contract is the caller's:
  * the same GridMaker, B, N, T, the same workspace, and nothing else enqueued on
- * that workspace in between (every ordinary forward / backward call rebuilds
- * it); the input arrays must be the ones prepared (weights and radii are read
+ * that workspace in between (an ordinary forward / backward call rebuilds its
+ * tables or, where it runs as one launch, leaves them as they are); the input
+ * arrays must be the ones prepared (weights and radii are read
  * again by the calls that take them).  As a guard, the tables carry a tag
  * of (B, N, T, D, subgrids, kind of types, binary, radius_type_indexed) and the
  * kernels of a *_prepared call whose tag differs return at once and write
@@ -326,10 +327,10 @@ int mg_last_hip_error(void);
  *                     example and 4 to 8 million voxels, or 256 atoms per example and
  *                     2048 in the batch, and neither "tile_floats" nor "waves_per_tile"
  *                     set: every tile's workgroup places the example's atoms itself.
- *                     0 = always the prep kernel and its tables.  Binary grids are the
- *                     same to the bit either way, real ones to rounding.  Backward
- *                     calls without subgrids likewise up to 49152 atoms in
- *                     all (vector types 8192): gradients are the same to the bit
+ *                     0 = always the prep kernel and its tables.  Backward calls
+ *                     without subgrids likewise up to 49152 atoms in all (vector
+ *                     types 8192).  Grids and gradients are the same to the bit
+ *                     either way
  *   "tile_order"      0 or 1 (default 0): 0 = all tiles of a channel, then the
  *                     next channel; 1 = tile k of every channel, then tile k+1
  *   "lds_floor"       -1..65536 (default -1 = chosen per call: 6144 for 4 KB

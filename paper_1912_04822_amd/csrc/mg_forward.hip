@@ -235,13 +235,15 @@ __device__ inline void run_tasks(const TileCtx &cx, const Cand &cd, int ntasks, 
             act = act && rem > 0.0f;
             const float hz = __builtin_amdgcn_sqrtf(fmaxf(rem, 0.0f)) * inv_stepk + 1.0e-3f;
             const float fzi = fz + cx.hD;                                   // as a grid index
-            const int klo = max(clip_lo, (int)ceilf(fzi - hz));
+            const int first = (int)ceilf(fzi - hz);         // of the whole chord
+            const int klo = max(clip_lo, first);
             const int khi = min(clip_hi, (int)floorf(fzi + hz));
             const int nz = act ? khi - klo + 1 : 0;
-            const float z0 = (((float)klo - cx.hD) - fz) * stepk;
+            // counted from the whole chord's first voxel: the same density wherever the tile cuts the row
+            const float z0 = (((float)first - cx.hD) - fz) * stepk;
             float cA = cx.cA;
             asm volatile("" : "+v"(cA));        // keep it in a VGPR across the loop
-            float fi = 0.0f;
+            float fi = (float)(klo - first);
             unsigned old = 0u;
             for (int i = 0; i < nz; ++i) {
                 const float zs = fmaf(fi, stepk, z0);

@@ -59,6 +59,36 @@ def test_the_same_bits_however_the_work_is_split(mg, B, N, T, D, crowd):
     assert np.array_equal(bits(tables[3]), bits(tables[4]))
     out64 = gm.mg_forward_index(*args, dtype=torch.float64).cpu().numpy()
     assert np.abs(out64 - ref).max() <= grid_tol(ref)
+    # other tiles cut the rows elsewhere: the densities are the same all the same
+    assert all(np.array_equal(bits(t), bits(first)) for t in tables)
+    assert np.array_equal(out64, first.double().cpu().numpy())
+
+
+@pytest.mark.parametrize("B,N,T,D", [
+    (1, 2040, 28, 48), (1, 2040, 4, 48), (2, 600, 9, 48), (1, 2047, 40, 49),
+    (3, 700, 5, 21), (1, 256, 28, 96), (1, 100, 4, 24), (2, 60, 3, 17)])
+def test_prepared_calls_give_the_bits_of_ordinary_ones(mg, B, N, T, D):
+    """Inside the range of the one-launch route, which cuts other tiles than the tables' kernel and
+    takes the atoms in another order; also through the layer, whose grid does not depend on whether a
+    gradient will be asked for."""
+    from paper_1912_04822_amd.autograd import GridLayer
+    coords, types, radii = problem(B, N, T, D)
+    rng = np.random.default_rng(7)
+    pose = dict(centers=dev(rng.uniform(-1, 1, (B, 3)).astype(np.float32)),
+                quats=dev(rng.standard_normal((B, 4)).astype(np.float32)),
+                translations=dev(rng.uniform(-1, 1, (B, 3)).astype(np.float32)),
+                natoms=dev(rng.integers(N // 2, N + 1, B).astype(np.int32)))
+    args = (dev(coords), dev(types), dev(radii), T)
+    for binary in (False, True):
+        gm = mg.GridMaker(0.5, (D - 1) * 0.5, radius_type_indexed=True, binary=binary)
+        out = gm.mg_forward_index(*args, **pose)
+        ws = gm.mg_prepare(*args, **pose)
+        prepared = gm.mg_forward_index_prepared(B, N, T, ws)
+        assert np.array_equal(bits(out), bits(prepared))
+    layer = GridLayer(0.5, (D - 1) * 0.5)
+    plain = layer(args[0], args[2], types=args[1], T=T, **pose)
+    asked = layer(args[0].clone().requires_grad_(), args[2], types=args[1], T=T, **pose)
+    assert np.array_equal(bits(plain), bits(asked.detach()))
 
 
 def test_a_million_atoms_in_reach_of_one_tile(mg):
