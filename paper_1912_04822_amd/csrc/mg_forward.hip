@@ -81,9 +81,7 @@ constexpr int kDigitBits = 13;                  // ... and fewer than 2^19 of th
 constexpr int kDigitHits = 1 << 19;
 constexpr float kFixedLimit = 120.0f;           // vector types: largest |sum| trusted to fixed point
 // Vector types: steps of 2^-25 -- as unsigned numbers up to 128 where no weight of the tile is
-// negative, as signed ones up to 64 otherwise.  (The weight's exponent carries the scale, so log2|w|
-// is rounded at its size: with 2^-24 the error against 64 bits was 1.2e-6, with 2^-25 7e-7, 1.1e-6
-// before the scale moved there.)
+// negative, as signed ones up to 64 otherwise.
 constexpr int kVecFixedBits = 25;
 
 struct FwdParams {
@@ -923,13 +921,14 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
 // The Gaussian and the quadratic tail are taken as a product, without a select between them:
 //   rho(x) = exp(-2 min(x, g)^2) clamp(2g (c - x), 0, 1)^2
 // (2g (c - g) = 1 and A = 4 g^2 exp(-2 g^2), so the second factor is 1 up to g and the tail's
-// A (x - c)^2 over exp(-2 g^2) beyond), the weight as an exponent:
-//   |w| rho_q = exp2(max(log2|w| - ratio2_q x'^2, log2|w| - g^2 k)) clamp(2gc - s tq_q, 0, 1)^2,
-// s = sqrt(x'^2).  log2|w| is worked out once per atom (in the lane that holds the atom) and
-// fetched by the lanes that walk its chords; it is all a chord needs per channel.
-// Bound by vector instruction issue: 34 instructions per step of 64 chords and four channels (38 with
-// the two branches selected: 516 instead of 501 us a call on 50 x 2040 atoms, 28 x 48^3).  Measured and
-// slower: chords cut into slots of four voxels and queued in LDS (7 % fewer instructions, 12 instead of
+// A (x - c)^2 over exp(-2 g^2) beyond):
+//   w rho_q = w exp2(max(-ratio2_q x'^2, -g^2 k)) clamp(2gc - s tq_q, 0, 1)^2,   s = sqrt(x'^2).
+// The weight, with the steps of the fixed point, is all a chord needs per channel; the lanes that walk
+// the chord fetch it from the lane that holds the atom.  It is a factor and not part of the exponent: an
+// exponent of log2|w| + 25 is rounded at 2^-20, which cost 38 -> 34 instructions per step but made the
+// error of weights of one and more 2.5 times as large (2.1e-7 -> 5.1e-7).
+// Bound by vector instruction issue: 38 instructions per step of 64 chords and four channels, 524 us a
+// call on 50 x 2040 atoms, 28 x 48^3 (532 us with the two branches selected).  Measured and slower: chords cut into slots of four voxels and queued in LDS (7 % fewer instructions, 12 instead of
 // 16 wavefronts per CU: 612 us); tasks in order of the row's distance from the atom (523 us); tile rows
 // padded in LDS (half the bank conflicts, 509 us).
 // ---------------------------------------------------------------------------
@@ -938,15 +937,15 @@ constexpr int kVecGroup = 4;
 struct VecGroup {           // wave-uniform: the channels of this workgroup
     int chan[kVecGroup];        // channel index (for dead slots: any valid channel)
     bool live[kVecGroup];       // slot q holds a channel with a positive radius
-    float ratio2[kVecGroup];    // (rmax / r_q)^2
+    float nr2[kVecGroup];       // -(rmax / r_q)^2
     float tq[kVecGroup];        // 2g/sqrt(k) rmax / r_q
     float r2[kVecGroup];        // binary mode: r_q * r_q (float, as the predicate's right-hand side)
     float rmax;
-    float g2k, tc;              // g^2 k; 2g c
+    float ng2k, tc;             // -g^2 k; 2g c
 };
 
 struct VecAtom {            // per atom, per channel of the group
-    float lw[kVecGroup];        // log2 |w_q|  (-inf for w_q = 0: the value is then 0); fixed point: + kVecFixedBits
+    float w[kVecGroup];         // w_q; fixed point: in steps
     int neg;                    // bit q: w_q < 0  (binary mode: bit q: w_q > 0, the atom marks channel q)
 };
 
@@ -968,17 +967,11 @@ __device__ inline void run_tasks_group(const TileCtx &cx, const VecGroup &vg, co
         const float pxA = fetch(src, cd.pxA), pxB = fetch(src, cd.pxB);
         const int pack = __builtin_amdgcn_ds_bpermute(src, cd.pack);
         const int k = tau - __builtin_amdgcn_ds_bpermute(src, cd.start);   // row number within the atom
-        float lw[kVecGroup], lwg[kVecGroup];
+        float w[kVecGroup], half[kVecGroup];
 #pragma unroll
         for (int q = 0; q < kVecGroup; ++q) {
-            lw[q] = fetch(src, va.lw[q]);
-            lwg[q] = lw[q] - vg.g2k;
-        }
-        int sb[kVecGroup];
-        if (SIGNED) {
-            const int neg = __builtin_amdgcn_ds_bpermute(src, va.neg);
-#pragma unroll
-            for (int q = 0; q < kVecGroup; ++q) sb[q] = ((neg >> q) & 1) << 31;
+            w[q] = fetch(src, va.w[q]);
+            half[q] = SIGNED ? copysignf(kAlmostHalf, w[q]) : kAlmostHalf;
         }
         const int nA = (pack >> 10) & 1023;
         const bool inB = k >= nA;
@@ -1008,19 +1001,17 @@ __device__ inline void run_tasks_group(const TileCtx &cx, const VecGroup &vg, co
             const float sx = __builtin_amdgcn_sqrtf(x2);
 #pragma unroll
             for (int q = 0; q < kVecGroup; ++q) {
-                const float e = __builtin_amdgcn_exp2f(__builtin_amdgcn_fmed3f(fmaf(-vg.ratio2[q], x2, lw[q]), lwg[q], lw[q]));
+                const float e = __builtin_amdgcn_exp2f(__builtin_amdgcn_fmed3f(x2 * vg.nr2[q], vg.ng2k, 0.0f));
                 const float u = __builtin_amdgcn_fmed3f(fmaf(-sx, vg.tq[q], tc), 0.0f, 1.0f);
-                float u2 = u * u;                                           // 0 beyond the cutoff
-                if (SIGNED) u2 = __int_as_float(__float_as_int(u2) | sb[q]);
+                const float u2 = u * u;                                     // 0 beyond the cutoff
                 if (FIXED) {
-                    // |w| rho 2^kVecFixedBits + 1/2, truncated: rounded to the nearest fixed-point step
-                    const float half = SIGNED ? __int_as_float(0x3f000000 | sb[q]) : 0.5f;
-                    const float v = fmaf(e, u2, half);
+                    // w rho 2^kVecFixedBits and a half, truncated: rounded to the nearest fixed-point step
+                    const float v = fmaf(e * w[q], u2, half[q]);
                     __hip_atomic_fetch_add(reinterpret_cast<unsigned *>(q0) + q * stride, SIGNED ? (unsigned)(int)v : (unsigned)v,
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 } else {
                     // (a weight may be infinite here; beyond the cutoff it adds nothing all the same)
-                    __hip_atomic_fetch_add(q0 + q * stride, u > 0.0f ? e * u2 : 0.0f, __ATOMIC_RELAXED,
+                    __hip_atomic_fetch_add(q0 + q * stride, u > 0.0f ? e * w[q] * u2 : 0.0f, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
@@ -1138,7 +1129,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     // the channels of this group and what depends on their radii only
     VecGroup vg;
     vg.rmax = 0.0f;
-    vg.g2k = p.vg2k;
+    vg.ng2k = -p.vg2k;
     vg.tc = p.tc;
     float rq[kVecGroup];
 #pragma unroll
@@ -1152,7 +1143,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 #pragma unroll
     for (int q = 0; q < kVecGroup; ++q) {
         const float ratio = vg.live[q] ? vg.rmax / rq[q] : 1.0f;
-        vg.ratio2[q] = ratio * ratio;
+        vg.nr2[q] = -(ratio * ratio);
         vg.tq[q] = p.tk * ratio;
         vg.r2[q] = vg.live[q] ? rq[q] * rq[q] : -1.0f;     // (nothing is within a dead channel's radius)
     }
@@ -1262,14 +1253,14 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 #pragma unroll
             for (int q = 0; q < kVecGroup; ++q) {
                 if (BINARY) {       // the atom marks the channels where its weight is positive
-                    va.lw[q] = 0.0f;
+                    va.w[q] = 0.0f;
                     va.neg |= (wc.w[q] > 0.0f ? 1 : 0) << q;
                     continue;
                 }
                 const float aw = fabsf(wc.w[q]);
                 wb[q] = aw > 0.0f ? (int)ceilf(fminf(aw, 4096.0f) * 256.0f) : 0;
                 wany = wany || aw > 0.0f;
-                va.lw[q] = __builtin_amdgcn_logf(aw) + (fixed ? (float)kVecFixedBits : 0.0f);       // log2
+                va.w[q] = wc.w[q] * (fixed ? (float)(1 << kVecFixedBits) : 1.0f);
                 va.neg |= (wc.w[q] < 0.0f ? 1 : 0) << q;
             }
             at.valid = (rc.a.w > 0.0f) && (BINARY ? va.neg != 0 : wany);
