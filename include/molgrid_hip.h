@@ -329,7 +329,9 @@ int mg_last_hip_error(void);
  *                     set: every tile's workgroup places the example's atoms itself.
  *                     0 = always the prep kernel and its tables.  Backward calls
  *                     without subgrids likewise up to 49152 atoms in all (vector
- *                     types 8192).  Grids and gradients are the same to the bit
+ *                     types 8192, and 1.5e10 atoms x channels x points; for one
+ *                     example of more than 4096 atoms 6.5e10, counting the atoms a
+ *                     grid of its size holds in proteins).  Grids and gradients are the same to the bit
  *                     either way
  *   "tile_order"      0 or 1 (default 0): 0 = all tiles of a channel, then the
  *                     next channel; 1 = tile k of every channel, then tile k+1

@@ -429,7 +429,7 @@ static int backward_call(const mg_gridmaker *gm, int B, int N, int T, const floa
     float *gw = (sub && grad_weights) ? ws.wtmp : grad_weights;
     // few atoms in all: one launch, every atom's wavefront places its atom itself
     const bool single = tables == Tables::kBuildAndRun && timing_prep_stop() == 0 &&
-                        g_single_launch.load(std::memory_order_relaxed) != 0 && mg::backward_takes_single_launch(bt);
+                        g_single_launch.load(std::memory_order_relaxed) != 0 && mg::backward_takes_single_launch(gm->gs, bt);
     if (tables != Tables::kUseBuilt && !single) {
         const int stop = timing_prep_stop();
         rc = hip_status(mg::launch_prep(gm->gs, bt, ws, stop, (hipStream_t)stream));

@@ -752,13 +752,29 @@ hipError_t launch_sum_subgrids(int subgrid_count, int B_source, size_t per_examp
 // the gradient grid) and, per atom, the transform worked out by a whole wavefront; what is saved is
 // the prep kernel's 10 us and more.  Whole calls, one launch / prep kernel and backward kernel:
 // 2040 atoms and 28 channels of 48^3 per example, us: index types 10.4 / 17.1 for 1 example, 34.7 / 38.2
-// for 16, 47.1 / 50.2 for 24, 61.5 / 61.3 for 32, 92.1 / 87.7 for 50; vector types, where every atom
-// reads every channel, 55 / 70 for 1, 130 / 144 for 4, 242 / 190 for 8.
+// for 16, 47.1 / 50.2 for 24, 61.5 / 61.3 for 32, 92.1 / 87.7 for 50.
+// Vector types read every channel for every atom.  Four channels of a grid of 48^3 are 1.8 MB and stay in
+// an XCD's L2 whatever the order of the atoms; those of larger grids stay there only in the order of the
+// tables, so the line lies at a product of atoms, channels and points.  2040 atoms that fill the grid, us:
+// 28 x 48^3 48 / 63, two examples 81 / 86, three 135 / 111; 12 x 64^3 42 / 52, 28 x 64^3 91 / 89; 12 x 80^3
+// 80 / 75; 4 x 96^3 60 / 55, 28 x 96^3 329 / 205.  One example of more than 4096 atoms is sorted by one
+// workgroup in 50 us and more, so the line lies further out, and what counts is the atoms that such a
+// grid can hold (proteins: 0.08 per cubic Angstrom; 2 A for their reach): 8160 atoms, 28 x 96^3 at 0.25 A
+// (1750 in reach) 372 / 658, 28 x 64^3 at 0.5 A 158 / 178, 12 x 96^3 at 0.5 A 158 / 124.
 constexpr long long kSingleAtoms = 49152;           // index types
-constexpr long long kSingleAtomsVector = 8192;      // vector types
-bool backward_takes_single_launch(const Batch &bt)
+constexpr long long kSingleAtomsVector = 8192;      // vector types, and ...
+constexpr double kSingleReads = 1.5e10;             // atoms x channels x points
+constexpr double kSingleReadsLong = 6.5e10;         // ... of one example of more than 4096, counting those it can hold
+bool backward_takes_single_launch(const GridSpec &gs, const Batch &bt)
 {
-    return bt.sub.count == 1 && (long long)bt.B * bt.N <= (bt.vec ? kSingleAtomsVector : kSingleAtoms);
+    if (bt.sub.count != 1) return false;
+    const long long atoms = (long long)bt.B * bt.N;
+    if (!bt.vec) return atoms <= kSingleAtoms;
+    if (atoms > kSingleAtomsVector) return false;
+    const double points = (double)bt.T * gs.D * gs.D * gs.D;
+    if (bt.B > 1 || bt.N <= 4096) return atoms * points <= kSingleReads;
+    const double side = (double)gs.D * gs.res + 4.0;
+    return std::fmin((double)atoms, 0.08 * side * side * side) * points <= kSingleReadsLong;
 }
 
 hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace &ws,

@@ -193,7 +193,7 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
                            const void *grad_out, bool grad_is_double, float *grad_coords,
                            float *grad_weights, bool single_launch, unsigned expect_tag,
                            KernelEvents ev, hipStream_t stream);
-bool backward_takes_single_launch(const Batch &bt);
+bool backward_takes_single_launch(const GridSpec &gs, const Batch &bt);
 // grad[b] = sum over the sub3 virtual examples of b, in order (subgrids only)
 hipError_t launch_sum_subgrids(int subgrid_count, int B_source, size_t per_example,
                                const float *tmp, float *grad, hipStream_t stream);
