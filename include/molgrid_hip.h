@@ -324,8 +324,9 @@ int mg_last_hip_error(void);
  *   "single_launch"   0 or 1 (default 1): small problems run as ONE kernel launch
  *                     (no prep kernel, the workspace is not touched).  Forward, index
  *                     types into a float grid without subgrids: at most 2048 atoms per
- *                     example and 4 to 8 million voxels, or 256 atoms per example and
- *                     2048 in the batch, and neither "tile_floats" nor "waves_per_tile"
+ *                     example and 8 million voxels (below 37 points a side: 4096 tiles
+ *                     of 1024 voxels or a part), or 64 atoms per example and 2048 in
+ *                     the batch, and neither "tile_floats" nor "waves_per_tile"
  *                     set: every tile's workgroup places the example's atoms itself.
  *                     0 = always the prep kernel and its tables.  Backward calls
  *                     without subgrids likewise up to 49152 atoms in all (vector

@@ -179,8 +179,6 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
                        hipStream_t stream);
 // Small problems (index types, float grid): the forward kernel alone, no prep kernel -- every
 // tile's workgroup transforms, culls and filters the example's atoms itself.
-constexpr int kSmallAtoms = 256;        // one wavefront looking at all of them: most atoms per example
-constexpr int kSmallTotal = 2048;       // ... and in the batch
 bool forward_takes_single_launch(const GridSpec &gs, const Batch &bt, bool out_is_double);
 // expect_tag != 0 (a *_prepared call): the kernel returns at once, writing nothing, unless the
 // workspace's tag equals it

@@ -1438,28 +1438,33 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
 
 // Small problems (index types into a float grid, no subgrids) in one launch: floats per
 // tile (negative: its type's atoms are listed first), 0 where the prep kernel and its tables are quicker.
-//   * up to 64 atoms: 1024, one wavefront that looks at all of them in one round;
+//   * up to 64 atoms, 2048 in the batch: 1024, one wavefront that looks at all of them in one round
+//     (with 65 to 256 it needs several rounds: 8 x 256 atoms, 28 x 48^3 39 us against 27 by the tables);
 //   * else, up to 2048 atoms: several wavefronts that first list the tile's type (find_atoms).
 //     Tiles of about two x-planes, so that the atoms found need one round: 1024 (two wavefronts)
 //     below 37 points a side, else 4096 (four); 2048 where that leaves less than three workgroups
 //     per CU and a tile more than one plane.
 //     Listing and placing the atoms per tile costs 7 us per 3.1 M voxels at 2040 atoms against the
-//     10 us and more of the prep kernel: up to 8 M voxels (4 M with the small tiles).
-// Whole calls, one launch / prep kernel and tables, us: 100 atoms, 4 x 24^3: 9.6 / 16 (one wavefront
-// that looks at all atoms: 13); 2040 atoms, 28 x 48^3: 12.5 / 18.3 (with 4096: 13.5), two of them 18.0 /
-// 20.2 (with 2048: 19.1), three 22.8 / 22.7; 1000 atoms, 14 x 64^3: 11.1 / 16.6; 20 x 200 atoms, 12 x
-// 24^3: 16.3 / 18.9; 40 x 600 atoms, 12 x 16^3: 14.7 / 21.2 (with 4096: 22).
+//     10 us and more of the prep kernel: up to 8 M voxels, or 4096 of the small tiles (tiles, not
+//     voxels: a channel of a few points a side is a tile all the same).
+// Whole calls, one launch / prep kernel and tables, us: 100 atoms, 4 x 24^3: 8.7 / 15 (one wavefront
+// that looks at all atoms: 13); 2040 atoms, 28 x 48^3: 11.9 / 17.7, 14 x 48^3 9.1 / 17.4, 4 x 48^3 13 / 30,
+// 1 x 48^3 20 / 44, 1 x 24^3 at 1 A 45 / 65; three of 24 x 48^3 18.2 / 22.9; 14 x 64^3 11.9 / 18.8; 20 x 28 x
+// 16^3 12.8 / 17.6, 50 x 28 x 12^3 19.8 / 20.3, 100 x 8 x 16^3 28.5 / 32, 500 x 14 x 8^3 48 / 35; 2000 x 200
+// atoms, 12 x 5^3 133 / 70.
+constexpr int kSmallTotal = 2048;
 static int single_launch_tile(const GridSpec &gs, const Batch &bt, bool out_is_double)
 {
     if (bt.vec || out_is_double || bt.sub.count != 1 || bt.N > kFusedAtoms) return 0;
     const long long voxels = (long long)bt.B * bt.T * gs.D * gs.D * gs.D;
     const bool large = gs.D >= 37;
-    if (bt.N > 64 && voxels <= (large ? 8LL << 20 : 4LL << 20)) {
-        if (!large) return -1024;
+    if (bt.N <= 64) return (long long)bt.B * bt.N <= kSmallTotal ? 1024 : 0;
+    if (!large) return (long long)bt.B * bt.T * forward_geometry(gs.D, 1024, gs.D % 4 != 0).tiles <= 4096 ? -1024 : 0;
+    if (voxels <= 8LL << 20) {
         const long long wgs = (long long)bt.B * bt.T * forward_geometry(gs.D, 4096).tiles;
         return wgs < 768 && gs.D < 64 ? -2048 : -4096;
     }
-    return bt.N <= kSmallAtoms && (long long)bt.B * bt.N <= kSmallTotal ? 1024 : 0;
+    return 0;
 }
 
 bool forward_takes_single_launch(const GridSpec &gs, const Batch &bt, bool out_is_double)

@@ -35,6 +35,11 @@ def route(mg, call, B, N, T, D, res):
     ("backward_vector", 1, 4096, 4, 100, 0.5, False), ("backward_vector", 1, 4097, 4, 100, 0.5, True),
     ("backward_vector", 1, 8192, 4, 128, 0.5, False), ("backward_vector", 1, 8192, 4, 128, 0.25, True),
     ("backward_vector", 2, 4096, 1, 12, 0.5, True), ("backward_vector", 2, 4097, 1, 12, 0.5, False),
+    ("forward", 1, 2048, 28, 48, 0.5, True), ("forward", 1, 2049, 28, 48, 0.5, False),
+    ("forward", 4, 2040, 28, 48, 0.5, False), ("forward", 100, 65, 8, 16, 1.0, True),
+    ("forward", 129, 65, 8, 16, 1.0, False), ("forward", 146, 70, 28, 8, 1.0, True),
+    ("forward", 147, 70, 28, 8, 1.0, False), ("forward", 32, 64, 14, 24, 0.5, True),
+    ("forward", 33, 64, 14, 24, 0.5, False), ("forward", 8, 256, 28, 48, 0.5, False),
     ("backward", 24, 2048, 3, 16, 0.5, True), ("backward", 24, 2049, 3, 16, 0.5, False)])
 def test_one_launch_or_tables(mg, call, B, N, T, D, res, single):
     alone, result = route(mg, call, B, N, T, D, res)
