@@ -38,7 +38,8 @@ def route(mg, call, B, N, T, D, res):
     ("forward", 1, 2048, 28, 48, 0.5, True), ("forward", 1, 2049, 28, 48, 0.5, False),
     ("forward", 4, 2040, 28, 48, 0.5, False), ("forward", 100, 65, 8, 16, 1.0, True),
     ("forward", 129, 65, 8, 16, 1.0, False), ("forward", 146, 70, 28, 8, 1.0, True),
-    ("forward", 147, 70, 28, 8, 1.0, False), ("forward", 32, 64, 14, 24, 0.5, True),
+    ("forward", 147, 70, 28, 8, 1.0, False), ("forward", 146, 70, 28, 9, 1.0, True),
+    ("forward", 29, 70, 28, 15, 1.0, True), ("forward", 30, 70, 28, 15, 1.0, False), ("forward", 32, 64, 14, 24, 0.5, True),
     ("forward", 33, 64, 14, 24, 0.5, False), ("forward", 8, 256, 28, 48, 0.5, False),
     ("backward", 24, 2048, 3, 16, 0.5, True), ("backward", 24, 2049, 3, 16, 0.5, False)])
 def test_one_launch_or_tables(mg, call, B, N, T, D, res, single):
