@@ -79,9 +79,10 @@ constexpr float kAlmostHalf = 0.49999997f;       // rounds to the nearest step: 
 constexpr int kSafeHits = 63;                   // this many densities of at most 1 stay below 2^32 steps
 constexpr int kDigitBits = 13;                  // ... and fewer than 2^19 of their upper or lower digits
 constexpr int kDigitHits = 1 << 19;
-constexpr float kFixedLimit = 120.0f;           // vector types: largest |sum| trusted to fixed point
-// Vector types: steps of 2^-25 -- as unsigned numbers up to 128 where no weight of the tile is
-// negative, as signed ones up to 64 otherwise.
+constexpr float kFixedLimit = 120.0f;           // vector types: largest sum of |weights| trusted to fixed point
+constexpr float kSignedTerm = 60.0f;            // ... and largest weight next to negative ones (signed conversion: 64)
+// Vector types: steps of 2^-25.  A voxel's sum lies between minus the negative weights that reach the tile
+// and the positive ones; while the two together stay below 128 the 32 bits name it, whatever its sign.
 constexpr int kVecFixedBits = 25;
 
 struct FwdParams {
@@ -124,7 +125,8 @@ struct TileCtx {
     float *tile;                // LDS: tile_floats floats, in output order
     unsigned char *marks;       // LDS (per wavefront): marks[first task of the atom in lane l] = l + 1
     int *shared;                // LDS (workgroup): [0] bound on |sum| (1/256 units; vector types), [1] bit 0:
-                                // any task, bit 1: sums may have passed 2^32 (vector types: a weight is negative)
+                                // any task, bit 1: sums may have passed 2^32; vector types: [4 + q] what channel
+                                // q's negative weights add up to (1/256 units)
     int lane, wave;
     int D, n;                   // points per side; floats in this tile
     int nrows;                  // grid rows the tile touches
@@ -380,15 +382,19 @@ typedef double Double2E __attribute__((ext_vector_type(2), aligned(8)));
 
 // Stream the finished tile to HBM (zeros if no atom touched it).  ITERS = tile_floats / 512
 // chunks of 2 KB; wavefront w of NW takes chunks w, w + NW, ...
-// VECTOR: fixed point is unsigned unless `neg`, in steps of 2^-kVecFixedBits.
+// VECTOR: in steps of 2^-kVecFixedBits, the sums at least -neg.
 // LOOSE: the output is only aligned like its elements.
 template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false, bool LOOSE = false>
-__device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed, bool neg = true)
+__device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed, unsigned neg = 0u)
 {
     const auto value = [&](float bits) {
-        const int i = __float_as_int(bits);
-        if (VECTOR) return (neg ? (float)i : (float)(unsigned)i) * (1.0f / (float)(1 << kVecFixedBits));
-        return (float)(unsigned)i * (1.0f / kFixedOne);
+        const unsigned i = __float_as_uint(bits);
+        if (VECTOR) {
+            const bool minus = i + neg < neg;       // [-neg, 0)
+            const float v = (float)(minus ? 0u - i : i) * (1.0f / (float)(1 << kVecFixedBits));
+            return minus ? -v : v;
+        }
+        return (float)i * (1.0f / kFixedOne);
     };
     constexpr bool kWide = sizeof(OUT) == 8;        // a grid of doubles: the same values, widened
     if (ALIGNED && kWide) {
@@ -478,7 +484,7 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
 // store full tiles 16 bytes at a time wherever they begin.)
 template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false>
 __device__ inline void store_any_tile(const FwdParams &p, const TileCtx &cx, OUT *dst, bool touched, bool fixed,
-                                      bool neg = true)
+                                      unsigned neg = 0u)
 {
     if (ALIGNED || ((VECTOR || p.shifted) && cx.n == ITERS * 512))
         store_tile<true, ITERS, NW, OUT, VECTOR, !ALIGNED && VECTOR>(cx, dst, touched, fixed, neg);
@@ -1173,7 +1179,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 
     const size_t total = (size_t)D * D * D;
     OUT *out = reinterpret_cast<OUT *>(p.out);
-    bool negs = false;          // some weight of the tiles is negative
+    int negs[kVecGroup] = {0, 0, 0, 0};     // what the negative weights of channel q add up to (1/256 units)
     auto store_all = [&](bool touched, bool fixed) {
 #pragma unroll
         for (int q = 0; q < kVecGroup; ++q) {
@@ -1181,7 +1187,8 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
             TileCtx cq = cx;
             cq.tile = lds + q * kTile;
             OUT *dst = out + ((size_t)b * T + vg.chan[q]) * total + tg.f0;
-            store_any_tile<ALIGNED, ITERS, NW, OUT, true>(p, cq, dst, touched && vg.live[q], fixed, negs);
+            store_any_tile<ALIGNED, ITERS, NW, OUT, true>(p, cq, dst, touched && vg.live[q], fixed,
+                                                          (unsigned)negs[q] << (kVecFixedBits - 8));
         }
     };
     const int count = r1 - r0;
@@ -1223,7 +1230,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 #pragma unroll
         for (int it = 0; it < kVecGroup * kTile / (256 * NW); ++it)
             reinterpret_cast<float4 *>(lds)[it * 64 * NW + threadIdx.x] = z4;
-        if (threadIdx.x < 2) cx.shared[threadIdx.x] = 0;
+        if (threadIdx.x < 4 + kVecGroup) cx.shared[threadIdx.x] = 0;
     };
 
     // One pass over the rounds first, first + stride, ...: returns whether any task ran; adds
@@ -1233,6 +1240,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     auto pass = [&](int first, int stride, bool fixed, bool clear_first, int &bound) {
         bool any = false;
         int add[kVecGroup] = {0, 0, 0, 0};      // what this lane's atoms can add to one voxel of channel q
+        int sub[kVecGroup] = {0, 0, 0, 0};      // ... of which negative
         Raw rc = load_raw(64 * first);
         Raw rn = load_raw(64 * (first + stride));
         Wq wc = gather(rc);
@@ -1266,7 +1274,11 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
             at.valid = (rc.a.w > 0.0f) && (BINARY ? va.neg != 0 : wany);
             at.a.w = vg.rmax;
             const bool any_neg = !BINARY && __ballot(at.valid && va.neg != 0) != 0ull;
-            negs = negs || any_neg;
+            if (!BINARY && any_neg) {       // a signed conversion holds less
+#pragma unroll
+                for (int q = 0; q < kVecGroup; ++q)
+                    if (fabsf(wc.w[q]) > kSignedTerm) wb[q] = 1 << 20;
+            }
             for (int iA = tg.i_lo; iA <= tg.i_hi; iA += 2) {
                 cx.rowA = iA * D - tg.R0;
                 cx.rowB = cx.rowA + D;
@@ -1275,7 +1287,11 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
                 PairHit h = pair_test<BINARY>(cx, p, at, ox, iA, jaA, jbA, jaB, jbB);
                 if (!BINARY) {
 #pragma unroll
-                    for (int q = 0; q < kVecGroup; ++q) add[q] = min(add[q] + (h.nA + h.nB > 0 ? wb[q] : 0), 1 << 24);
+                    for (int q = 0; q < kVecGroup; ++q) {
+                        const int b = h.nA + h.nB > 0 ? wb[q] : 0;
+                        add[q] = min(add[q] + b, 1 << 24);
+                        if (any_neg) sub[q] = min(sub[q] + (wc.w[q] < 0.0f ? b : 0), 1 << 24);
+                    }
                 }
                 const bool ran = any_neg ? pair_run_group<BINARY, true>(cx, vg, h, va, kTile, fixed)
                                          : pair_run_group<BINARY, false>(cx, vg, h, va, kTile, fixed);
@@ -1290,6 +1306,10 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
 #pragma unroll
             for (int q = 0; q < kVecGroup; ++q)
                 bound = max(bound, min(bcast(wave_inclusive_scan(add[q]), 63), 1 << 26));
+            if (__ballot((sub[0] | sub[1] | sub[2] | sub[3]) != 0) != 0ull) {
+#pragma unroll
+                for (int q = 0; q < kVecGroup; ++q) negs[q] = min(bcast(wave_inclusive_scan(sub[q]), 63), 1 << 26);
+            }
         }
         return any;
     };
@@ -1301,14 +1321,18 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     if (NW > 1) {
         if (lane == 0) {
             atomicAdd(&cx.shared[0], bound);
-            if (any) atomicOr(&cx.shared[1], negs ? 3 : 1);
+            if (any) cx.shared[1] = 1;
+#pragma unroll
+            for (int q = 0; q < kVecGroup; ++q)
+                if (negs[q] != 0) atomicAdd(&cx.shared[4 + q], negs[q]);
         }
         __syncthreads();                    // every wavefront's additions are in the tiles
         bound = cx.shared[0];
         any = cx.shared[1] != 0;
-        negs = (cx.shared[1] & 2) != 0;
+#pragma unroll
+        for (int q = 0; q < kVecGroup; ++q) negs[q] = cx.shared[4 + q];
     }
-    if (!BINARY && bound > (negs ? limit >> 1 : limit)) {       // uniform over the workgroup: the sums may not fit; again, in floats
+    if (!BINARY && bound > limit) {         // uniform over the workgroup: the sums may not fit; again, in floats
         if (NW > 1) __syncthreads();        // shared[] has been read by all
         fixed = false;
         clear_tiles();
@@ -1416,7 +1440,8 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
     int nw = waves_per_tile == 0 ? 4 : waves_per_tile;
     if (tile_floats == 512 || out_is_double) nw = 1;
     if (nw > tile_floats / 512) nw = tile_floats / 512;
-    const size_t lds_bytes = (size_t)kVecGroup * tile_floats * sizeof(float) + (size_t)nw * kTaskCap + 16;
+    const size_t lds_bytes = (size_t)kVecGroup * tile_floats * sizeof(float) + (size_t)nw * kTaskCap +
+                             (4 + kVecGroup) * sizeof(int);
     const bool aligned = (gs.D % 4 == 0) && (((uintptr_t)out & 15u) == 0);
     const dim3 blk(64 * nw), grd((unsigned)wgs);
 #define MG_VEC(Al, It, Nw, Ot)                                                                        \
