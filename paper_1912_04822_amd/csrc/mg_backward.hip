@@ -569,11 +569,8 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         apply_xform(X, pos, pos);
         gc = make_float4((float)X.c[0], (float)X.c[1], (float)X.c[2], 0.0f);
         const float org[3] = {gc.x - gs.half, gc.y - gs.half, gc.z - gs.half};
-        const float span = (float)(D - 1) * gs.res, pad = 1.0e-3f * gs.res;
-        bool live = member && (r > 0.0f) && (reach < 1.0e30f);
-        for (int m = 0; m < 3; ++m)     // also false for NaN / infinite coordinates
-            live = live && (pos[m] >= org[m] - reach - pad) && (pos[m] <= org[m] + span + reach + pad);
-        if (!live) {
+        const bool inside = meets_grid(gs, org, pos, r, reach);
+        if (!(member & inside)) {
             if (p.grad_coords && lane < 3) p.grad_coords[k * 3 + lane] = 0.0f;
             if (VECTOR && p.grad_weights)
                 for (int c = lane; c < T; c += 64) p.grad_weights[k * T + c] = 0.0f;

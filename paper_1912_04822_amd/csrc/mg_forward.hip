@@ -611,11 +611,7 @@ __device__ __forceinline__ void tile_body(const FwdParams &p, float *lds, int b,
             const float r = gs.radius_scale * ra.rad;
             const float reach = BINARY ? r : r * gs.c;
             const float org[3] = {ox, cx.oy, cx.oz};
-            const float span = (float)(D - 1) * gs.res, pad = 1.0e-3f * gs.res;
-            bool live = (r > 0.0f) && (reach < 1.0e30f);
-            for (int k = 0; k < 3; ++k)     // also false for NaN / infinite coordinates
-                live = live && (pp[k] >= org[k] - reach - pad) && (pp[k] <= org[k] + span + reach + pad);
-            if (live) at.a = make_float4(pp[0], pp[1], pp[2], r);
+            if (meets_grid(gs, org, pp, r, reach)) at.a = make_float4(pp[0], pp[1], pp[2], r);
         }
         at.valid = at.a.w > 0.0f;
         return at;

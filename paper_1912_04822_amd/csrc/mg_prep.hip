@@ -67,12 +67,6 @@ __device__ inline int wave_exclusive_scan(int v, int *total)
     return incl - v;
 }
 
-struct Culler {
-    float org[3];       // grid origin (center - half)
-    float span;         // (D-1)*res
-    float pad;
-};
-
 // Centre of the grid of virtual example b (source example bs); X holds bs's centre (a float
 // widened to double, so narrowing it back is exact).
 __device__ inline void grid_center(const Subgrids &sub, const Xform &X, int b, int bs, float *gc)
@@ -191,13 +185,11 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         }
         if (!gs.binary) vec_reach *= gs.c;
     }
-    Culler cu;
-    cu.pad = 1.0e-3f * gs.res;
-    cu.span = (float)(D - 1) * gs.res;
+    float org[3];                   // the grid's first point
     float gc[3];
     grid_center(bt.sub, X, b, bs, gc);
     if (tid < 3) ws.gcen[b * 4 + tid] = gc[tid];
-    for (int m = 0; m < 3; ++m) cu.org[m] = gc[m] - gs.half;
+    for (int m = 0; m < 3; ++m) org[m] = gc[m] - gs.half;
 
     if (rad_table) {
         if (tid < Tg) s_rad[tid] = my_rad;
@@ -231,13 +223,10 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
                 r = gs.radius_scale * (gs.radius_type_indexed ? s_rad[tg] : my_r[u]);
                 reach = gs.binary ? r : r * gs.c;
             }
-            bool live = (r > 0.0f) && (reach < 1.0e30f);
-            for (int k = 0; k < 3; ++k)     // also false for NaN / infinite coordinates
-                live = live && (my_p[u][k] >= cu.org[k] - reach - cu.pad) &&
-                       (my_p[u][k] <= cu.org[k] + cu.span + reach + cu.pad);
+            const bool live = meets_grid(gs, org, my_p[u], r, reach);
             int bin = D + 2;
             if (live) {
-                const float f = floorf((my_p[u][0] - cu.org[0]) * gs.inv_res);
+                const float f = floorf((my_p[u][0] - org[0]) * gs.inv_res);
                 bin = f < 0.0f ? 0 : (f >= (float)D ? D + 1 : (int)f + 1);
                 atomicMax(&s_rmax[tg], __float_as_int(r));      // r > 0: ordered like ints
                 my_w[u] = r;
@@ -293,7 +282,7 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         // plane i is reached from bins [i - Rv, i + Rv + 1]
         const float rmax = VECTOR ? vec_reach
                                   : __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
-        const int Rv = (int)ceilf(rmax * gs.inv_res + cu.pad) + 1;
+        const int Rv = (int)ceilf(rmax * gs.inv_res + 1.0e-3f * gs.res) + 1;
         const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
         ws.range[((size_t)b * T + tg) * D + i] = make_int2(s_pos[tg * nb + lo], s_pos[tg * nb + hi + 1]);
     }
@@ -373,12 +362,10 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
         for (int m = 32; m > 0; m >>= 1) vec_reach = fmaxf(vec_reach, __shfl_xor(vec_reach, m));
         if (!gs.binary) vec_reach *= gs.c;
     }
-    Culler cu;
-    cu.pad = 1.0e-3f * gs.res;
-    cu.span = (float)(D - 1) * gs.res;
+    float org[3];                   // the grid's first point
     float gc[3];
     grid_center(bt.sub, X, b, bs, gc);
-    for (int m = 0; m < 3; ++m) cu.org[m] = gc[m] - gs.half;
+    for (int m = 0; m < 3; ++m) org[m] = gc[m] - gs.half;
     if (p == 0) {
         if (tid < 9) ws.rot[b * 12 + tid] = (float)X.R[tid];
         if (tid < 3) ws.gcen[b * 4 + tid] = gc[tid];
@@ -406,12 +393,10 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
         apply_xform(X, w.c, pp);
         r = VECTOR ? 1.0f : gs.radius_scale * w.r;
         const float reach = VECTOR ? vec_reach : (gs.binary ? r : r * gs.c);
-        bool live = (r > 0.0f) && (reach < 1.0e30f);
-        for (int k = 0; k < 3; ++k)     // also false for NaN / infinite coordinates
-            live = live && (pp[k] >= cu.org[k] - reach - cu.pad) && (pp[k] <= cu.org[k] + cu.span + reach + cu.pad);
+        const bool live = meets_grid(gs, org, pp, r, reach);
         int bin = D + 2;
         if (live) {
-            const float f = floorf((pp[0] - cu.org[0]) * gs.inv_res);
+            const float f = floorf((pp[0] - org[0]) * gs.inv_res);
             bin = f < 0.0f ? 0 : (f >= (float)D ? D + 1 : (int)f + 1);
         } else {
             r = 0.0f;
@@ -539,7 +524,7 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
             const int tg = e / D, i = e - tg * D;
             // plane i is reached from bins [i - Rv, i + Rv + 1]
             const float rmax = VECTOR ? vec_reach : __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
-            const int Rv = (int)ceilf(rmax * gs.inv_res + cu.pad) + 1;
+            const int Rv = (int)ceilf(rmax * gs.inv_res + 1.0e-3f * gs.res) + 1;
             const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
             ws.range[((size_t)b * T + tA + tg) * D + i] =
                 make_int2(first + s_pos[tg * nb + lo], first + s_pos[tg * nb + hi + 1]);

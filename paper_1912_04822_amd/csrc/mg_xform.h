@@ -12,6 +12,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "mg_common.h"
+
 namespace mg {
 
 struct Xform {
@@ -68,6 +70,18 @@ __device__ inline void apply_xform(const Xform &X, const float *p, float *o)
     o[0] = (float)((((X.R[0] * u0 + X.R[1] * u1) + X.R[2] * u2) + X.c[0]) + X.t[0]);
     o[1] = (float)((((X.R[3] * u0 + X.R[4] * u1) + X.R[5] * u2) + X.c[1]) + X.t[1]);
     o[2] = (float)((((X.R[6] * u0 + X.R[7] * u1) + X.R[8] * u2) + X.c[2]) + X.t[2]);
+}
+
+// Whether an atom placed at p can touch the grid whose first point is `org`: its radius and how far it
+// reaches are usable and the cube about it meets the grid's box (padded by 1e-3 steps).  The one test of
+// every kernel that places atoms: grids and gradients are the same whichever of them does.
+__device__ inline bool meets_grid(const GridSpec &gs, const float (&org)[3], const float (&p)[3], float r, float reach)
+{
+    const float span = (float)(gs.D - 1) * gs.res, pad = 1.0e-3f * gs.res;
+    bool live = (r > 0.0f) && (reach < 1.0e30f);
+    for (int k = 0; k < 3; ++k)     // also false for NaN / infinite coordinates
+        live = live && (p[k] >= org[k] - reach - pad) && (p[k] <= org[k] + span + reach + pad);
+    return live;
 }
 
 // the inverse map, same precision and rounding:  x = R^T ((x' - t) - c) + c
