@@ -68,7 +68,6 @@ struct BwdParams {
     unsigned long long wg_magic;    // ceil(2^64 / wgs_per_example), 0 if that is 1
     float sk, inv_sk, g2k, c2k;     // sqrt(k), 1/sqrt(k), g^2 k, c^2 k with k = 2 log2(e)
     float hA, hAck;         // A/2, (A/2) c sqrt(k): -f/4 = clamp(hAck / x' - hA, 0, 1) in the tail
-    float sAk, cA;          // sqrt(A/k), c sqrt(A)
     float ng2k, nfA, fAck;  // vector types (reduce_group): -g^2 k, -2g^2, 2g^2 c sqrt(k)
     float tk, tc;           // ... 2g / sqrt(k), 2g c
 };
@@ -128,7 +127,7 @@ __device__ inline bool atom_box(const GridSpec &gs, float reach, const float4 &a
 }
 
 // Accumulate over one channel volume, in coordinates scaled to units of r/sqrt(k),
-// k = 2 log2(e) (then exp(-2x^2) = exp2(-x'^2)):  (sx, sy, sz) += sum G (-f/4) u',  sv += sum G rho.
+// k = 2 log2(e) (then exp(-2x^2) = exp2(-x'^2)):  (sx, sy, sz) += sum G (-f/4) u'.
 //   -f/4 = exp2(-x'^2)                                  x'^2 <= g^2 k
 //        = clamp((A/2) c sqrt(k) / x' - A/2, 0, 1)      beyond (zero from the cutoff on)
 // One slot: the four voxels k4 .. k4+3 of the grid row at float offset `row_off` of the
@@ -186,9 +185,8 @@ __device__ inline void load_slot(const BwdParams &p, const GT *Gc, unsigned row_
     d.ux = ux; d.uy = uy; d.k4 = k4;
 }
 
-template <bool WANT_VALUE>
 __device__ inline void reduce_slot(const BwdParams &p, float step, float azs, const SlotData &d,
-                                   float &sx, float &sy, float &sz, float &sv)
+                                   float &sx, float &sy, float &sz)
 {
     const float ux = d.ux, uy = d.uy;
     const int k4 = d.k4;
@@ -207,21 +205,16 @@ __device__ inline void reduce_slot(const BwdParams &p, float step, float azs, co
         const float gf = gv[u] * f;
         fsum += gf;
         sz = fmaf(gf, uz, sz);
-        if (WANT_VALUE) {
-            const float tl = __builtin_amdgcn_fmed3f(fmaf(-(x2 * rs), p.sAk, p.cA), 0.0f, 1.0f);     // sqrt(A) (c - x), clamped to [0, 1]
-            const float rho = x2 <= p.g2k ? e : tl * tl;
-            sv = fmaf(gv[u], rho, sv);
-        }
     }
     sx = fmaf(fsum, ux, sx);
     sy = fmaf(fsum, uy, sy);
 }
 
 // Every slot of the box (boxes with very many segments per row).
-template <bool ALIGNED, bool WANT_VALUE, typename GT>
+template <bool ALIGNED, typename GT>
 __device__ inline void reduce_channel_box(const BwdParams &p, const GT *Gc, const float4 &a,
                                           float r, const Box &bx, float ox, float oy, float oz,
-                                          float &sx, float &sy, float &sz, float &sv)
+                                          float &sx, float &sy, float &sz)
 {
     const GridSpec &gs = p.gs;
     const int per_plane = bx.nr * bx.ns;
@@ -242,22 +235,21 @@ __device__ inline void reduce_channel_box(const BwdParams &p, const GT *Gc, cons
         SlotData d;
         load_slot<ALIGNED, false>(p, Gc, (unsigned)((bx.ilo + pi) * gs.D + bx.jlo + row) * (unsigned)gs.D,
                            (bx.seg0 + seg) << 2, ux, uy, d);
-        reduce_slot<WANT_VALUE>(p, step, azs, d, sx, sy, sz, sv);
+        reduce_slot(p, step, azs, d, sx, sy, sz);
     }
 }
 
 // Only the slots that meet the cutoff sphere.  `marks` is this wavefront's kSlotCap bytes of
 // LDS, all zero on entry and on return.
 // The channel is G + t * D3 (index types: t comes with the record, from the workspace).
-template <bool ALIGNED, bool WANT_VALUE, typename GT>
+template <bool ALIGNED, typename GT>
 __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, size_t D3,
                                       const float4 &a, float r, const Box &bx, float ox, float oy,
                                       float oz, unsigned char *marks, float &sx, float &sy,
-                                      float &sz, float &sv)
+                                      float &sz)
 {
     if (bx.ns > kMaxCulledSegs || bx.np * bx.nr > kMaxCulledRows) {
-        reduce_channel_box<ALIGNED, WANT_VALUE>(p, G + (size_t)t * D3, a, r, bx, ox, oy, oz, sx, sy,
-                                                sz, sv);
+        reduce_channel_box<ALIGNED>(p, G + (size_t)t * D3, a, r, bx, ox, oy, oz, sx, sy, sz);
         return;
     }
     const GridSpec &gs = p.gs;
@@ -336,7 +328,7 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
                 SlotData d;
                 load_slot<ALIGNED, true>(p, Gc, off0 + ((unsigned)pi * D + (unsigned)jr) * D, k4, ux,
                                    uy, d);
-                reduce_slot<WANT_VALUE>(p, step, azs, d, sx, sy, sz, sv);
+                reduce_slot(p, step, azs, d, sx, sy, sz);
             }
         }
         lds_sync();
@@ -621,10 +613,10 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         const int t = t_rec;
         const float r = a.w;
         Box bx;
-        float sx = 0.0f, sy = 0.0f, sz = 0.0f, sv = 0.0f;
+        float sx = 0.0f, sy = 0.0f, sz = 0.0f;
         if (atom_box(gs, r * gs.c, a, ox, oy, oz, bx))
-            reduce_channel<ALIGNED, false>(p, reinterpret_cast<const GT *>(p.G) + (size_t)b * T * D3, t, D3, a, r, bx, ox, oy, oz,
-                                           marks, sx, sy, sz, sv);
+            reduce_channel<ALIGNED>(p, reinterpret_cast<const GT *>(p.G) + (size_t)b * T * D3, t, D3, a, r, bx, ox, oy, oz,
+                                    marks, sx, sy, sz);
         // -4 (the sums hold -f/4) / r^2 times r/sqrt(k) (they are in scaled units)
         const float inv_r2 = -4.0f * __builtin_amdgcn_rcpf(r * p.sk);
         tx = wave_sum(sx) * inv_r2;
@@ -795,8 +787,6 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
         p.c2k = (float)((double)gs.c * (double)gs.c * k);
         p.hA = (float)(0.5 * (double)gs.A);
         p.hAck = (float)(0.5 * (double)gs.A * (double)gs.c * std::sqrt(k));
-        p.sAk = (float)std::sqrt((double)gs.A / k);
-        p.cA = (float)((double)gs.c * std::sqrt((double)gs.A));
         // (beyond x = 100 the density is 0 in float whatever the branch: larger g need no larger constants)
         const double g2 = std::fmax(std::fmin((double)gs.g2, 1.0e4), 1.0e-30), g = std::sqrt(g2), c = g + 0.5 / g;
         p.ng2k = (float)(-g2 * k);

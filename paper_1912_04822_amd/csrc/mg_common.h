@@ -65,7 +65,7 @@ __host__ __device__ inline int source_example(int subgrid_count, int e)
 //                         a bin, in atom order.  Slots first+live .. first+all
 //                         hold w = 0.
 //   idx   [B][N] int32    original atom index of each record
-//   meta  [B][T] int4     {first, live, all, 1}
+//   meta  [B][T] int4     {first, live, all, unused}
 //   range [B][T][D] int2  for x-plane i: the span [r0, r1) of records, counted from
 //                         the example's first record rec[b][0], that can reach
 //                         the plane; r0 and r1 do not decrease with i, so planes

@@ -115,8 +115,8 @@ struct FwdParams {
     unsigned ka_skip;               // 0, 1, 3 or 7: wavefronts whose id has none of these bits set do the read
     float sk;           // sqrt(k), k = 2 log2(e)
     float inv_sk;
-    float g2k, c2k;     // g^2 k, c^2 k
-    float sA, cA;       // tail coefficients
+    float g2k, c2k;     // g^2 k (index types), c^2 k
+    float sA, cA;       // tail coefficients (index types)
     float vg2k, tk, tc; // vector types: g^2 k, 2g/sqrt(k), 2g c
 };
 
@@ -427,7 +427,6 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
         const int n4 = cx.n >> 2;                   // even: D^3 and the tile size are multiples of 8
         float4 *dst4 = reinterpret_cast<float4 *>(dst);         // float grids
         Float4E *dst4e = reinterpret_cast<Float4E *>(dst);
-        double2 *dst2 = reinterpret_cast<double2 *>(dst);       // double grids
         const float4 *src4 = reinterpret_cast<const float4 *>(cx.tile);
         // Constant trip count, fully unrolled; the tile comes from LDS into registers
         // under a uniform branch (zeros otherwise), so that the stores below are one
@@ -454,19 +453,12 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
             }
             const int o = (it * NW + cx.wave) * 128 + cx.lane * 2;
             if (o < n4) {
-                if (kWide) {        // the lane's 8 values are 64 contiguous bytes: four 16-byte stores
-                    dst2[2 * o] = make_double2((double)a.x, (double)a.y);
-                    dst2[2 * o + 1] = make_double2((double)a.z, (double)a.w);
-                    dst2[2 * o + 2] = make_double2((double)b.x, (double)b.y);
-                    dst2[2 * o + 3] = make_double2((double)b.z, (double)b.w);
+                if (LOOSE) {
+                    dst4e[o] = Float4E{a.x, a.y, a.z, a.w};
+                    dst4e[o + 1] = Float4E{b.x, b.y, b.z, b.w};
                 } else {
-                    if (LOOSE) {
-                        dst4e[o] = Float4E{a.x, a.y, a.z, a.w};
-                        dst4e[o + 1] = Float4E{b.x, b.y, b.z, b.w};
-                    } else {
-                        dst4[o] = a;
-                        dst4[o + 1] = b;
-                    }
+                    dst4[o] = a;
+                    dst4[o + 1] = b;
                 }
             }
         }
@@ -1165,7 +1157,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
     cx.rowB = 0;
     cx.res = gs.res;
     cx.inv_res = gs.inv_res;
-    cx.g2k = p.g2k; cx.c2k = p.c2k; cx.sA = p.sA; cx.cA = p.cA;
+    cx.c2k = p.c2k;
     cx.debug = 0;
     cx.cen_x = cen.x; cx.cen_y = cen.y; cx.cen_z = cen.z;
     cx.hD = 0.5f * (float)(D - 1);
@@ -1419,10 +1411,7 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
     const double k = 2.8853900817779268;        // 2 / ln 2
     p.sk = (float)std::sqrt(k);
     p.inv_sk = (float)(1.0 / std::sqrt(k));
-    p.g2k = (float)((double)gs.g2 * k);
     p.c2k = (float)((double)gs.c * (double)gs.c * k);
-    p.sA = (float)std::sqrt((double)gs.A / k);
-    p.cA = (float)((double)gs.c * std::sqrt((double)gs.A));
     // (beyond x = 100 the density is 0 in float whatever the branch: larger g need no larger constants)
     const double g2 = std::fmax(std::fmin((double)gs.g2, 1.0e4), 1.0e-30), gr = std::sqrt(g2);
     p.vg2k = (float)(g2 * k);

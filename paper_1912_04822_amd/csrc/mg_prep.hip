@@ -107,7 +107,7 @@ __device__ inline void rank_channels(const Batch &bt, const Workspace &ws, int b
 // ---------------------------------------------------------------------------
 constexpr int kExThreads = 1024;            // the larger of the two block sizes
 constexpr int kExMaxAtoms = 8192;           // 8 atoms per thread (4 in the kernel for N <= 4096)
-constexpr int kExMaxKeys = 12288;
+constexpr size_t kExMaxLds = 64 * 1024;     // two words per (type, bin) key, two per type and two bytes per atom
 
 struct ExLayout {       // LDS, in ints
     int K, Tg, N;
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         const int first = s_pos[tg * nb];
         const int dead = s_pos[tg * nb + D + 2];
         const int end = tg + 1 < Tg ? s_pos[(tg + 1) * nb] : total;
-        ws.meta[(size_t)b * T + tg] = make_int4(first, dead - first, end - first, 1);
+        ws.meta[(size_t)b * T + tg] = make_int4(first, dead - first, end - first, 0);
     }
     for (int e = tid; e < Tg * D; e += NT) {
         const int tg = e / D, i = e - tg * D;
@@ -518,7 +518,7 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     if (!VECTOR || p == 0) {
         for (int tg = tid; tg < Tg; tg += NT) {
             const int f = s_pos[tg * nb], dead = s_pos[tg * nb + D + 2], end = s_pos[(tg + 1) * nb];
-            ws.meta[(size_t)b * T + tA + tg] = make_int4(first + f, dead - f, end - f, 1);
+            ws.meta[(size_t)b * T + tA + tg] = make_int4(first + f, dead - f, end - f, 0);
         }
         for (int e = tid; e < Tg * D; e += NT) {
             const int tg = e / D, i = e - tg * D;
@@ -683,9 +683,10 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     L.Tg = vec ? 1 : bt.T;
     L.N = bt.N;
     const long long K = (long long)L.Tg * (gs.D + 3);
-    L.K = (int)(K <= kExMaxKeys ? K : 0);
+    const bool fits = bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
+    L.K = fits ? (int)K : 0;
     const size_t lds_bytes = (size_t)L.ints() * sizeof(int);
-    if (K <= kExMaxKeys && bt.N <= kExMaxAtoms && lds_bytes <= 64 * 1024) {
+    if (fits && lds_bytes <= kExMaxLds) {
         const dim3 grd(bt.B);
         // 512 threads while they still hold all the atoms four apiece: half as many wavefronts
         // behind every barrier (1 us less per call at 2040 atoms; 256 threads with eight atoms
