@@ -388,13 +388,13 @@ template <bool ALIGNED, int ITERS, int NW, typename OUT, bool VECTOR = false, bo
 __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, bool fixed, unsigned neg = 0u)
 {
     const auto value = [&](float bits) {
+        return (float)__float_as_uint(bits) * (VECTOR ? 1.0f / (float)(1 << kVecFixedBits) : 1.0f / kFixedOne);
+    };
+    const auto signed_value = [&](float bits) {
         const unsigned i = __float_as_uint(bits);
-        if (VECTOR) {
-            const bool minus = i + neg < neg;       // [-neg, 0)
-            const float v = (float)(minus ? 0u - i : i) * (1.0f / (float)(1 << kVecFixedBits));
-            return minus ? -v : v;
-        }
-        return (float)i * (1.0f / kFixedOne);
+        const bool minus = i + neg < neg;           // [-neg, 0)
+        const float v = (float)(minus ? 0u - i : i) * (1.0f / (float)(1 << kVecFixedBits));
+        return minus ? -v : v;
     };
     constexpr bool kWide = sizeof(OUT) == 8;        // a grid of doubles: the same values, widened
     if (ALIGNED && kWide) {
@@ -412,9 +412,10 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
             for (int k = 0; k < 4; ++k) {
                 const int o = ((it * NW + cx.wave) * 4 + k) * 64 + cx.lane;
                 v[k] = touched ? src2[o] : make_float2(0.0f, 0.0f);
-                if (convert) {
+                if (convert && VECTOR && neg != 0u)
+                    v[k] = make_float2(signed_value(v[k].x), signed_value(v[k].y));
+                else if (convert)
                     v[k] = make_float2(value(v[k].x), value(v[k].y));
-                }
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -447,7 +448,10 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
 #pragma unroll
         for (int it = 0; it < MINE; ++it) {
             float4 a = v[2 * it], b = v[2 * it + 1];
-            if (convert) {
+            if (convert && VECTOR && neg != 0u) {
+                a = make_float4(signed_value(a.x), signed_value(a.y), signed_value(a.z), signed_value(a.w));
+                b = make_float4(signed_value(b.x), signed_value(b.y), signed_value(b.z), signed_value(b.w));
+            } else if (convert) {
                 a = make_float4(value(a.x), value(a.y), value(a.z), value(a.w));
                 b = make_float4(value(b.x), value(b.y), value(b.z), value(b.w));
             }
@@ -466,7 +470,7 @@ __device__ inline void store_tile(const TileCtx &cx, OUT *dst, bool touched, boo
         for (int o = cx.wave * 64 + cx.lane; o < cx.n; o += 64 * NW) {
             float v = 0.0f;
             if (touched)
-                v = fixed ? value(cx.tile[o]) : cx.tile[o];
+                v = !fixed ? cx.tile[o] : VECTOR && neg != 0u ? signed_value(cx.tile[o]) : value(cx.tile[o]);
             dst[o] = (OUT)v;
         }
     }
@@ -1318,7 +1322,7 @@ __global__ __launch_bounds__(64 * NW) void forward_vector_kernel(FwdParams p)
         bound = cx.shared[0];
         any = cx.shared[1] != 0;
 #pragma unroll
-        for (int q = 0; q < kVecGroup; ++q) negs[q] = cx.shared[4 + q];
+        for (int q = 0; q < kVecGroup; ++q) negs[q] = __builtin_amdgcn_readfirstlane(cx.shared[4 + q]);
     }
     if (!BINARY && bound > limit) {         // uniform over the workgroup: the sums may not fit; again, in floats
         if (NW > 1) __syncthreads();        // shared[] has been read by all
