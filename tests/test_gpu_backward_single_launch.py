@@ -11,7 +11,8 @@ from test_gpu_parity import dev, mg  # noqa: E402,F401
 
 
 @pytest.mark.parametrize("B,N,T,D", [(1, 1, 1, 1), (3, 5, 70, 12), (2, 130, 4, 13), (7, 1170, 3, 10),
-                                     (24, 2048, 5, 8)])
+                                     (24, 2048, 5, 8),      # the most atoms of index types ...
+                                     (4, 2048, 5, 8)])      # ... and of vector types
 @pytest.mark.parametrize("kind", ["type", "atom", "vector"])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
 def test_equals_the_tables_bit_for_bit(mg, B, N, T, D, kind, dtype):

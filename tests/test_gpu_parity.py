@@ -125,8 +125,8 @@ def test_forward_ragged_small_unaligned_grid(mg, grm, scale):
 @pytest.mark.parametrize("N,single_type", [(5000, False), (9000, False), (9000, True)])
 def test_forward_backward_many_atoms_per_example(mg, N, single_type):
     """N = 5000: eight atoms per thread in the one-workgroup-per-example prep kernel.  N = 9000 is
-    past what that kernel takes (the per-group kernel runs instead); with every atom of one type
-    the group is also too long for that kernel to bin by x-plane (records stay in atom order)."""
+    past what that kernel takes (several workgroups share an example instead), also with every atom
+    of one type."""
     w = workloads.ragged_small(seed=11, B=2, N=N, T=3, D=16, resolution=0.5)
     if single_type:
         w.types[:] = 1
@@ -147,7 +147,7 @@ def test_forward_backward_many_atoms_per_example(mg, N, single_type):
 
 def test_forward_backward_many_channels(mg):
     """T * (D + 3) = 300 * 27 (type, x-bin) pairs are more than the one-workgroup-per-example prep
-    kernel keeps in LDS: the per-group kernel runs instead."""
+    kernel keeps in LDS: several workgroups share an example instead."""
     w = workloads.ragged_small(seed=23, B=2, N=400, T=300, D=24, resolution=0.5)
     got = run_forward_index(mg, w)
     ref = oracle_forward_index(w)
