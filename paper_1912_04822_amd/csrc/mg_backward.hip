@@ -26,8 +26,9 @@
 // the lanes numbers the live slots, and slot s finds its row through a byte
 // array in LDS (the first slot of each lane's rows is marked with the lane, a
 // running maximum over the slots gives the owner) and one register exchange.
-// The kernel is bound by vector arithmetic (two transcendentals per voxel), so
-// the time goes with the number of voxels evaluated.  The three partial sums
+// Index types are bound by vector instruction issue (3.745e7 instructions on 50 x 2040 atoms,
+// 28 x 48^3: 61 of 72 us; a third of them the density, the rest finding rows and slots), with the
+// arrival of the scattered lines close behind (45 % of their rate).  The three partial sums
 // are reduced across the wavefront by DPP adds in a fixed order.  Records are grouped by
 // channel (and, within a channel, by x-plane), so neighbouring wavefronts read
 // the same part of the same channel volume.
@@ -304,9 +305,8 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
         // Round k works on slots 64k .. 64k+63, one per lane.  (Issuing the reads of two or three
         // rounds before the arithmetic of the first was measured slower -- 69 against 62 us with
         // the gradient grid partly in the memory-side cache, 102 against 100 us with a grid that
-        // has to come from HBM: the kernel fetches every 128-byte line of the gradient grid that
-        // holds an in-cutoff voxel exactly once, 270 MB on the 48^3 batch, and runs at the rate
-        // those scattered lines arrive, whatever the wavefronts have in flight.)
+        // has to come from HBM: more requests in flight do not shorten a wavefront's chain of
+        // dependent trips, and instruction issue comes before the lines as the bound.)
         int carry = 0;
         for (int base = 0; base < total; base += 64) {
             const int sidx = base + lane;

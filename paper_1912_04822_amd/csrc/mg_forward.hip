@@ -1376,8 +1376,8 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
                                         hipStream_t stream)
 {
     // 2048-float tiles and four wavefronts per workgroup: the four channel tiles of a group take
-    // 33 KB of LDS, so four workgroups (sixteen wavefronts; 98 registers would allow twenty) fit a CU.
-    // Measured on the 48^3 batch of 50 x 2040 atoms x 28 channels: 0.50 ms; relative to it, 1024
+    // 33 KB of LDS, so four workgroups (sixteen wavefronts, what 98 registers allow too) fit a CU.
+    // Measured on the 48^3 batch of 50 x 2040 atoms x 28 channels (0.51 ms now): relative to it, 1024
     // floats x 2 wavefronts +10 % (each tile tests the atoms in reach anew), 2048 x 2 and 1024 x 1
     // +43 % (too few wavefronts), 512 x 1 +33 %.  A grid of doubles takes 512 voxels per tile.
     if (tile_floats != 512 && tile_floats != 1024 && tile_floats != 2048) tile_floats = 2048;
