@@ -54,6 +54,7 @@ struct BwdParams {
     const int4 *meta;
     const float *rot;
     const int *rchan;       // [B][N] channel of each record (index types)
+    const int *chan_order;  // [B][T] channels in order of radius (vector types)
     const float *weights;
     const float *radii;
     const float *gcen;
@@ -69,8 +70,9 @@ struct BwdParams {
     unsigned long long wg_magic;    // ceil(2^64 / wgs_per_example), 0 if that is 1
     float sk, inv_sk, g2k, c2k;     // sqrt(k), 1/sqrt(k), g^2 k, c^2 k with k = 2 log2(e)
     float hA, hAck;         // A/2, (A/2) c sqrt(k): -f/4 = clamp(hAck / x' - hA, 0, 1) in the tail
-    float ng2k, nfA, fAck;  // vector types (reduce_group): -g^2 k, -2g^2, 2g^2 c sqrt(k)
-    float tk, tc;           // ... 2g / sqrt(k), 2g c
+    float k;                // vector types: k
+    float ng2k, nfA, fAc;   // ... -g^2 k, -2g^2, 2g^2 c
+    float tg, tc;           // ... 2g, 2g c
 };
 
 // a value that is the same in all lanes, kept in a scalar register
@@ -338,55 +340,136 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
 }
 
 // ---------------------------------------------------------------------------
-// Vector types: kChanGroup channels of one atom in one pass.  The channels differ only in
-// radius, so the slots are listed once, for the widest sphere of the group (radius rmax),
-// and every voxel's x'^2 (in units of rmax/sqrt(k)) is rescaled per channel:
-//   x'^2_q = x'^2 (rmax/r_q)^2.   Beyond channel q's own cutoff f and rho are 0 by their
-// formulas, so the voxels the narrower spheres do not reach add nothing.
+// Vector types: kChanGroup channels of one atom in one pass.  The channels differ only in radius, so
+// the slots are found once, for the widest sphere of the group.  Beyond channel q's own cutoff f and rho
+// are 0 by their formulas, so the voxels the narrower spheres do not reach add nothing.
+// What depends on the channel's radius and the atom's weight is worked out once per atom, lane l for the
+// channel of rank l (the tables' ranking where there are tables), and read into scalar registers group by
+// group; the four weight sums of a group are reduced together (19 instructions instead of 52) and
+// kept by the lanes of their channels, so that an atom's weight gradients leave in one store.  Distances
+// are in Angstrom for all groups.  50 x 2040 atoms, 28 x 48^3: 778 instead of 907 us a call; 8 x 12 channels
+// 87 / 95; 2 x 100 channels of 32^3 126 / 165; few channels alike.
+// Bound by vector instruction issue and, as close, by the lines that the L2s deliver: the loads alone,
+// 128-byte lines for every 26 bytes of a chord, take 740 us (26 TB/s).
+// Measured and not kept: the slots of an atom listed once in LDS for all its channels, in shells of the
+// row's distance, so that rounds of far slots take the tail's half of the density only: 33 % fewer
+// loads issued and 20 % fewer instructions, and no faster (792 us; 0.25 A: 332 against 256; only 24^3
+// at 1 A gains, 225 against 255).
 // ---------------------------------------------------------------------------
 constexpr int kChanGroup = 4;
+constexpr float kTinyDistance2 = 1.0e-30f;      // added to squared distances whose roots are divided by
 
-struct GroupCoef {
-    float nr2[kChanGroup];          // -(rmax / r_q)^2
-    float fq[kChanGroup];           // fA c sqrt(k) r_q / rmax: tail of -f/4 (see reduce_group)
-    float tq[kChanGroup];           // -2 g/sqrt(k) rmax / r_q: root of the tail of rho
-    float cq[kChanGroup];           // -4 w_q rmax / (sqrt(k) r_q^2): channel q's share of the coordinate sums
-    bool live[kChanGroup];          // r_q > 0 and t0 + q < T (uniform over the wavefront)
+struct GroupCoef {              // wave-uniform
+    float nr2[kChanGroup];          // -k / r_q^2
+    float fq[kChanGroup];           // 2 g^2 c r_q: tail of -f/4
+    float tq[kChanGroup];           // -2g / r_q: root of the tail of rho
+    float cq[kChanGroup];           // -4 w_q / r_q^2: channel q's share of the coordinate sums
+    unsigned live;                  // bit q: r_q > 0
 };
 
-// body(row_off, k4, ux, uy) for every slot of the box that meets the sphere of radius r:
-// the slot is the four voxels k4 .. k4+3 of the row at float offset row_off of a channel;
-// ux, uy are the row's distances in units of r/sqrt(k).  The same enumeration as
-// reduce_channel (marks: this wavefront's kSlotCap bytes of LDS, zero on entry and return).
-template <bool ALIGNED, typename Body>
-__device__ inline void for_each_slot(const BwdParams &p, const float4 &a, float r, const Box &bx,
-                                     float ox, float oy, float oz, unsigned char *marks,
-                                     Body body)
+// The four voxels from float `off` of the channel at Gc on, the first `back` of which count as 0.
+template <bool ALIGNED, typename GT>
+__device__ inline void load_voxels(const BwdParams &p, const GT *Gc, unsigned off, int back, float (&gv)[4])
+{
+    const GT *src = Gc + off;
+    if (!ALIGNED && p.gs.D < 4) {           // (a row is one slot, from its first voxel)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) gv[u] = u < p.gs.D ? (float)src[u] : 0.0f;
+        return;
+    }
+    if (sizeof(GT) == 8) {      // a grid of doubles: two 16-byte loads, narrowed
+        const Double2E *s2 = reinterpret_cast<const Double2E *>(src);
+        const Double2E lo = s2[0], hi = s2[1];
+        gv[0] = (float)lo.x; gv[1] = (float)lo.y; gv[2] = (float)hi.x; gv[3] = (float)hi.y;
+    } else {
+        const Float4E g4 = *reinterpret_cast<const Float4E *>(src);
+        gv[0] = g4.x; gv[1] = g4.y; gv[2] = g4.z; gv[3] = g4.w;
+    }
+    if (!ALIGNED) {             // voxels that belong to the slot before count as 0
+#pragma unroll
+        for (int u = 0; u < 3; ++u) gv[u] = u < back ? 0.0f : gv[u];
+    }
+}
+
+// One slot against the channels of a group; ux, uy: the distances of its row from the atom, uz0: that of its first
+// voxel.
+// The two branches of the density and of its slope are taken as a product without a select: with
+// E = exp(-2 min(x, g)^2),
+//   rho  = E clamp(2g (c - x), 0, 1)^2        (2g (c - g) = 1, and A = 4 g^2 exp(-2g^2))
+//   -f/4 = E clamp(2g^2 (c/x - 1), 0, 1)      (2g^2 (c/g - 1) = 1)
+// so the channels share one reciprocal square root per voxel (the distance is the square times that).
+//   (sx, sy, sz) += sum_q cq sum G_q f_q u,  sv[q] += sum G_q rho_q
+template <bool ALIGNED, bool WANT_W, bool ALL_LIVE, typename GT>
+__device__ inline void reduce_slot_group(const BwdParams &p, const GT *const (&Gq)[kChanGroup], unsigned off, int back,
+                                         float ux, float uy, float uz0, const GroupCoef &gc, float ng2k, float nfA,
+                                         float tc, float &sx, float &sy, float &sz, float (&sv)[kChanGroup])
+{
+    const float b2 = fmaf(ux, ux, fmaf(uy, uy, kTinyDistance2));
+    float gv[kChanGroup][4];
+#pragma unroll
+    for (int q = 0; q < kChanGroup; ++q)
+        if (ALL_LIVE || (gc.live >> q) & 1u) load_voxels<ALIGNED>(p, Gq[q], off, back, gv[q]);
+    float fsum = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float uz = fmaf(-(float)u, p.gs.res, uz0);
+        const float x2 = fmaf(uz, uz, b2);
+        const float rs = __builtin_amdgcn_rsqf(x2), d = x2 * rs;
+        float F = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kChanGroup; ++q) {
+            if (!ALL_LIVE && !((gc.live >> q) & 1u)) continue;
+            const float ge = gv[q][u] * __builtin_amdgcn_exp2f(fmaxf(x2 * gc.nr2[q], ng2k));
+            const float ft = __builtin_amdgcn_fmed3f(fmaf(gc.fq[q], rs, nfA), 0.0f, 1.0f);
+            F = fmaf(gc.cq[q], ge * ft, F);
+            if (WANT_W) {
+                const float tl = __builtin_amdgcn_fmed3f(fmaf(gc.tq[q], d, tc), 0.0f, 1.0f);
+                sv[q] = fmaf(ge * tl, tl, sv[q]);
+            }
+        }
+        fsum += F;
+        sz = fmaf(F, uz, sz);
+    }
+    sx = fmaf(fsum, ux, sx);
+    sy = fmaf(fsum, uy, sy);
+}
+
+// Every slot of the box that meets the sphere of radius `reach` about the atom (the same enumeration as
+// reduce_channel; marks: this wavefront's kSlotCap bytes of LDS, zero on entry and return).
+template <bool ALIGNED, bool WANT_W, bool ALL_LIVE, typename GT>
+__device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kChanGroup], const float4 &a, float reach,
+                                    const Box &bx, float ox, float oy, float oz, unsigned char *marks,
+                                    const GroupCoef &gc, float &sx, float &sy, float &sz, float (&sv)[kChanGroup])
 {
     const GridSpec &gs = p.gs;
     const int lane = (int)(threadIdx.x & 63u);
     const unsigned D = (unsigned)gs.D;
-    const float s = p.sk * __builtin_amdgcn_rcpf(r), step = gs.res * s;
-    const float ux0 = (a.x - (ox + (float)bx.ilo * gs.res)) * s;
-    const float uy0 = (a.y - (oy + (float)bx.jlo * gs.res)) * s;
+    const float ux0 = a.x - (ox + (float)bx.ilo * gs.res), uy0 = a.y - (oy + (float)bx.jlo * gs.res);
+    const float az = a.z - oz, fz = az * gs.inv_res;        // fz: the atom's z in grid steps
     const unsigned off0 = ((unsigned)bx.ilo * D + (unsigned)bx.jlo) * D;   // the box's first row
+    float ng2k = p.ng2k, nfA = p.nfA, tc = p.tc;
+    asm volatile("" : "+v"(ng2k), "+v"(nfA), "+v"(tc));
+    // the slot of voxels k4 .. k4 + 3 of row (pi, jr) of the box
+    const auto slot = [&](int pi, int jr, int k4) {
+        const int back = ALIGNED ? 0 : max(k4 - max(gs.D - 4, 0), 0);      // reaches past the row's end
+        k4 -= back;
+        reduce_slot_group<ALIGNED, WANT_W, ALL_LIVE>(p, Gq, off0 + ((unsigned)pi * D + (unsigned)jr) * D + (unsigned)k4, back,
+                                                     fmaf(-(float)pi, gs.res, ux0), fmaf(-(float)jr, gs.res, uy0),
+                                                     fmaf(-(float)k4, gs.res, az), gc, ng2k, nfA, tc, sx, sy, sz, sv);
+    };
     if (bx.ns > kMaxCulledSegs || bx.np * bx.nr > kMaxCulledRows) {     // a very large box: every slot of it
         const int per_plane = bx.nr * bx.ns;
         const int slots = bx.np * per_plane;        // at most D^3 / 4 < 2^31
         for (int sl = lane; sl < slots; sl += 64) {
             const int pi = sl / per_plane;          // integer division: exact for any box
             const int rem = sl - pi * per_plane;
-            const int row = rem / bx.ns;
-            const int seg = rem - row * bx.ns;
-            body(off0 + ((unsigned)pi * D + (unsigned)row) * D, (bx.seg0 + seg) << 2,
-                 fmaf(-(float)pi, step, ux0), fmaf(-(float)row, step, uy0));
+            const int jr = rem / bx.ns;
+            slot(pi, jr, (bx.seg0 + rem - jr * bx.ns) << 2);
         }
         return;
     }
     const int rows = bx.np * bx.nr;
-    const float inv_nr = __builtin_amdgcn_rcpf((float)bx.nr);
-    const float inv_step = __builtin_amdgcn_rcpf(step);
-    const float fz = (a.z - oz) * gs.inv_res;           // the atom's z in grid steps
+    const float inv_nr = __builtin_amdgcn_rcpf((float)bx.nr), reach2 = reach * reach;
     for (int row0 = 0; row0 < rows; row0 += 128) {
         int cnt[2] = {0, 0}, slo[2] = {0, 0};
 #pragma unroll
@@ -395,15 +478,15 @@ __device__ inline void for_each_slot(const BwdParams &p, const float4 &a, float 
             if (row < rows) {
                 const int pi = (int)(((float)row + 0.5f) * inv_nr);
                 const int jr = row - pi * bx.nr;
-                const float ux = fmaf(-(float)pi, step, ux0), uy = fmaf(-(float)jr, step, uy0);
-                const float h2 = p.c2k - (ux * ux + uy * uy);
+                const float ux = fmaf(-(float)pi, gs.res, ux0), uy = fmaf(-(float)jr, gs.res, uy0);
+                const float h2 = reach2 - (ux * ux + uy * uy);
                 if (h2 > 0.0f) {
-                    const float hv = __builtin_amdgcn_sqrtf(h2) * inv_step + 1.0e-3f;
+                    const float hv = __builtin_amdgcn_sqrtf(h2) * gs.inv_res + 1.0e-3f;
                     const int klo = max(bx.klo, (int)ceilf(fz - hv));
                     const int khi = min(bx.khi, (int)floorf(fz + hv));
                     if (khi >= klo) {       // 4-voxel slots from the chord's first voxel, kept inside the row
                         cnt[q] = (khi - klo + 4) >> 2;
-                        slo[q] = ALIGNED ? min(klo, gs.D - 4 * cnt[q]) : klo;
+                        slo[q] = max(min(klo, gs.D - 4 * cnt[q]), 0);
                     }
                 }
             }
@@ -428,12 +511,9 @@ __device__ inline void for_each_slot(const BwdParams &p, const float4 &a, float 
                 const int o = sidx - (w & 0x7ff);
                 const int c0 = w >> 11;
                 const int q = o >= c0 ? 1 : 0;
-                const int k4 = q ? (st >> 16) + 4 * (o - c0) : (st & 0xffff) + 4 * o;
                 const int row = row0 + 2 * owner + q;
                 const int pi = (int)(((float)row + 0.5f) * inv_nr);
-                const int jr = row - pi * bx.nr;
-                body(off0 + ((unsigned)pi * D + (unsigned)jr) * D, k4,
-                     fmaf(-(float)pi, step, ux0), fmaf(-(float)jr, step, uy0));
+                slot(pi, row - pi * bx.nr, q ? (st >> 16) + 4 * (o - c0) : (st & 0xffff) + 4 * o);
             }
         }
         lds_sync();
@@ -442,64 +522,26 @@ __device__ inline void for_each_slot(const BwdParams &p, const float4 &a, float 
     }
 }
 
-// One atom against kChanGroup channels (Gq[q]: the volume of the q-th of them).
-// The two branches of the density and of its slope are taken as a product without a select: with
-// E = exp(-2 min(x, g)^2),
-//   rho  = E clamp(2g (c - x), 0, 1)^2        (2g (c - g) = 1, and A = 4 g^2 exp(-2g^2))
-//   -f/4 = E clamp(2g^2 (c/x - 1), 0, 1)      (2g^2 (c/g - 1) = 1)
-// so the channels share one square root and one reciprocal square root per voxel, and a channel
-// takes 10 instructions per voxel instead of 13 with its own reciprocal root and two selects.
-// Bound by vector instruction issue and the wavefronts in flight: the constants live in scalar
-// registers, which leaves 80 vector registers instead of 95 (six wavefronts per SIMD instead of five);
-// with grids, 16 examples of 2040 atoms, 21 x 48^3: 416 instead of 449 us a training step.
-//   (sx, sy, sz) += sum_q cq sum G_q f_q u   (u in units of rmax/sqrt(k)),  sv[q] += sum G_q rho_q
-template <bool ALIGNED, bool WANT_W, bool ALL_LIVE, typename GT>
-__device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kChanGroup],
-                                    const float4 &a, float rmax, const Box &bx, float ox, float oy,
-                                    float oz, unsigned char *marks, const GroupCoef &gc, float &sx,
-                                    float &sy, float &sz, float (&sv)[kChanGroup])
+// Four sums over the wavefront at once, in a fixed order: sum (lane & 3) in every lane.
+__device__ inline float wave_sum4(float a, float b, float c, float d)
 {
-    const float s = p.sk * __builtin_amdgcn_rcpf(rmax), step = p.gs.res * s;
-    const float azs = (a.z - oz) * s;
-    // kept in vector registers: an instruction takes one scalar operand, and theirs have one already
-    float ng2k = p.ng2k, nfA = p.nfA, tc = p.tc;
-    asm volatile("" : "+v"(ng2k), "+v"(nfA), "+v"(tc));
-    for_each_slot<ALIGNED>(p, a, rmax, bx, ox, oy, oz, marks,
-                  [&](unsigned row_off, int k4, float ux, float uy) {
-        SlotData d[kChanGroup];
-#pragma unroll
-        for (int q = 0; q < kChanGroup; ++q)
-            if (ALL_LIVE || gc.live[q]) load_slot<ALIGNED, false>(p, Gq[q], row_off, k4, ux, uy, d[q]);
-        const float b2 = ux * ux + uy * uy;
-        const int k0 = ALIGNED || p.gs.D < 4 ? k4 : min(k4, p.gs.D - 4);    // where load_slot began
-        const float uz0 = fmaf(-(float)k0, step, azs);
-        float fsum = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float uz = uz0 - (float)u * step;
-            const float x2m = fmaf(uz, uz, b2);
-            const float rs = __builtin_amdgcn_rsqf(x2m), sx2 = WANT_W ? __builtin_amdgcn_sqrtf(x2m) : 0.0f;
-            float F = 0.0f;
-#pragma unroll
-            for (int q = 0; q < kChanGroup; ++q) {
-                if (!ALL_LIVE && !gc.live[q]) continue;
-                const float ge = d[q].gv[u] * __builtin_amdgcn_exp2f(__builtin_amdgcn_fmed3f(x2m * gc.nr2[q], ng2k, 0.0f));
-                const float ft = __builtin_amdgcn_fmed3f(fmaf(gc.fq[q], rs, nfA), 0.0f, 1.0f);
-                F = fmaf(gc.cq[q], ge * ft, F);
-                if (WANT_W) {
-                    const float tl = __builtin_amdgcn_fmed3f(fmaf(gc.tq[q], sx2, tc), 0.0f, 1.0f);
-                    sv[q] = fmaf(ge * tl, tl, sv[q]);
-                }
-            }
-            fsum += F;
-            sz = fmaf(F, uz, sz);
-        }
-        sx = fmaf(fsum, ux, sx);
-        sy = fmaf(fsum, uy, sy);
-    });
+    const int lane = (int)(threadIdx.x & 63u);
+    const auto bits = [](float x) { return __float_as_int(x); };
+    const bool odd = (lane & 1) != 0, upper = (lane & 2) != 0;
+    // lane l keeps one of a pair and gets the neighbour's part of it: quad_perm [1,0,3,2], then [2,3,0,1]
+    const float ab = (odd ? b : a) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(odd ? a : b), 0xB1, 0xf, 0xf, false));
+    const float cd = (odd ? d : c) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(odd ? c : d), 0xB1, 0xf, 0xf, false));
+    float r = (upper ? cd : ab) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(upper ? ab : cd), 0x4E, 0xf, 0xf, false));
+    r += __int_as_float(__builtin_amdgcn_update_dpp(0, bits(r), 0x124, 0xf, 0xf, false));     // row_ror:4
+    r += __int_as_float(__builtin_amdgcn_update_dpp(0, bits(r), 0x128, 0xf, 0xf, false));     // row_ror:8
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)bits(r), (unsigned)bits(r), false, false);
+    r = __uint_as_float(h[0]) + __uint_as_float(h[1]);          // rows 0 + 1, rows 2 + 3
+    const auto w = __builtin_amdgcn_permlane32_swap((unsigned)bits(r), (unsigned)bits(r), false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
 }
 
-template <bool VECTOR, bool ALIGNED, typename GT, bool FUSED = false>
+// WANT_W: gradients of the weights are asked for (vector types).
+template <bool VECTOR, bool ALIGNED, typename GT, bool FUSED, bool WANT_W = false>
 __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void backward_kernel(BwdParams p)
 {
     const GridSpec &gs = p.gs;
@@ -564,7 +606,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         const bool inside = meets_grid(gs, org, pos, r, reach);
         if (!(member & inside)) {
             if (p.grad_coords && lane < 3) p.grad_coords[k * 3 + lane] = 0.0f;
-            if (VECTOR && p.grad_weights)
+            if (WANT_W)
                 for (int c = lane; c < T; c += 64) p.grad_weights[k * T + c] = 0.0f;
             return;
         }
@@ -596,7 +638,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         if (slot < N && atom_alive == 0) {
             const size_t atom = (size_t)b * N + slot;
             if (p.grad_coords && lane < 3) p.grad_coords[atom * 3 + lane] = 0.0f;
-            if (VECTOR && p.grad_weights)
+            if (WANT_W)
                 for (int k = lane; k < T; k += 64) p.grad_weights[atom * T + k] = 0.0f;
         }
         if (slot >= last.x + last.z) return;            // past the last group's slots (per wavefront)
@@ -626,84 +668,78 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         // the atom is the wavefront's: what depends on it and on the channel stays in scalar registers
         ai = __builtin_amdgcn_readfirstlane(ai);
         a = make_float4(uniform(a.x), uniform(a.y), uniform(a.z), a.w);
-        const size_t arow = ((size_t)bs * N + ai) * T;
-        // The channels are taken in order of radius (T <= 64: lane l ranks channel l among the
-        // others; more channels are taken as they come), so that the spheres of a group are
-        // nearly the same size and few voxels of the widest lie outside the others.
-        __shared__ unsigned char s_perm[4][64];
-        unsigned char *perm = s_perm[threadIdx.x >> 6];
-        const bool sorted = T <= 64;
-        if (sorted) {
-            float mine = lane < T ? p.radii[lane] : 0.0f;
-            mine = mine > 0.0f ? mine : 0.0f;       // NaN and negative radii rank as 0: still a permutation
-            int rank = 0;
-            for (int m = 0; m < T; ++m) {
-                const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), m));
-                rank += (other < mine || (other == mine && m < lane)) ? 1 : 0;
+        const size_t arow = ((size_t)bs * N + ai) * T, grow = ((size_t)b * N + ai) * T;
+        // 64 channels at a time, in order of radius (so that the spheres of a group are nearly the same
+        // size): lane l holds the l-th of them
+        for (int base = 0; base < T; base += 64) {
+            const int count = min(64, T - base);
+            int chan = base + lane;         // of rank `lane`
+            if (count <= kChanGroup) {
+                chan = base + min(lane, count - 1);     // one group, in any order
+            } else if (!FUSED && T <= 64) {
+                chan = p.chan_order[(size_t)b * T + min(lane, T - 1)];
+            } else {
+                __shared__ unsigned char s_perm[4][64];
+                unsigned char *perm = s_perm[threadIdx.x >> 6];
+                float mine = lane < count ? p.radii[base + lane] : 0.0f;
+                mine = mine > 0.0f ? mine : 0.0f;       // NaN and negative radii rank as 0: still a permutation
+                int rank = 0;
+                for (int m = 0; m < count; ++m) {
+                    const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), m));
+                    rank += (other < mine || (other == mine && m < lane)) ? 1 : 0;
+                }
+                lds_sync();
+                if (lane < count) perm[rank] = (unsigned char)lane;
+                lds_sync();
+                chan = base + (lane < count ? min((int)perm[lane], count - 1) : 0);
             }
-            if (lane < T) perm[rank] = (unsigned char)lane;
-            lds_sync();
-        }
-        for (int t0 = 0; t0 < T; t0 += kChanGroup) {
-            float rq[kChanGroup], wq[kChanGroup];
-            int tq[kChanGroup];
-            const GT *Gq[kChanGroup];
-            GroupCoef gc;
-            float rmax = 0.0f;
-#pragma unroll
-            for (int q = 0; q < kChanGroup; ++q) {
-                const int pos = min(t0 + q, T - 1);
-                tq[q] = sorted ? min(__builtin_amdgcn_readfirstlane((int)perm[pos]), T - 1) : pos;
-                rq[q] = gs.radius_scale * p.radii[tq[q]];
-                wq[q] = p.weights[arow + tq[q]];
-                Gq[q] = reinterpret_cast<const GT *>(p.G) + ((size_t)b * T + tq[q]) * D3;
-                gc.live[q] = t0 + q < T && rq[q] > 0.0f;
-                if (gc.live[q]) rmax = fmaxf(rmax, rq[q]);
+            const float r = lane < count ? gs.radius_scale * p.radii[chan] : 0.0f;
+            const float w = lane < count ? p.weights[arow + chan] : 0.0f;
+            const unsigned long long live = __ballot(r > 0.0f);
+            float v_reach = r * gs.c;
+            if (count <= kChanGroup) {      // (in any order: the widest of the four)
+                v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 1));
+                v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 2));
             }
-            float sx = 0.0f, sy = 0.0f, sz = 0.0f, sv[kChanGroup];
-            const float inv_rmax = __builtin_amdgcn_rcpf(rmax);
-#pragma unroll
-            for (int q = 0; q < kChanGroup; ++q) {
-                const float inv = gc.live[q] ? __builtin_amdgcn_rcpf(rq[q]) : 0.0f;
-                const float ratio = rmax * inv;
-                gc.nr2[q] = uniform(-(ratio * ratio));
-                gc.fq[q] = uniform(p.fAck * (rq[q] * inv_rmax));
-                gc.tq[q] = uniform(-(p.tk * ratio));
-                gc.cq[q] = uniform(-4.0f * (wq[q] * ratio * inv * p.inv_sk));
-                sv[q] = 0.0f;
-            }
-            Box bx;
-            if (rmax > 0.0f && atom_box(gs, rmax * gs.c, a, ox, oy, oz, bx))
-            {
-                bool all = true;        // a full group needs no test per voxel and channel
-#pragma unroll
-                for (int q = 0; q < kChanGroup; ++q) all = all && gc.live[q];
-                if (p.grad_weights && all)
-                    reduce_group<ALIGNED, true, true>(p, Gq, a, rmax, bx, ox, oy, oz, marks, gc, sx, sy, sz, sv);
-                else if (p.grad_weights)
-                    reduce_group<ALIGNED, true, false>(p, Gq, a, rmax, bx, ox, oy, oz, marks, gc, sx, sy, sz, sv);
-                else if (all)
-                    reduce_group<ALIGNED, false, true>(p, Gq, a, rmax, bx, ox, oy, oz, marks, gc, sx, sy, sz, sv);
-                else
-                    reduce_group<ALIGNED, false, false>(p, Gq, a, rmax, bx, ox, oy, oz, marks, gc, sx, sy, sz, sv);
-            }
-            tx += sx;       // per lane; summed over the wavefront once, after the last group
-            ty += sy;
-            tz += sz;
-            if (p.grad_weights) {
+            const float inv = r > 0.0f ? __builtin_amdgcn_rcpf(r) : 0.0f;
+            const float v_nr2 = -(p.k * inv) * inv, v_fq = p.fAc * r, v_tq = -(p.tg * inv), v_cq = -4.0f * (w * inv) * inv;
+            const auto lane_value = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+            float gw = 0.0f;                // lane l: the weight gradient of the channel of rank l
+            for (int t0 = 0; t0 < count; t0 += kChanGroup) {
+                GroupCoef gc;
+                gc.live = (unsigned)(live >> t0) & ((1u << kChanGroup) - 1u);
+                if (gc.live == 0u) continue;
+                const GT *Gq[kChanGroup];
 #pragma unroll
                 for (int q = 0; q < kChanGroup; ++q) {
-                    if (t0 + q >= T) break;
-                    const float val = wave_sum(sv[q]);
-                    if (lane == 0) p.grad_weights[((size_t)b * N + ai) * T + tq[q]] = val;
+                    const int l = min(t0 + q, 63);
+                    Gq[q] = reinterpret_cast<const GT *>(p.G) + ((size_t)b * T + bcast(chan, l)) * D3;
+                    gc.nr2[q] = lane_value(v_nr2, l);
+                    gc.fq[q] = lane_value(v_fq, l);
+                    gc.tq[q] = lane_value(v_tq, l);
+                    gc.cq[q] = lane_value(v_cq, l);
+                }
+                const float reach = lane_value(v_reach, t0 + 31 - (int)__builtin_clz(gc.live));     // of the last live channel
+                Box bx;
+                if (!atom_box(gs, reach, a, ox, oy, oz, bx)) continue;
+                float sv[kChanGroup] = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (gc.live == (1u << kChanGroup) - 1u)         // a full group needs no test per voxel and channel
+                    reduce_group<ALIGNED, WANT_W, true>(p, Gq, a, reach, bx, ox, oy, oz, marks, gc, tx, ty, tz, sv);
+                else
+                    reduce_group<ALIGNED, WANT_W, false>(p, Gq, a, reach, bx, ox, oy, oz, marks, gc, tx, ty, tz, sv);
+                if (WANT_W) {
+                    const float sum = wave_sum4(sv[0], sv[1], sv[2], sv[3]);
+                    gw = (lane >> 2) == (t0 >> 2) ? sum : gw;
                 }
             }
+            if (WANT_W && lane < count) p.grad_weights[grow + chan] = gw;
         }
     }
     if (VECTOR && p.grad_coords) {
-        tx = wave_sum(tx);
-        ty = wave_sum(ty);
-        tz = wave_sum(tz);
+        const float t = wave_sum4(tx, ty, tz, 0.0f);
+        tx = __int_as_float(bcast(__float_as_int(t), 0));
+        ty = __int_as_float(bcast(__float_as_int(t), 1));
+        tz = __int_as_float(bcast(__float_as_int(t), 2));
     }
     if (lane == 0 && p.grad_coords) {
         float *o = p.grad_coords + ((size_t)b * N + ai) * 3;
@@ -774,7 +810,7 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
     BwdParams p;
     p.gs = gs;
     p.rec = ws.rec; p.idx = ws.idx; p.meta = ws.meta; p.rot = ws.rot;
-    p.rchan = ws.rchan; p.weights = bt.weights; p.radii = bt.radii; p.gcen = ws.gcen;
+    p.rchan = ws.rchan; p.chan_order = ws.chan_order; p.weights = bt.weights; p.radii = bt.radii; p.gcen = ws.gcen;
     p.alive = ws.alive; p.tag = ws.tag; p.expect_tag = expect_tag;
     p.G = grad_out; p.grad_coords = grad_coords; p.grad_weights = grad_weights;
     p.subgrids = bt.sub.count; p.N = bt.N; p.T = bt.T;
@@ -791,9 +827,10 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
         const double g2 = std::fmax(std::fmin((double)gs.g2, 1.0e4), 1.0e-30), g = std::sqrt(g2), c = g + 0.5 / g;
         p.ng2k = (float)(-g2 * k);
         p.nfA = (float)(-2.0 * g2);
-        p.fAck = (float)(2.0 * g2 * c * std::sqrt(k));
-        p.tk = (float)(2.0 * g / std::sqrt(k));
+        p.fAc = (float)(2.0 * g2 * c);
+        p.tg = (float)(2.0 * g);
         p.tc = (float)(2.0 * g * c);
+        p.k = (float)k;
     }
     const bool aligned = (gs.D % 4 == 0) && (((uintptr_t)grad_out & 15u) == 0);
     p.wgs_per_example = (unsigned)((bt.N + 3) / 4);
@@ -801,18 +838,21 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
     p.share = (p.units + 7u) / 8u;
     p.wg_magic = p.wgs_per_example <= 1u ? 0ull : (~0ull / p.wgs_per_example) + 1ull;
     const dim3 grd(p.share * 8u), blk(256);
-#define MG_BWD(V, Al, Gt, Fu) \
-    hipExtLaunchKernelGGL((backward_kernel<V, Al, Gt, Fu>), grd, blk, 0, stream, ev.start, ev.stop, 0, p)
-#define MG_BWD_FUSED(V, Al, Gt) \
-    if (single_launch) MG_BWD(V, Al, Gt, true); else MG_BWD(V, Al, Gt, false)
-#define MG_BWD_TYPE(Gt)                                                             \
-    if (bt.vec) {                                                                   \
-        if (aligned) { MG_BWD_FUSED(true, true, Gt); } else { MG_BWD_FUSED(true, false, Gt); }   \
-    } else {                                                                        \
-        if (aligned) { MG_BWD_FUSED(false, true, Gt); } else { MG_BWD_FUSED(false, false, Gt); } \
-    }
-    if (grad_is_double) { MG_BWD_TYPE(double) } else { MG_BWD_TYPE(float) }
+#define MG_BWD(V, Al, Gt, Fu, Ww) \
+    hipExtLaunchKernelGGL((backward_kernel<V, Al, Gt, Fu, Ww>), grd, blk, 0, stream, ev.start, ev.stop, 0, p)
+#define MG_BWD_FUSED(V, Al, Gt, Ww) \
+    do { if (single_launch) MG_BWD(V, Al, Gt, true, Ww); else MG_BWD(V, Al, Gt, false, Ww); } while (0)
+#define MG_BWD_ALIGNED(V, Gt, Ww) \
+    do { if (aligned) MG_BWD_FUSED(V, true, Gt, Ww); else MG_BWD_FUSED(V, false, Gt, Ww); } while (0)
+#define MG_BWD_TYPE(Gt)                                                 \
+    do {                                                                \
+        if (!bt.vec) MG_BWD_ALIGNED(false, Gt, false);                  \
+        else if (grad_weights) MG_BWD_ALIGNED(true, Gt, true);          \
+        else MG_BWD_ALIGNED(true, Gt, false);                           \
+    } while (0)
+    if (grad_is_double) MG_BWD_TYPE(double); else MG_BWD_TYPE(float);
 #undef MG_BWD_TYPE
+#undef MG_BWD_ALIGNED
 #undef MG_BWD_FUSED
 #undef MG_BWD
     return hipGetLastError();
