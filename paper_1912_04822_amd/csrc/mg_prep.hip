@@ -67,6 +67,28 @@ __device__ inline int wave_exclusive_scan(int v, int *total)
     return incl - v;
 }
 
+// The pose, the same in all lanes, in scalar registers: 30 vector registers less.
+__device__ inline void keep_scalar(Xform &X)
+{
+    const auto uniform = [](double v) {
+        const long long bits = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_readfirstlane((int)bits), hi = __builtin_amdgcn_readfirstlane((int)(bits >> 32));
+        return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+    };
+    for (int m = 0; m < 9; ++m) X.R[m] = uniform(X.R[m]);
+    for (int m = 0; m < 3; ++m) X.c[m] = uniform(X.c[m]);
+    for (int m = 0; m < 3; ++m) X.t[m] = uniform(X.t[m]);
+}
+
+// The rotation's rows for the backward pass (with constant indices: an index by lane would keep the whole
+// pose in scratch memory).
+__device__ inline void store_rotation(const Xform &X, float *rot)
+{
+    *reinterpret_cast<float4 *>(rot) = make_float4((float)X.R[0], (float)X.R[1], (float)X.R[2], (float)X.R[3]);
+    *reinterpret_cast<float4 *>(rot + 4) = make_float4((float)X.R[4], (float)X.R[5], (float)X.R[6], (float)X.R[7]);
+    rot[8] = (float)X.R[8];
+}
+
 // Centre of the grid of virtual example b (source example bs); X holds bs's centre (a float
 // widened to double, so narrowing it back is exact).
 __device__ inline void grid_center(const Subgrids &sub, const Xform &X, int b, int bs, float *gc)
@@ -80,25 +102,38 @@ __device__ inline void grid_center(const Subgrids &sub, const Xform &X, int b, i
     }
 }
 
-// Vector types: the channels of (virtual) example b in order of radius, for the kernels that
-// take several channels of an atom together (thread `tid` of `nthreads`).  NaN and negative
-// radii rank as 0, so the result is a permutation whatever the table holds.
-__device__ inline void rank_channels(const Batch &bt, const Workspace &ws, int b, int tid, int nthreads)
+// Vector types: the reach of the widest channel (the lanes of a wavefront read the radii together).
+__device__ inline float widest_reach(const GridSpec &gs, const Batch &bt)
 {
-    const int T = bt.T;
-    for (int k = tid; k < T; k += nthreads) {
+    float widest = 0.0f;
+    for (int k = (int)(threadIdx.x & 63u); k < bt.T; k += 64) widest = fmaxf(widest, gs.radius_scale * bt.radii[k]);
+    widest = __int_as_float(bcast(wave_inclusive_max(__float_as_int(widest)), 63));     // (>= 0: ordered like ints)
+    return gs.binary ? widest : widest * gs.c;
+}
+
+// Vector types: the channels of (virtual) example b in order of radius, for the kernels that
+// take several channels of an atom together; called by one wavefront.  NaN and negative
+// radii rank as 0, so the result is a permutation whatever the table holds.
+__device__ inline void rank_channels(const Batch &bt, const Workspace &ws, int b)
+{
+    const int T = bt.T, lane = threadIdx.x & 63;
+    for (int k0 = 0; k0 < T; k0 += 64) {
+        const int k = k0 + lane;
+        float mine = k < T ? bt.radii[k] : 0.0f;
+        mine = mine > 0.0f ? mine : 0.0f;
         int rank = k;
         if (T <= kRankCap) {
-            float mine = bt.radii[k];
-            mine = mine > 0.0f ? mine : 0.0f;
             rank = 0;
-            for (int j = 0; j < T; ++j) {
-                float other = bt.radii[j];
-                other = other > 0.0f ? other : 0.0f;
-                rank += (other < mine || (other == mine && j < k)) ? 1 : 0;
+            for (int j0 = 0; j0 < T; j0 += 64) {
+                float theirs = j0 + lane < T ? bt.radii[j0 + lane] : 0.0f;
+                theirs = theirs > 0.0f ? theirs : 0.0f;
+                for (int j = 0; j < min(64, T - j0); ++j) {
+                    const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(theirs), j));
+                    rank += (other < mine || (other == mine && j0 + j < k)) ? 1 : 0;
+                }
             }
         }
-        ws.chan_order[(size_t)b * T + rank] = k;
+        if (k < T) ws.chan_order[(size_t)b * T + rank] = k;
     }
 }
 
@@ -120,7 +155,7 @@ struct ExLayout {       // LDS, in ints
     __host__ __device__ int ints() const { return order() + (N + 1) / 2; }
 };
 
-template <bool VECTOR, int kPer, int NT>
+template <int kPer, int NT>
 __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
                                                                   Workspace ws, unsigned tag,
                                                                   int stop)
@@ -130,7 +165,7 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
     const int bs = source_example(bt.sub.count, b);       // whose atoms and pose this (virtual) example reads
     const int N = bt.N, T = bt.T, D = gs.D;
     if (MG_STOP_IS(stop, 1)) return;
-    const int Tg = VECTOR ? 1 : T;      // groups per example
+    const int Tg = T;                   // groups per example
     const int nb = D + 3;               // bins per group; bin D+2 holds the culled atoms
     ExLayout L;
     L.K = Tg * nb; L.Tg = Tg; L.N = N;
@@ -144,9 +179,9 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
 
     // Everything this thread needs from HBM is requested before anything is waited for:
     // its atoms (thread tid owns atoms tid, tid + 1024, ...), the radii table, the pose.
-    const int32_t *ty = VECTOR ? nullptr : bt.types + (size_t)bs * N;
+    const int32_t *ty = bt.types + (size_t)bs * N;
     const float *crd = bt.coords + (size_t)bs * N * 3;          // 32-bit offsets from here on
-    const float *rad_b = bt.radii + ((!VECTOR && !gs.radius_type_indexed) ? (size_t)bs * N : 0);
+    const float *rad_b = bt.radii + (!gs.radius_type_indexed ? (size_t)bs * N : 0);
     int my_t[kPer];
     float my_c[kPer][3], my_r[kPer];
 #pragma unroll
@@ -156,15 +191,15 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         my_c[u][0] = 0.0f; my_c[u][1] = 0.0f; my_c[u][2] = 0.0f;
         my_r[u] = 0.0f;
         if (a < N) {
-            my_t[u] = VECTOR ? 0 : ty[a];
+            my_t[u] = ty[a];
             my_c[u][0] = crd[a * 3];
             my_c[u][1] = crd[a * 3 + 1];
             my_c[u][2] = crd[a * 3 + 2];
-            if (!VECTOR && !gs.radius_type_indexed) my_r[u] = rad_b[a];
+            if (!gs.radius_type_indexed) my_r[u] = rad_b[a];
         }
     }
     // (the radius table too: this thread's entry now, into LDS once the loads have landed)
-    const bool rad_table = !VECTOR && gs.radius_type_indexed;
+    const bool rad_table = gs.radius_type_indexed;
     float my_rad = 0.0f;
     if (rad_table && tid < Tg) my_rad = bt.radii[tid];
     int n = N;
@@ -174,21 +209,12 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
     }
     Xform X;
     load_xform(X, bs, bt.centers, bt.quats, bt.translations);
-    if (tid < 9) ws.rot[b * 12 + tid] = (float)X.R[tid];
+    if (tid == 0) store_rotation(X, ws.rot + b * 12);
     if (b == 0 && tid == 0) *ws.tag = tag;
-    float vec_reach = 0.0f;         // reach of the widest channel, for vector types
-    if (VECTOR) {
-        rank_channels(bt, ws, b, tid, NT);
-        for (int k = 0; k < T; ++k) {
-            const float r = gs.radius_scale * bt.radii[k];
-            if (r > vec_reach) vec_reach = r;
-        }
-        if (!gs.binary) vec_reach *= gs.c;
-    }
     float org[3];                   // the grid's first point
     float gc[3];
     grid_center(bt.sub, X, b, bs, gc);
-    if (tid < 3) ws.gcen[b * 4 + tid] = gc[tid];
+    if (tid == 0) *reinterpret_cast<float4 *>(ws.gcen + b * 4) = make_float4(gc[0], gc[1], gc[2], 0.0f);
     for (int m = 0; m < 3; ++m) org[m] = gc[m] - gs.half;
 
     if (rad_table) {
@@ -215,14 +241,8 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         const bool member = a < n && tg >= 0 && tg < Tg;
         if (member) {
             apply_xform(X, my_c[u], my_p[u]);
-            float r, reach;
-            if (VECTOR) {
-                r = 1.0f;
-                reach = vec_reach;
-            } else {
-                r = gs.radius_scale * (gs.radius_type_indexed ? s_rad[tg] : my_r[u]);
-                reach = gs.binary ? r : r * gs.c;
-            }
+            const float r = gs.radius_scale * (gs.radius_type_indexed ? s_rad[tg] : my_r[u]);
+            const float reach = gs.binary ? r : r * gs.c;
             const bool live = meets_grid(gs, org, my_p[u], r, reach);
             int bin = D + 2;
             if (live) {
@@ -280,8 +300,7 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
     for (int e = tid; e < Tg * D; e += NT) {
         const int tg = e / D, i = e - tg * D;
         // plane i is reached from bins [i - Rv, i + Rv + 1]
-        const float rmax = VECTOR ? vec_reach
-                                  : __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
+        const float rmax = __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
         const int Rv = (int)ceilf(rmax * gs.inv_res + 1.0e-3f * gs.res) + 1;
         const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
         ws.range[((size_t)b * T + tg) * D + i] = make_int2(s_pos[tg * nb + lo], s_pos[tg * nb + hi + 1]);
@@ -306,7 +325,145 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         }
         ws.rec[(size_t)b * N + lo + rank] = make_float4(my_p[u][0], my_p[u][1], my_p[u][2], my_w[u]);
         ws.idx[(size_t)b * N + lo + rank] = a;
-        if (!VECTOR) ws.rchan[(size_t)b * N + lo + rank] = key / nb;
+        ws.rchan[(size_t)b * N + lo + rank] = key / nb;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Vector types, one workgroup per example: counting sort by x-bin in LDS.  All atoms are in one group, so
+// bins are long (34 atoms each on 2040 atoms and 48 planes), and putting every bin in atom order by
+// counting (as for index types) was 7 of 18 us.  The sort is stable by itself instead: every wavefront has a
+// run of consecutive atoms and its own count of every bin, looks at 64 atoms at a time and tells by
+// ballots over the bits of the key which of its lanes hold the same bin; the counts are summed over bins
+// and, within a bin, over wavefronts.
+// ---------------------------------------------------------------------------
+template <int kPer>
+__global__ __launch_bounds__(kExThreads) void prep_example_vector_kernel(GridSpec gs, Batch bt, Workspace ws,
+                                                                         unsigned tag, int stop)
+{
+    constexpr int NT = kExThreads, NW = NT / 64;
+    extern __shared__ int s_mem[];
+    __shared__ int s_part[NW + 1];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bs = source_example(bt.sub.count, b);       // whose atoms and pose this (virtual) example reads
+    const int N = bt.N, D = gs.D;
+    if (MG_STOP_IS(stop, 1)) return;
+    const int nb = D + 3;               // bin D+2 holds the culled atoms
+    unsigned short *s_cnt = reinterpret_cast<unsigned short *>(s_mem);     // [nb][NW], later where they begin
+
+    // everything this thread needs from HBM is requested before anything is waited for
+    const float *crd = bt.coords + (size_t)bs * N * 3;
+    float my_c[kPer][3];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int a = (wave * kPer + u) * 64 + lane;
+        my_c[u][0] = 0.0f; my_c[u][1] = 0.0f; my_c[u][2] = 0.0f;
+        if (a < N) {
+            my_c[u][0] = crd[a * 3];
+            my_c[u][1] = crd[a * 3 + 1];
+            my_c[u][2] = crd[a * 3 + 2];
+        }
+    }
+    int n = N;
+    if (bt.natoms) {
+        n = bt.natoms[bs];
+        n = n < 0 ? 0 : (n > N ? N : n);
+    }
+    Xform X;
+    load_xform(X, bs, bt.centers, bt.quats, bt.translations);
+    if (tid == 0) store_rotation(X, ws.rot + b * 12);
+    if (b == 0 && tid == 0) *ws.tag = tag;
+    const float reach = widest_reach(gs, bt);
+    float org[3];                   // the grid's first point
+    float gc[3];
+    grid_center(bt.sub, X, b, bs, gc);
+    if (tid == 0) *reinterpret_cast<float4 *>(ws.gcen + b * 4) = make_float4(gc[0], gc[1], gc[2], 0.0f);
+    for (int m = 0; m < 3; ++m) org[m] = gc[m] - gs.half;
+    for (int k = tid; k < (nb * NW + 1) / 2; k += NT) s_mem[k] = 0;
+    __syncthreads();
+    if (MG_STOP_IS(stop, 2)) return;
+
+    // ---- 1. bin and place within (bin, wavefront) for every atom ----
+    int my_key[kPer], my_slot[kPer];
+    float my_p[kPer][3];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int a = (wave * kPer + u) * 64 + lane;
+        const bool member = a < n;
+        bool live = false;
+        int key = 0;
+        my_p[u][0] = my_p[u][1] = my_p[u][2] = 0.0f;
+        if (member) {
+            apply_xform(X, my_c[u], my_p[u]);
+            live = meets_grid(gs, org, my_p[u], 1.0f, reach);
+            const float f = floorf((my_p[u][0] - org[0]) * gs.inv_res);
+            key = !live ? D + 2 : f < 0.0f ? 0 : (f >= (float)D ? D + 1 : (int)f + 1);
+        }
+        if (a < N) ws.alive[(size_t)b * N + a] = live ? 1 : 0;
+        // the lanes with the same key
+        unsigned long long same = __ballot(member);
+        for (int bit = 1; bit < nb; bit <<= 1) {
+            const bool set = (key & bit) != 0;
+            const unsigned long long m = __ballot(set);
+            same &= set ? m : ~m;
+        }
+        my_key[u] = member ? key : -1;
+        my_slot[u] = 0;
+        if (member) {
+            const int before = (int)__builtin_popcountll(same & ((1ull << lane) - 1ull));
+            unsigned short *c = &s_cnt[key * NW + wave];
+            const int base = *c;
+            my_slot[u] = base + before;
+            lds_sync();
+            if (before == 0) *c = (unsigned short)(base + (int)__builtin_popcountll(same));
+        }
+        lds_sync();
+    }
+    if (wave == NW - 1) rank_channels(bt, ws, b);       // (while the others wait)
+    __syncthreads();
+    if (MG_STOP_IS(stop, 3)) return;
+
+    // ---- 2. exclusive scan of the counts ----
+    const int K = nb * NW;
+    const int chunk = (K + NT - 1) / NT;
+    const int k0 = min(K, tid * chunk), k1 = min(K, k0 + chunk);
+    int mine = 0;
+    for (int k = k0; k < k1; ++k) mine += s_cnt[k];
+    int wtotal;
+    int run = wave_exclusive_scan(mine, &wtotal);
+    if (lane == 0) s_part[wave] = wtotal;
+    __syncthreads();
+    if (wave == 0) {
+        int t16;
+        const int v = lane < NW ? s_part[lane] : 0;
+        const int ex = wave_exclusive_scan(v, &t16);
+        if (lane < NW) s_part[lane] = ex;
+        if (lane == 0) s_part[NW] = t16;
+    }
+    __syncthreads();
+    run += s_part[wave];
+    for (int k = k0; k < k1; ++k) {
+        const int c = s_cnt[k];
+        s_cnt[k] = (unsigned short)run;
+        run += c;
+    }
+    __syncthreads();
+    if (MG_STOP_IS(stop, 4)) return;
+
+    // ---- 3. records, group descriptor, spans ----
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (my_key[u] < 0) continue;
+        const size_t at = (size_t)b * N + s_cnt[my_key[u] * NW + wave] + my_slot[u];
+        ws.rec[at] = make_float4(my_p[u][0], my_p[u][1], my_p[u][2], my_key[u] == D + 2 ? 0.0f : 1.0f);
+        ws.idx[at] = (wave * kPer + u) * 64 + lane;
+    }
+    const int total = s_part[NW];
+    if (tid == 0) ws.meta[(size_t)b * bt.T] = make_int4(0, s_cnt[(D + 2) * NW], total, 0);
+    const int Rv = (int)ceilf(reach * gs.inv_res + 1.0e-3f * gs.res) + 1;
+    for (int i = tid; i < D; i += NT) {             // plane i is reached from bins [i - Rv, i + Rv + 1]
+        const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
+        ws.range[(size_t)b * bt.T * D + i] = make_int2(s_cnt[lo * NW], s_cnt[(hi + 1) * NW]);
     }
 }
 
@@ -325,7 +482,8 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
 // it: 130 us, now 24).
 // ---------------------------------------------------------------------------
 constexpr int kRangeThreads = 1024;
-constexpr int kRangeMaxKeys = 5120;     // keys of a workgroup: two words of LDS each
+constexpr int kRangeMaxKeys = 1700;     // keys of a workgroup: two words of LDS each
+constexpr int kOwnAtoms = 12288;        // atoms of a share that are listed in LDS, twelve per thread
 constexpr int kRankBin = 2048;          // longer bins are put in atom order by one wavefront, not by counting
 
 template <bool VECTOR>
@@ -338,7 +496,9 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     int *s_cnt = s_mem + keys_cap + 1;          // [keys] count, then fill cursor
     int *s_rmax = s_cnt + keys_cap;             // [types of the share]
     __shared__ int s_part[NT / 64 + 1], s_less, s_found;
-    __shared__ unsigned short s_mine[VECTOR ? 1 : NT * U];     // the share's atoms of a round
+    __shared__ int s_own[kOwnAtoms];            // the share's atoms, later in order of bins
+    unsigned short *s_mine = reinterpret_cast<unsigned short *>(s_own);        // ... of a round
+    static_assert(kOwnAtoms * sizeof(int) >= NT * U * sizeof(unsigned short), "a round's atoms");
     const int p = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bs = source_example(bt.sub.count, b);       // whose atoms and pose this (virtual) example reads
     const int N = bt.N, T = bt.T, D = gs.D, nb = D + 3;   // bin D+2 holds the culled atoms
@@ -356,25 +516,24 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
 
     Xform X;
     load_xform(X, bs, bt.centers, bt.quats, bt.translations);
+    keep_scalar(X);
     float vec_reach = 0.0f;         // reach of the widest channel, for vector types
     if (VECTOR) {
-        for (int k = lane; k < T; k += 64) vec_reach = fmaxf(vec_reach, gs.radius_scale * bt.radii[k]);
-        for (int m = 32; m > 0; m >>= 1) vec_reach = fmaxf(vec_reach, __shfl_xor(vec_reach, m));
-        if (!gs.binary) vec_reach *= gs.c;
+        vec_reach = widest_reach(gs, bt);
+        if (p == 0 && wave == NT / 64 - 1) rank_channels(bt, ws, b);
     }
     float org[3];                   // the grid's first point
     float gc[3];
     grid_center(bt.sub, X, b, bs, gc);
     for (int m = 0; m < 3; ++m) org[m] = gc[m] - gs.half;
     if (p == 0) {
-        if (tid < 9) ws.rot[b * 12 + tid] = (float)X.R[tid];
-        if (tid < 3) ws.gcen[b * 4 + tid] = gc[tid];
+        if (tid == 0) store_rotation(X, ws.rot + b * 12);
+        if (tid == 0) *reinterpret_cast<float4 *>(ws.gcen + b * 4) = make_float4(gc[0], gc[1], gc[2], 0.0f);
         if (b == 0 && tid == 0) *ws.tag = tag;
-        if (VECTOR) rank_channels(bt, ws, b, tid, NT);
     }
     for (int k = tid; k < K; k += NT) s_cnt[k] = 0;
     for (int k = tid; k < Tg; k += NT) s_rmax[k] = 0;
-    if (tid == 0) s_less = 0;
+    if (tid == 0) s_less = s_found = 0;
     __syncthreads();
 
     const float *crd = bt.coords + (size_t)bs * N * 3;
@@ -403,10 +562,9 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
         }
         return (t - tA) * nb + bin;
     };
-    // body(atom, type, Raw) for every atom of the share, other(atom, type) for the rest.  Index
-    // types: the share's atoms of a round (8192) are gathered in LDS first, so that all lanes
-    // place atoms (a share is a fraction of the types: without it 48 us for 20000 atoms in nine shares).
-    auto for_mine = [&](auto body, auto other) {
+    // body(atom, type, Raw) for every atom of the share.  Index types: the share's atoms of a round (8192)
+    // are gathered in LDS first, so that all lanes place atoms.
+    auto for_mine = [&](auto body) {
         for (int base = 0; base < N; base += NT * U) {
             int v[U], found = 0;
 #pragma unroll
@@ -422,7 +580,6 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
             for (int u = 0; u < U; ++u) {
                 const int a = base + u * NT + tid;
                 const bool own = v[u] >= tA && v[u] < tB;
-                if (!own && a < N) other(a, v[u]);
                 if (VECTOR) continue;
                 const unsigned long long m = __ballot(own);
                 int at = 0;
@@ -456,23 +613,104 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
         }
     };
 
-    // ---- 1. atoms per key ----
+    // ---- 0. the share's atoms; what it has to know of the others ----
+    // Index types: how many atoms of smaller types there are.  Vector types: every atom is placed, those of
+    // other bins are counted, and the share with the last bin writes the records of the culled atoms, from
+    // the end of the example's records backwards.
     int less = 0;
-    for_mine(
-        [&](int a, int t, const Raw &w) {
-            float pp[3], r;
-            const int key = place(w, t, pp, r);
-            atomicAdd(&s_cnt[key], 1);
-            if (r > 0.0f) atomicMax(&s_rmax[t - tA], __float_as_int(r));        // r > 0: ordered like ints
-            if (key >= kA && key < kB) ws.alive[(size_t)b * N + a] = r > 0.0f ? 1 : 0;
-        },
-        [&](int a, int t) {
-            less += (t >= 0 && t < tA) ? 1 : 0;
-            if (p == 0 && (t < 0 || t >= T)) ws.alive[(size_t)b * N + a] = 0;       // no group owns this atom
-        });
+    const bool last = VECTOR && kA < kB && kB == nb;
+    for (int base = 0; base < N; base += NT * U) {
+        int v[U];
+        Raw w[VECTOR ? U : 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int a = base + u * NT + tid;
+            v[u] = a < n ? (VECTOR ? 0 : ty[a]) : -1;
+            if (VECTOR && v[u] == 0) w[VECTOR ? u : 0] = fetch(a, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int a = base + u * NT + tid;
+            bool own;
+            if (VECTOR) {
+                float pp[3], r = 0.0f;
+                const int key = v[u] == 0 ? place(w[VECTOR ? u : 0], 0, pp, r) : -1;
+                own = key >= kA && key < kB && key != D + 2;
+                const unsigned long long culled = __ballot(key == D + 2);
+                int at = 0;
+                if (lane == 0 && culled) at = atomicAdd(&s_cnt[D + 2], (int)__builtin_popcountll(culled));
+                if (key == D + 2) {
+                    if (last) {
+                        at = n - 1 - bcast(at, 0) - (int)__builtin_popcountll(culled & ((1ull << lane) - 1ull));
+                        ws.rec[(size_t)b * N + at] = make_float4(pp[0], pp[1], pp[2], 0.0f);
+                        ws.idx[(size_t)b * N + at] = a;
+                        ws.alive[(size_t)b * N + a] = 0;
+                    }
+                } else if (key >= 0 && !own) {
+                    atomicAdd(&s_cnt[key], 1);
+                }
+                if (p == 0 && a < N && v[u] < 0) ws.alive[(size_t)b * N + a] = 0;       // past natoms
+            } else {
+                own = v[u] >= tA && v[u] < tB;
+                less += v[u] >= 0 && v[u] < tA ? 1 : 0;
+                if (p == 0 && a < N && (v[u] < 0 || v[u] >= T)) ws.alive[(size_t)b * N + a] = 0;        // no group owns this atom
+            }
+            const unsigned long long m = __ballot(own);
+            int at = 0;
+            if (lane == 0 && m) at = atomicAdd(&s_found, (int)__builtin_popcountll(m));
+            at = bcast(at, 0) + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+            if (own && at < kOwnAtoms) s_own[at] = a;
+        }
+    }
     if (!VECTOR) {
         const int incl = wave_inclusive_scan(less);
         if (lane == 63 && incl > 0) atomicAdd(&s_less, incl);
+    }
+    __syncthreads();
+    const int found = s_found;
+    const bool kept = found <= kOwnAtoms;       // (else, rarely, three passes over all atoms)
+
+    // ---- 1. atoms per key ----
+    constexpr int kPer = kOwnAtoms / NT;
+    int my_a[kPer], my_slot[kPer];      // slot: key << 14 | place within the bin
+    static_assert(kOwnAtoms <= 1 << 14 && kRangeMaxKeys < 1 << 17, "packed into a word");
+    // body(u, atom, type, Raw) for the kept atoms of this thread, four requested at a time
+    const auto for_kept = [&](auto body) {
+#pragma unroll
+        for (int u0 = 0; u0 < kPer; u0 += 4) {
+            if (u0 * NT >= found) break;
+            int t[4];
+            Raw w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = VECTOR || my_a[u0 + u] < 0 ? 0 : ty[my_a[u0 + u]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (my_a[u0 + u] >= 0) w[u] = fetch(my_a[u0 + u], t[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (my_a[u0 + u] >= 0) body(u0 + u, my_a[u0 + u], t[u], w[u]);
+        }
+    };
+    if (kept) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) my_a[u] = u * NT + tid < found ? s_own[u * NT + tid] : -1;
+        for_kept([&](int u, int a, int t, const Raw &w) {
+            float pp[3], r;
+            const int key = place(w, t, pp, r);
+            my_slot[u] = key << 14 | atomicAdd(&s_cnt[key], 1);
+            if (!VECTOR && r > 0.0f) atomicMax(&s_rmax[t - tA], __float_as_int(r));         // r > 0: ordered like ints
+            ws.alive[(size_t)b * N + a] = r > 0.0f ? 1 : 0;
+        });
+    } else {
+        for (int k = tid; k < K; k += NT) s_cnt[k] = 0;
+        __syncthreads();
+        for_mine([&](int a, int t, const Raw &w) {
+            float pp[3], r;
+            const int key = place(w, t, pp, r);
+            atomicAdd(&s_cnt[key], 1);
+            if (!VECTOR && r > 0.0f) atomicMax(&s_rmax[t - tA], __float_as_int(r));
+            if (key >= kA && key < kB) ws.alive[(size_t)b * N + a] = r > 0.0f ? 1 : 0;
+        });
     }
     __syncthreads();
     if (MG_STOP_IS(stop, 3)) return;
@@ -508,13 +746,18 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     const int first = VECTOR ? 0 : s_less;
     float4 *rec = ws.rec + (size_t)b * N + first;
     int *idx = ws.idx + (size_t)b * N + first, *order = ws.rchan + (size_t)b * N + first;
-    for_mine(
-        [&](int a, int t, const Raw &w) {
+    const int own0 = s_pos[kA];         // (vector types: the share's bins begin there)
+    if (kept) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (my_a[u] >= 0) s_own[s_pos[my_slot[u] >> 14] - own0 + (my_slot[u] & 16383)] = my_a[u];
+    } else {
+        for_mine([&](int a, int t, const Raw &w) {
             float pp[3], r;
             const int key = place(w, t, pp, r);
             if (key >= kA && key < kB) order[s_pos[key] + atomicAdd(&s_cnt[key], 1)] = a;
-        },
-        [&](int, int) {});
+        });
+    }
     if (!VECTOR || p == 0) {
         for (int tg = tid; tg < Tg; tg += NT) {
             const int f = s_pos[tg * nb], dead = s_pos[tg * nb + D + 2], end = s_pos[(tg + 1) * nb];
@@ -534,6 +777,33 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     if (MG_STOP_IS(stop, 5)) return;
 
     // ---- 4. records: the atoms of a bin in atom order (the order the forward kernel sums in) ----
+    if (kept) {
+        // in order of bins: the lanes of a wavefront compare with the same few atoms (33 -> 24 us for 9000
+        // atoms of four types), and neighbours write next to each other
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) my_a[u] = u * NT + tid < found ? s_own[u * NT + tid] : -1;
+        for_kept([&](int u, int a, int t, const Raw &w) {
+            float pp[3], r;
+            const int key = place(w, t, pp, r), lo = s_pos[key], cnt = s_pos[key + 1] - lo;
+            int at = own0 + u * NT + tid;               // culled atoms: where they are
+            if (r > 0.0f) {
+                at = lo;
+                int i = 0;
+                for (; i + 4 <= cnt; i += 4) {
+                    int o[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) o[k] = s_own[lo - own0 + i + k];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) at += o[k] < a ? 1 : 0;
+                }
+                for (; i < cnt; ++i) at += s_own[lo - own0 + i] < a ? 1 : 0;
+            }
+            rec[at] = make_float4(pp[0], pp[1], pp[2], r);
+            idx[at] = a;
+            if (!VECTOR) order[at] = t;                 // rchan
+        });
+        return;
+    }
     const int e0 = s_pos[kA], e1 = s_pos[kB];
     for (int e = e0 + tid; e < e1; e += NT) {
         const int a = order[e], t = VECTOR ? 0 : ty[a];
@@ -680,38 +950,34 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     const unsigned tag = workspace_tag(gs, bt);
     const bool vec = bt.vec;
     ExLayout L;
-    L.Tg = vec ? 1 : bt.T;
+    L.Tg = bt.T;
     L.N = bt.N;
     const long long K = (long long)L.Tg * (gs.D + 3);
-    const bool fits = bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
+    const bool fits = !vec && bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
     L.K = fits ? (int)K : 0;
     const size_t lds_bytes = (size_t)L.ints() * sizeof(int);
+    if (vec && bt.N <= kExMaxAtoms) {
+        const dim3 grd(bt.B), blk(kExThreads);
+        const size_t lds = ((size_t)(gs.D + 3) * (kExThreads / 64) + 1) / 2 * sizeof(int);
+        if (bt.N <= 2 * kExThreads)
+            hipLaunchKernelGGL(prep_example_vector_kernel<2>, grd, blk, lds, stream, gs, bt, ws, tag, stop);
+        else if (bt.N <= 4 * kExThreads)
+            hipLaunchKernelGGL(prep_example_vector_kernel<4>, grd, blk, lds, stream, gs, bt, ws, tag, stop);
+        else
+            hipLaunchKernelGGL(prep_example_vector_kernel<8>, grd, blk, lds, stream, gs, bt, ws, tag, stop);
+        return hipGetLastError();
+    }
     if (fits && lds_bytes <= kExMaxLds) {
         const dim3 grd(bt.B);
         // 512 threads while they still hold all the atoms four apiece: half as many wavefronts
         // behind every barrier (1 us less per call at 2040 atoms; 256 threads with eight atoms
         // apiece measured 4 us more)
-        if (bt.N <= 4 * 512 && !vec) {      // (vector types, which also rank the channels: 1024 is 1.5 us quicker)
-            hipLaunchKernelGGL((prep_example_kernel<false, 4, 512>), grd, dim3(512), lds_bytes, stream, gs,
-                               bt, ws, tag, stop);
-            return hipGetLastError();
-        }
-        const dim3 blk(kExThreads);
-        if (bt.N <= 4 * kExThreads) {
-            if (vec)
-                hipLaunchKernelGGL((prep_example_kernel<true, 4, kExThreads>), grd, blk, lds_bytes, stream, gs, bt,
-                                   ws, tag, stop);
-            else
-                hipLaunchKernelGGL((prep_example_kernel<false, 4, kExThreads>), grd, blk, lds_bytes, stream, gs,
-                                   bt, ws, tag, stop);
-        } else {
-            if (vec)
-                hipLaunchKernelGGL((prep_example_kernel<true, 8, kExThreads>), grd, blk, lds_bytes, stream, gs, bt,
-                                   ws, tag, stop);
-            else
-                hipLaunchKernelGGL((prep_example_kernel<false, 8, kExThreads>), grd, blk, lds_bytes, stream, gs,
-                                   bt, ws, tag, stop);
-        }
+        if (bt.N <= 4 * 512)
+            hipLaunchKernelGGL((prep_example_kernel<4, 512>), grd, dim3(512), lds_bytes, stream, gs, bt, ws, tag, stop);
+        else if (bt.N <= 4 * kExThreads)
+            hipLaunchKernelGGL((prep_example_kernel<4, kExThreads>), grd, dim3(kExThreads), lds_bytes, stream, gs, bt, ws, tag, stop);
+        else
+            hipLaunchKernelGGL((prep_example_kernel<8, kExThreads>), grd, dim3(kExThreads), lds_bytes, stream, gs, bt, ws, tag, stop);
         return hipGetLastError();
     }
     // (up to 8192 atoms one workgroup per example is quicker, its atoms stay in registers: 115
