@@ -17,7 +17,8 @@
 // atom whose cutoff cube misses the grid box contributes nothing.
 //
 // Usual sizes: one workgroup per example (512 threads up to 2048 atoms of index
-// types, 1024 otherwise) does a counting sort of the example's atoms by (type, x-plane bin) in LDS:
+// types, 1024 otherwise) does a counting sort of the example's atoms by (type, x-plane bin) in LDS (vector
+// types: by bin, with a sort that is stable by itself, see prep_example_vector_kernel):
 //   1. every atom: transform, cull, key = type * bins + bin (bins 0 and D+1 are
 //      the atoms left / right of the grid, bin D+2 the culled ones), count;
 //   2. exclusive scan of the counts = where each (type, bin) starts;
@@ -471,15 +472,15 @@ __global__ __launch_bounds__(kExThreads) void prep_example_vector_kernel(GridSpe
 // Large examples: P workgroups per example, no exchange between them.  Workgroup p looks at all
 // atoms of the example but sorts and writes only its share of the keys: index types, the types
 // [tA, tB) (the atoms of smaller types are counted on the way: where its records start; the
-// coordinates of other types' atoms are not even read); vector types, a run of x-plane bins.
-// Nothing of an atom is kept between the passes -- key, counting pass, placing pass and
-// ranking pass each place the atom anew, which costs less than a trip to memory -- so N is not
-// limited by registers or LDS, and the list of the atoms in bin order sits in the workspace
-// (rchan, whose final contents are written last).
-// Bound: trips to memory, N / 8192 rounds of two per pass.  Two examples of 20000 atoms and 18
-// channels as eight subgrids each: 42 us (one wavefront per channel and example: 206 us; and a
-// channel of more than 2048 atoms was then left unsorted, so that every forward tile read all of
-// it: 130 us, now 24).
+// coordinates of other types' atoms are not even read); vector types, a run of x-plane bins (all
+// atoms are placed once, to count the other bins).
+// The share's atoms are listed in LDS on the way.  Only those are placed after that, twice (which costs
+// less than keeping their positions in registers): for the counts, and in order of bins for the
+// records.  A share of more than kOwnAtoms atoms goes through all atoms again instead for the counts and for
+// the places, and its list in bin order sits in the workspace (rchan, whose final contents are written last).
+// Bound: trips to memory one after the other, and placing atoms in double precision.  Two examples of
+// 20000 atoms and 18 channels as eight subgrids each: 27 us, 42 when all passes went through all
+// atoms; one of 20000, 28 channels 17 / 31; 12000 in two channels 34 / 57; vector types, two of 20000 28 / 56.
 // ---------------------------------------------------------------------------
 constexpr int kRangeThreads = 1024;
 constexpr int kRangeMaxKeys = 1700;     // keys of a workgroup: two words of LDS each
@@ -787,6 +788,7 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
             const int key = place(w, t, pp, r), lo = s_pos[key], cnt = s_pos[key + 1] - lo;
             int at = own0 + u * NT + tid;               // culled atoms: where they are
             if (r > 0.0f) {
+                if (cnt > kRankBin) return;             // below
                 at = lo;
                 int i = 0;
                 for (; i + 4 <= cnt; i += 4) {
@@ -800,12 +802,10 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
             }
             rec[at] = make_float4(pp[0], pp[1], pp[2], r);
             idx[at] = a;
-            if (!VECTOR) order[at] = t;                 // rchan
         });
-        return;
     }
     const int e0 = s_pos[kA], e1 = s_pos[kB];
-    for (int e = e0 + tid; e < e1; e += NT) {
+    for (int e = e0 + tid; !kept && e < e1; e += NT) {
         const int a = order[e], t = VECTOR ? 0 : ty[a];
         float pp[3], r;
         const int key = place(fetch(a, t), t, pp, r);
@@ -953,7 +953,12 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     L.Tg = bt.T;
     L.N = bt.N;
     const long long K = (long long)L.Tg * (gs.D + 3);
-    const bool fits = !vec && bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
+    // Index types of more than 4096 atoms: shares of the types for several workgroups while there are few
+    // examples, else one workgroup per example.  Kernel, us, shares / one workgroup: 16 x 8000 atoms, 28 channels 13 / 20,
+    // 1 x 8000 11 / 18, 32 x 8000 16 / 19, 48 x 8000 26 / 20, 64 x 8000 in eight channels 24 / 18, 12 x 8000 in one 29 / 37;
+    // below 4096 atoms alike for few examples (20 x 3000 11 / 11), worse for many (50 x 2040 18 / 10).
+    const bool shared = bt.N > 4096 && bt.B <= 32;
+    const bool fits = !vec && !shared && bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
     L.K = fits ? (int)K : 0;
     const size_t lds_bytes = (size_t)L.ints() * sizeof(int);
     if (vec && bt.N <= kExMaxAtoms) {
@@ -980,9 +985,6 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
             hipLaunchKernelGGL((prep_example_kernel<8, kExThreads>), grd, dim3(kExThreads), lds_bytes, stream, gs, bt, ws, tag, stop);
         return hipGetLastError();
     }
-    // (up to 8192 atoms one workgroup per example is quicker, its atoms stay in registers: 115
-    // against 132 us a call at 50 x 3000 atoms, 22.5 against 24 us at 1 x 4000, 296 against 305 us
-    // at 16 x 8000)
     // shares per example: enough workgroups for the chip, at most kRangeMaxKeys keys each
     const int nb = gs.D + 3, units = vec ? nb : bt.T;
     const int want = std::max(1, std::min(units, (256 + bt.B - 1) / bt.B));

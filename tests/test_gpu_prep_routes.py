@@ -1,0 +1,73 @@
+"""The kernels that sort the atoms, at the sizes where another one or another way through it takes over:
+vector types up to 2048, 4096 and 8192 atoms (two, four and eight per thread of one workgroup), index types up to
+4096 atoms or past 32 examples (one workgroup) and beyond (shares of the types, listed in LDS up to 12288
+atoms), bins of thousands of atoms, planes of many bins.  Records have one order: every run gives the same bits."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import GRAD_RTOL, dev, grid_tol, mg  # noqa: E402,F401
+
+
+def _inputs(B, N, T, D, spread, skew, seed):
+    rng = np.random.default_rng(seed)
+    dim = (D - 1) * 0.75
+    coords = rng.uniform(-dim / 2 - spread, dim / 2 + spread, (B, N, 3)).astype(np.float32)
+    types = rng.integers(0, T, (B, N)).astype(np.int32)
+    types[rng.random((B, N)) < skew] = 0            # most atoms of one type
+    radii = rng.uniform(0.6, 1.5, T).astype(np.float32)
+    natoms = np.maximum(N - np.arange(B, dtype=np.int32) * (N // 3), 1)
+    pose = dict(natoms=natoms, quats=rng.standard_normal((B, 4)).astype(np.float32))
+    return rng, dim, coords, types, radii, pose, {k: dev(v) for k, v in pose.items()}
+
+
+@pytest.mark.parametrize("B,N,T,D,spread,skew", [
+    (2, 4097, 3, 16, 2.0, 0.0), (1, 8192, 5, 16, 20.0, 0.0), (33, 4097, 2, 8, 3.0, 0.0),
+    (1, 12288, 1, 16, 6.0, 0.0), (1, 12289, 1, 16, 6.0, 0.0), (1, 14000, 9, 12, 8.0, 0.95), (2, 9000, 4, 70, 1.0, 0.5),
+])
+def test_index_types(mg, B, N, T, D, spread, skew):
+    rng, dim, coords, types, radii, pose, dpose = _inputs(B, N, T, D, spread, skew, N + D)
+    co, ty, ra = dev(coords), dev(types), dev(radii)
+    gm = mg.GridMaker(0.75, dim, radius_type_indexed=True)
+    ws = gm.mg_prepare(co, ty, ra, T, **dpose)
+    outs = [gm.mg_forward_index(co, ty, ra, T, **dpose).cpu().numpy() for _ in range(2)]
+    outs.append(gm.mg_forward_index_prepared(B, N, T, ws).cpu().numpy())
+    ref = oracle.forward_index(coords, types, radii, T, 0.75, dim, **pose)
+    assert np.abs(outs[0] - ref).max() <= grid_tol(ref)
+    for o in outs[1:]:
+        assert np.array_equal(outs[0].view(np.uint32), o.view(np.uint32))
+    G = rng.standard_normal(ref.shape).astype(np.float32)
+    want = oracle.backward_index(coords, types, radii, T, 0.75, dim, G, **pose)
+    got = gm.mg_backward_index(co, ty, ra, T, dev(G), **dpose).cpu().numpy()
+    assert np.abs(got - want).max() <= GRAD_RTOL * np.abs(want).max()
+
+
+@pytest.mark.parametrize("B,N,T,D,spread,crowd", [
+    (1, 1, 2, 9, 0.0, 0), (2, 63, 3, 9, 1.0, 0), (3, 2048, 5, 14, 2.0, 0), (2, 2049, 4, 14, 2.0, 0), (1, 4097, 3, 13, 4.0, 3000),
+    (1, 8192, 70, 8, 6.0, 0), (1, 8193, 2, 13, 10.0, 0), (1, 20011, 3, 12, 2.0, 9000), (1, 500, 2, 130, 0.5, 0),
+])
+def test_vector_types(mg, B, N, T, D, spread, crowd):
+    rng, dim, coords, _, radii, pose, dpose = _inputs(B, N, T, D, spread, 0.0, N + D)
+    if crowd:                       # one plane's bin holds thousands of atoms
+        pose["quats"] = dpose["quats"] = None
+        coords[:, rng.permutation(N)[:crowd], 0] = 0.4
+    # sums of thousands of weights stay within what fixed point holds
+    w = (rng.random((B, N, T)) * min(1.0, 60.0 / (N * 0.2))).astype(np.float32)
+    co, ra = dev(coords), dev(radii)
+    gm = mg.GridMaker(0.75, dim, radius_type_indexed=True)
+    ws = gm.mg_prepare(co, None, ra, T, **dpose)
+    outs = [gm.mg_forward_vector(co, dev(w), ra, **dpose).cpu().numpy() for _ in range(2)]
+    outs.append(gm.mg_forward_vector_prepared(dev(w), ra, ws).cpu().numpy())
+    ref = oracle.forward_vector(coords, w, radii, 0.75, dim, **pose)
+    assert np.abs(outs[0] - ref).max() <= grid_tol(ref)
+    for o in outs[1:]:
+        assert np.array_equal(outs[0].view(np.uint32), o.view(np.uint32))
+    G = rng.standard_normal(ref.shape).astype(np.float32)
+    wc, ww = oracle.backward_vector(coords, w, radii, 0.75, dim, G, **pose)
+    gc, gw = gm.mg_backward_vector_prepared(dev(w), ra, dev(G), ws)
+    assert np.abs(gc.cpu().numpy() - wc).max() <= GRAD_RTOL * max(np.abs(wc).max(), 1e-30)
+    assert np.abs(gw.cpu().numpy() - ww).max() <= GRAD_RTOL * max(np.abs(ww).max(), 1e-30)
