@@ -10,9 +10,8 @@
 //   -f/4 = exp(-2x^2)            x <= g
 //        = (A/2) (c/x - 1)       g < x < c     (at most exp(-2g^2) <= 1 there)
 //        = 0                     x >= c
-// which the hardware evaluates as one fused multiply-add clamped to [0,1] (the tail
-// is <= 1 on its own interval and negative beyond the cutoff), and the factor -4 goes
-// into the scale applied once per atom.  The gradient with respect to the caller's
+// as a product without a select (see reduce_slot), and the factor -4 goes into the scale
+// applied once per atom.  The gradient with respect to the caller's
 // coordinates is R^T times that sum.
 //
 // One wavefront per atom record (four records per workgroup, no barrier).  The
@@ -26,10 +25,11 @@
 // the lanes numbers the live slots, and slot s finds its row through a byte
 // array in LDS (the first slot of each lane's rows is marked with the lane, a
 // running maximum over the slots gives the owner) and one register exchange.
-// Index types are bound by vector instruction issue (3.745e7 instructions on 50 x 2040 atoms,
-// 28 x 48^3: 61 of 72 us; a third of them the density, the rest finding rows and slots), with the
-// arrival of the scattered lines close behind (45 % of their rate).  The three partial sums
-// are reduced across the wavefront by DPP adds in a fixed order.  Records are grouped by
+// Index types are bound by vector instruction issue (50 x 2040 atoms, 28 x 48^3: three quarters of
+// the time; a third of the instructions the density, the rest finding rows and slots) and by the arrival of the
+// scattered lines (376 MB of 128-byte lines from HBM, 5.2 TB/s).  The three partial sums
+// are reduced across the wavefront together, in a fixed order (wave_sum4; with the slope as a
+// product instead of a select 76 instead of 78.6 us a call).  Records are grouped by
 // channel (and, within a channel, by x-plane), so neighbouring wavefronts read
 // the same part of the same channel volume.
 // (Consecutive lanes take consecutive slots of a row, so a 64-lane load touches about 25
@@ -68,11 +68,9 @@ struct BwdParams {
     unsigned wgs_per_example;       // workgroups (of four records) per example
     unsigned units, share;          // workgroups in all; per XCD (ceil(units / 8))
     unsigned long long wg_magic;    // ceil(2^64 / wgs_per_example), 0 if that is 1
-    float sk, inv_sk, g2k, c2k;     // sqrt(k), 1/sqrt(k), g^2 k, c^2 k with k = 2 log2(e)
-    float hA, hAck;         // A/2, (A/2) c sqrt(k): -f/4 = clamp(hAck / x' - hA, 0, 1) in the tail
-    float k;                // vector types: k
-    float ng2k, nfA, fAc;   // ... -g^2 k, -2g^2, 2g^2 c
-    float tg, tc;           // ... 2g, 2g c
+    float k;                // 2 log2(e)
+    float ng2k, nfA, fAc;   // -g^2 k, -2g^2, 2g^2 c
+    float tg, tc;           // vector types: 2g, 2g c
 };
 
 // a value that is the same in all lanes, kept in a scalar register
@@ -81,25 +79,10 @@ __device__ inline float uniform(float v)
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// v + (v of the lane the DPP control selects, 0 where there is none or the row is masked out)
-template <int CTRL, int ROW_MASK>
-__device__ inline float add_dpp(float v)
+// 1 / r (the hardware's approximation, 1 ulp), small enough to be squared
+__device__ inline float scale_of(float r)
 {
-    return v + __int_as_float(
-                   __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
-}
-
-// Sum over the 64 lanes in a fixed order (an inclusive scan by DPP row shifts and row
-// broadcasts, whose last lane holds the total); returned in every lane.
-__device__ inline float wave_sum(float v)
-{
-    v = add_dpp<0x111, 0xf>(v);     // row_shr:1
-    v = add_dpp<0x112, 0xf>(v);     // row_shr:2
-    v = add_dpp<0x114, 0xf>(v);     // row_shr:4
-    v = add_dpp<0x118, 0xf>(v);     // row_shr:8
-    v = add_dpp<0x142, 0xa>(v);     // row_bcast:15 -> rows 1, 3
-    v = add_dpp<0x143, 0xc>(v);     // row_bcast:31 -> rows 2, 3
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+    return fminf(__builtin_amdgcn_rcpf(r), 1.0e18f);
 }
 
 struct Box {
@@ -129,12 +112,13 @@ __device__ inline bool atom_box(const GridSpec &gs, float reach, const float4 &a
     return bx.np > 0 && bx.nr > 0 && bx.ns > 0 && khi >= klo;
 }
 
-// Accumulate over one channel volume, in coordinates scaled to units of r/sqrt(k),
-// k = 2 log2(e) (then exp(-2x^2) = exp2(-x'^2)):  (sx, sy, sz) += sum G (-f/4) u'.
-//   -f/4 = exp2(-x'^2)                                  x'^2 <= g^2 k
-//        = clamp((A/2) c sqrt(k) / x' - A/2, 0, 1)      beyond (zero from the cutoff on)
+// Accumulate over one channel volume: (sx, sy, sz) += sum G (-f/4) u, distances in Angstrom (differences of
+// nearby numbers and whole steps of the spacing: a scaled spacing, rounded, times a row's length was the largest
+// error of a gradient).  With E = exp(-2 min(x, g)^2) = exp2(max(-k d^2 / r^2, -g^2 k)), k = 2 log2(e),
+//   -f/4 = E clamp(2g^2 (c r / d - 1), 0, 1)
+// (2g^2 (c/g - 1) = 1, and A = 4 g^2 exp(-2g^2)): no select.
 // One slot: the four voxels k4 .. k4+3 of the grid row at float offset `row_off` of the
-// channel (a channel has at most 2^30 floats); ux, uy: the row's scaled x and y distance.
+// channel (a channel has at most 2^30 floats); ux, uy: the row's x and y distance.
 struct SlotData {
     float gv[4];        // upstream gradient of the four voxels
     float ux, uy;
@@ -188,24 +172,26 @@ __device__ inline void load_slot(const BwdParams &p, const GT *Gc, unsigned row_
     d.ux = ux; d.uy = uy; d.k4 = k4;
 }
 
-__device__ inline void reduce_slot(const BwdParams &p, float step, float azs, const SlotData &d,
+struct ChannelCoef {
+    float nr2;          // -k / r^2
+    float fq;           // 2 g^2 c r
+};
+
+__device__ inline void reduce_slot(const BwdParams &p, const ChannelCoef &cc, float az, const SlotData &d,
                                    float &sx, float &sy, float &sz)
 {
     const float ux = d.ux, uy = d.uy;
-    const int k4 = d.k4;
     const float *gv = d.gv;
-    const float b2 = ux * ux + uy * uy;
-    const float uz0 = fmaf(-(float)k4, step, azs);
+    const float b2 = fmaf(ux, ux, uy * uy);
+    const float uz0 = fmaf(-(float)d.k4, p.gs.res, az);
     float fsum = 0.0f;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const float uz = uz0 - (float)u * step;
-        const float x2 = fmaf(uz, uz, b2);
-        const float e = __builtin_amdgcn_exp2f(-x2);
-        const float rs = __builtin_amdgcn_rsqf(x2);
-        const float ft = __builtin_amdgcn_fmed3f(fmaf(p.hAck, rs, -p.hA), 0.0f, 1.0f);
-        const float f = x2 <= p.g2k ? e : ft;       // -f/4
-        const float gf = gv[u] * f;
+        const float uz = fmaf(-(float)u, p.gs.res, uz0);
+        const float d2 = fmaf(uz, uz, b2);
+        const float e = __builtin_amdgcn_exp2f(fmaxf(d2 * cc.nr2, p.ng2k));
+        const float ft = __builtin_amdgcn_fmed3f(fmaf(cc.fq, __builtin_amdgcn_rsqf(d2), p.nfA), 0.0f, 1.0f);
+        const float gf = gv[u] * e * ft;
         fsum += gf;
         sz = fmaf(gf, uz, sz);
     }
@@ -216,17 +202,14 @@ __device__ inline void reduce_slot(const BwdParams &p, float step, float azs, co
 // Every slot of the box (boxes with very many segments per row).
 template <bool ALIGNED, typename GT>
 __device__ inline void reduce_channel_box(const BwdParams &p, const GT *Gc, const float4 &a,
-                                          float r, const Box &bx, float ox, float oy, float oz,
+                                          const ChannelCoef &cc, const Box &bx, float ox, float oy, float oz,
                                           float &sx, float &sy, float &sz)
 {
     const GridSpec &gs = p.gs;
     const int per_plane = bx.nr * bx.ns;
     const int slots = bx.np * per_plane;        // at most D^3 / 4 < 2^31
-    const float s = p.sk / r, step = gs.res * s;
-    const float azs = (a.z - oz) * s;
-    // scaled distance of the box's first row; rows step by `step`
-    const float ux0 = (a.x - (ox + (float)bx.ilo * gs.res)) * s;
-    const float uy0 = (a.y - (oy + (float)bx.jlo * gs.res)) * s;
+    // distances of the box's first row
+    const float ux0 = a.x - (ox + (float)bx.ilo * gs.res), uy0 = a.y - (oy + (float)bx.jlo * gs.res);
     for (int sl = (int)(threadIdx.x & 63u); sl < slots; sl += 64) {
         // integer division: a box of hundreds of voxels per side has more slots than a float
         // holds exactly
@@ -234,11 +217,11 @@ __device__ inline void reduce_channel_box(const BwdParams &p, const GT *Gc, cons
         const int rem = sl - pi * per_plane;
         const int row = rem / bx.ns;
         const int seg = rem - row * bx.ns;
-        const float ux = fmaf(-(float)pi, step, ux0), uy = fmaf(-(float)row, step, uy0);
+        const float ux = fmaf(-(float)pi, gs.res, ux0), uy = fmaf(-(float)row, gs.res, uy0);
         SlotData d;
         load_slot<ALIGNED, false>(p, Gc, (unsigned)((bx.ilo + pi) * gs.D + bx.jlo + row) * (unsigned)gs.D,
                            (bx.seg0 + seg) << 2, ux, uy, d);
-        reduce_slot(p, step, azs, d, sx, sy, sz);
+        reduce_slot(p, cc, a.z - oz, d, sx, sy, sz);
     }
 }
 
@@ -251,23 +234,21 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
                                       float oz, unsigned char *marks, float &sx, float &sy,
                                       float &sz)
 {
+    // reciprocals by the hardware approximation (1 ulp): the row split below has a margin of
+    // 0.5/nr and the scale enters the result with a relative error of 1e-7
+    const float inv_r = scale_of(r), reach = r * p.gs.c, reach2 = reach * reach;
+    const ChannelCoef cc = {-(p.k * inv_r) * inv_r, p.fAc * r};
     if (bx.ns > kMaxCulledSegs || bx.np * bx.nr > kMaxCulledRows) {
-        reduce_channel_box<ALIGNED>(p, G + (size_t)t * D3, a, r, bx, ox, oy, oz, sx, sy, sz);
+        reduce_channel_box<ALIGNED>(p, G + (size_t)t * D3, a, cc, bx, ox, oy, oz, sx, sy, sz);
         return;
     }
     const GridSpec &gs = p.gs;
     const int lane = (int)(threadIdx.x & 63u);
     const int rows = bx.np * bx.nr;
-    // reciprocals by the hardware approximation (1 ulp): the row split below has a margin of
-    // 0.5/nr and the scale enters the result with a relative error of 1e-7
     const float inv_nr = __builtin_amdgcn_rcpf((float)bx.nr);
-    const float s = p.sk * __builtin_amdgcn_rcpf(r), step = gs.res * s;
-    const float inv_step = __builtin_amdgcn_rcpf(step);
-    const float azs = (a.z - oz) * s;
-    const float fz = (a.z - oz) * gs.inv_res;           // the atom's z in grid steps
-    // scaled distance of the box's first row; rows step by `step`
-    const float ux0 = (a.x - (ox + (float)bx.ilo * gs.res)) * s;
-    const float uy0 = (a.y - (oy + (float)bx.jlo * gs.res)) * s;
+    const float az = a.z - oz, fz = az * gs.inv_res;    // fz: the atom's z in grid steps
+    // distances of the box's first row
+    const float ux0 = a.x - (ox + (float)bx.ilo * gs.res), uy0 = a.y - (oy + (float)bx.jlo * gs.res);
     const unsigned D = (unsigned)gs.D;
     const unsigned off0 = ((unsigned)bx.ilo * D + (unsigned)bx.jlo) * D;   // the box's first row
     for (int row0 = 0; row0 < rows; row0 += 128) {
@@ -279,11 +260,11 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
             if (row < rows) {
                 const int pi = (int)(((float)row + 0.5f) * inv_nr);
                 const int jr = row - pi * bx.nr;
-                const float ux = fmaf(-(float)pi, step, ux0), uy = fmaf(-(float)jr, step, uy0);
-                const float h2 = p.c2k - (ux * ux + uy * uy);
+                const float ux = fmaf(-(float)pi, gs.res, ux0), uy = fmaf(-(float)jr, gs.res, uy0);
+                const float h2 = reach2 - (ux * ux + uy * uy);
                 if (h2 > 0.0f) {
                     // half chord in grid steps; the pad only adds voxels that contribute 0
-                    const float hv = __builtin_amdgcn_sqrtf(h2) * inv_step + 1.0e-3f;
+                    const float hv = __builtin_amdgcn_sqrtf(h2) * gs.inv_res + 1.0e-3f;
                     const int klo = max(bx.klo, (int)ceilf(fz - hv));
                     const int khi = min(bx.khi, (int)floorf(fz + hv));
                     if (khi >= klo) {       // 4-voxel slots from the chord's first voxel, kept inside the row
@@ -326,11 +307,11 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
                 const int row = row0 + 2 * owner + q;
                 const int pi = (int)(((float)row + 0.5f) * inv_nr);
                 const int jr = row - pi * bx.nr;
-                const float ux = fmaf(-(float)pi, step, ux0), uy = fmaf(-(float)jr, step, uy0);
+                const float ux = fmaf(-(float)pi, gs.res, ux0), uy = fmaf(-(float)jr, gs.res, uy0);
                 SlotData d;
                 load_slot<ALIGNED, true>(p, Gc, off0 + ((unsigned)pi * D + (unsigned)jr) * D, k4, ux,
                                    uy, d);
-                reduce_slot(p, step, azs, d, sx, sy, sz);
+                reduce_slot(p, cc, az, d, sx, sy, sz);
             }
         }
         lds_sync();
@@ -659,11 +640,10 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         if (atom_box(gs, r * gs.c, a, ox, oy, oz, bx))
             reduce_channel<ALIGNED>(p, reinterpret_cast<const GT *>(p.G) + (size_t)b * T * D3, t, D3, a, r, bx, ox, oy, oz,
                                     marks, sx, sy, sz);
-        // -4 (the sums hold -f/4) / r^2 times r/sqrt(k) (they are in scaled units)
-        const float inv_r2 = -4.0f * __builtin_amdgcn_rcpf(r * p.sk);
-        tx = wave_sum(sx) * inv_r2;
-        ty = wave_sum(sy) * inv_r2;
-        tz = wave_sum(sz) * inv_r2;
+        const float inv_r2 = -4.0f * scale_of(r) * scale_of(r);         // (the sums hold -f/4)
+        tx = sx * inv_r2;
+        ty = sy * inv_r2;
+        tz = sz * inv_r2;
     } else {
         // the atom is the wavefront's: what depends on it and on the channel stays in scalar registers
         ai = __builtin_amdgcn_readfirstlane(ai);
@@ -701,7 +681,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
                 v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 1));
                 v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 2));
             }
-            const float inv = r > 0.0f ? __builtin_amdgcn_rcpf(r) : 0.0f;
+            const float inv = r > 0.0f ? scale_of(r) : 0.0f;
             const float v_nr2 = -(p.k * inv) * inv, v_fq = p.fAc * r, v_tq = -(p.tg * inv), v_cq = -4.0f * (w * inv) * inv;
             const auto lane_value = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
             float gw = 0.0f;                // lane l: the weight gradient of the channel of rank l
@@ -735,7 +715,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
             if (WANT_W && lane < count) p.grad_weights[grow + chan] = gw;
         }
     }
-    if (VECTOR && p.grad_coords) {
+    if (p.grad_coords) {
         const float t = wave_sum4(tx, ty, tz, 0.0f);
         tx = __int_as_float(bcast(__float_as_int(t), 0));
         ty = __int_as_float(bcast(__float_as_int(t), 1));
@@ -817,12 +797,6 @@ hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace 
     p.raw = raw_inputs(bt);
     {
         const double k = 2.8853900817779268;    // 2 / ln 2
-        p.sk = (float)std::sqrt(k);
-        p.inv_sk = (float)(1.0 / std::sqrt(k));
-        p.g2k = (float)((double)gs.g2 * k);
-        p.c2k = (float)((double)gs.c * (double)gs.c * k);
-        p.hA = (float)(0.5 * (double)gs.A);
-        p.hAck = (float)(0.5 * (double)gs.A * (double)gs.c * std::sqrt(k));
         // (beyond x = 100 the density is 0 in float whatever the branch: larger g need no larger constants)
         const double g2 = std::fmax(std::fmin((double)gs.g2, 1.0e4), 1.0e-30), g = std::sqrt(g2), c = g + 0.5 / g;
         p.ng2k = (float)(-g2 * k);
