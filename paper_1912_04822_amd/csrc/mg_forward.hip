@@ -925,10 +925,14 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
 // the chord fetch it from the lane that holds the atom.  It is a factor and not part of the exponent: an
 // exponent of log2|w| + 25 is rounded at 2^-20, which cost 38 -> 34 instructions per step but made the
 // error of weights of one and more 2.5 times as large (2.1e-7 -> 5.1e-7).
-// Bound by vector instruction issue: 38 instructions per step of 64 chords and four channels, 524 us a
-// call on 50 x 2040 atoms, 28 x 48^3 (532 us with the two branches selected).  Measured and slower: chords cut into slots of four voxels and queued in LDS (7 % fewer instructions, 12 instead of
-// 16 wavefronts per CU: 612 us); tasks in order of the row's distance from the atom (523 us); tile rows
-// padded in LDS (half the bank conflicts, 509 us).
+// Bound by vector instruction issue: 38 instructions per step of 64 chords and four channels (some 137 cycles: 24
+// of them at 2.3, nine at 4.4, the five roots and exponentials at 8.5), with 54 % of the lanes inside the
+// sphere; 501 us a call on 50 x 2040 atoms, 28 x 48^3.  Measured and slower: chords cut into slots of four voxels and
+// queued in LDS (7 % fewer instructions, 12 instead of 16 wavefronts per CU: 612 us); tasks in order of the
+// row's distance from the atom (523 us); tile rows padded in LDS (half the bank conflicts, 509 us); no chords at
+// all, a voxel per lane in bricks of 4 x 4 x 4 that visit the atoms in reach one after the other, sums in
+// doubles, far visits with the tail's half of the density only (541 us: 30 % of the lanes are inside, a
+// visit of seven channels takes 290 cycles, 145 in the tail).
 // ---------------------------------------------------------------------------
 constexpr int kVecGroup = 4;
 
