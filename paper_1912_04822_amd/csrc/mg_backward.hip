@@ -79,10 +79,11 @@ __device__ inline float uniform(float v)
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// 1 / r (the hardware's approximation, 1 ulp), small enough to be squared
+// 1 / r (the hardware's approximation, 1 ulp), small enough to be squared, and for its square times
+// kTinyDistance2 to be nothing: an atom on a voxel has rho = 1 there however small its radius
 __device__ inline float scale_of(float r)
 {
-    return fminf(__builtin_amdgcn_rcpf(r), 1.0e18f);
+    return fminf(__builtin_amdgcn_rcpf(r), 1.0e14f);
 }
 
 struct Box {
@@ -338,7 +339,7 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
 // at 1 A gains, 225 against 255).
 // ---------------------------------------------------------------------------
 constexpr int kChanGroup = 4;
-constexpr float kTinyDistance2 = 1.0e-30f;      // added to squared distances whose roots are divided by
+constexpr float kTinyDistance2 = 1.0e-37f;      // added to squared distances whose roots are divided by (see scale_of)
 
 struct GroupCoef {              // wave-uniform
     float nr2[kChanGroup];          // -k / r_q^2
@@ -450,7 +451,8 @@ __device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kC
         return;
     }
     const int rows = bx.np * bx.nr;
-    const float inv_nr = __builtin_amdgcn_rcpf((float)bx.nr), reach2 = reach * reach;
+    const float inv_nr = __builtin_amdgcn_rcpf((float)bx.nr);
+    const float reach2 = fmaxf(reach * reach, kTinyDistance2);      // (the square of a very small reach is 0)
     for (int row0 = 0; row0 < rows; row0 += 128) {
         int cnt[2] = {0, 0}, slo[2] = {0, 0};
 #pragma unroll

@@ -38,3 +38,27 @@ def test_channel_groups(mg, T, D, res):
         assert np.abs(gw.cpu().numpy() - ww).max() <= GRAD_RTOL * np.abs(ww).max()
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("radius", [1e-3, 1e-11, 1e-13, 1e-15, 1e-20, 1e-30])
+@pytest.mark.parametrize("T", [3, 9])
+def test_radii_far_below_a_grid_step(mg, T, radius):
+    """An atom on a voxel counts there in full (rho(0) = 1) and nowhere else; beside channels of usual radii."""
+    B, N, D, res = 1, 40, 9, 0.5
+    rng = np.random.default_rng(T)
+    dim = (D - 1) * res
+    coords = (rng.integers(0, D, (B, N, 3)) * res - dim / 2).astype(np.float32)
+    w = rng.standard_normal((B, N, T)).astype(np.float32)
+    radii = np.where(np.arange(T) % 3 == 1, 1.4, radius).astype(np.float32)
+    G = rng.standard_normal((B, T, D, D, D)).astype(np.float32)
+    wc, ww = oracle.backward_vector(coords, w, radii, res, dim, G)
+    gm = mg.GridMaker(res, dim, radius_type_indexed=True)
+    for single in (1, 0):
+        mg.set_option("single_launch", single)
+        try:
+            gc, gw = gm.mg_backward_vector(dev(coords), dev(w), dev(radii), dev(G))
+        finally:
+            mg.set_option("single_launch", 1)
+        assert np.abs(gc.cpu().numpy() - wc).max() <= GRAD_RTOL * np.abs(wc).max()
+        for t in range(T):      # (by channel: the narrow ones beside the wide)
+            assert np.abs(gw.cpu().numpy() - ww)[..., t].max() <= GRAD_RTOL * np.abs(ww[..., t]).max(), t
