@@ -505,16 +505,23 @@ __device__ inline void reduce_group(const BwdParams &p, const GT *const (&Gq)[kC
     }
 }
 
+// The value of another lane of the same four: quad_perm [1,0,3,2] (0xB1) or [2,3,0,1] (0x4E).
+template <int CTRL>
+__device__ inline float quad_swap(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
 // Four sums over the wavefront at once, in a fixed order: sum (lane & 3) in every lane.
 __device__ inline float wave_sum4(float a, float b, float c, float d)
 {
     const int lane = (int)(threadIdx.x & 63u);
     const auto bits = [](float x) { return __float_as_int(x); };
     const bool odd = (lane & 1) != 0, upper = (lane & 2) != 0;
-    // lane l keeps one of a pair and gets the neighbour's part of it: quad_perm [1,0,3,2], then [2,3,0,1]
-    const float ab = (odd ? b : a) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(odd ? a : b), 0xB1, 0xf, 0xf, false));
-    const float cd = (odd ? d : c) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(odd ? c : d), 0xB1, 0xf, 0xf, false));
-    float r = (upper ? cd : ab) + __int_as_float(__builtin_amdgcn_update_dpp(0, bits(upper ? ab : cd), 0x4E, 0xf, 0xf, false));
+    // lane l keeps one of a pair and gets the neighbour's part of it
+    const float ab = (odd ? b : a) + quad_swap<0xB1>(odd ? a : b);
+    const float cd = (odd ? d : c) + quad_swap<0xB1>(odd ? c : d);
+    float r = (upper ? cd : ab) + quad_swap<0x4E>(upper ? ab : cd);
     r += __int_as_float(__builtin_amdgcn_update_dpp(0, bits(r), 0x124, 0xf, 0xf, false));     // row_ror:4
     r += __int_as_float(__builtin_amdgcn_update_dpp(0, bits(r), 0x128, 0xf, 0xf, false));     // row_ror:8
     const auto h = __builtin_amdgcn_permlane16_swap((unsigned)bits(r), (unsigned)bits(r), false, false);
@@ -678,11 +685,11 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
             const float r = lane < count ? gs.radius_scale * p.radii[chan] : 0.0f;
             const float w = lane < count ? p.weights[arow + chan] : 0.0f;
             const unsigned long long live = __ballot(r > 0.0f);
+            // the widest of each group of four, in whatever order the channels are: the tables' order is that
+            // of the radii they were made with, and these are read in this call
             float v_reach = r * gs.c;
-            if (count <= kChanGroup) {      // (in any order: the widest of the four)
-                v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 1));
-                v_reach = fmaxf(v_reach, __shfl_xor(v_reach, 2));
-            }
+            v_reach = fmaxf(v_reach, quad_swap<0xB1>(v_reach));
+            v_reach = fmaxf(v_reach, quad_swap<0x4E>(v_reach));
             const float inv = r > 0.0f ? scale_of(r) : 0.0f;
             const float v_nr2 = -(p.k * inv) * inv, v_fq = p.fAc * r, v_tq = -(p.tg * inv), v_cq = -4.0f * (w * inv) * inv;
             const auto lane_value = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
@@ -701,7 +708,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
                     gc.tq[q] = lane_value(v_tq, l);
                     gc.cq[q] = lane_value(v_cq, l);
                 }
-                const float reach = lane_value(v_reach, t0 + 31 - (int)__builtin_clz(gc.live));     // of the last live channel
+                const float reach = lane_value(v_reach, t0);
                 Box bx;
                 if (!atom_box(gs, reach, a, ox, oy, oz, bx)) continue;
                 float sv[kChanGroup] = {0.0f, 0.0f, 0.0f, 0.0f};

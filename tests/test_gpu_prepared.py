@@ -89,6 +89,30 @@ def test_vector_types_forward_then_backward_on_one_workspace(mg):
     assert np.abs(gw_p.cpu().numpy() - rw).max() <= GRAD_RTOL * np.abs(rw).max()
 
 
+@pytest.mark.parametrize("T", [5, 9, 70])
+def test_radii_changed_in_place_after_the_tables_were_made(mg, T):
+    """Weights and radii are read again by the calls that take them: with the widest radius still that of the
+    tables, the order of the channels in them must not matter (the same radii, dealt out anew)."""
+    rng = np.random.default_rng(T)
+    B, N, D, res = 2, 80, 16, 0.5
+    dim = (D - 1) * res
+    coords = rng.uniform(-dim / 2 - 1, dim / 2 + 1, (B, N, 3)).astype(np.float32)
+    w = rng.standard_normal((B, N, T)).astype(np.float32)
+    radii = rng.uniform(0.7, 2.0, T).astype(np.float32)
+    G = rng.standard_normal((B, T, D, D, D)).astype(np.float32)
+    gm = mg.GridMaker(res, dim, radius_type_indexed=True)
+    ra = dev(radii)
+    ws = gm.mg_prepare(dev(coords), None, ra, T)
+    now = np.ascontiguousarray(np.roll(radii[::-1], 1))
+    ra.copy_(dev(now))
+    out = gm.mg_forward_vector_prepared(dev(w), ra, ws).cpu().numpy()
+    gc, gw = gm.mg_backward_vector_prepared(dev(w), ra, dev(G), ws)
+    assert np.abs(out - oracle.forward_vector(coords, w, now, res, dim)).max() <= GRID_TOL
+    wc, ww = oracle.backward_vector(coords, w, now, res, dim, G)
+    assert np.abs(gc.cpu().numpy() - wc).max() <= GRAD_RTOL * np.abs(wc).max()
+    assert np.abs(gw.cpu().numpy() - ww).max() <= GRAD_RTOL * np.abs(ww).max()
+
+
 def test_tables_of_another_shape_leave_the_outputs_untouched(mg):
     """The kernels of a *_prepared call compare the tag the tables carry with their own shape
     and return without writing when it differs (here: tables of B = 3 used with B = 2, tables
