@@ -638,11 +638,12 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
                 const int key = v[u] == 0 ? place(w[VECTOR ? u : 0], 0, pp, r) : -1;
                 own = key >= kA && key < kB && key != D + 2;
                 const unsigned long long culled = __ballot(key == D + 2);
-                int at = 0;
-                if (lane == 0 && culled) at = atomicAdd(&s_cnt[D + 2], (int)__builtin_popcountll(culled));
+                int base_c = 0;
+                if (lane == 0 && culled) base_c = atomicAdd(&s_cnt[D + 2], (int)__builtin_popcountll(culled));
+                base_c = bcast(base_c, 0);      // (here, where lane 0 is active: it need not be culled itself)
                 if (key == D + 2) {
                     if (last) {
-                        at = n - 1 - bcast(at, 0) - (int)__builtin_popcountll(culled & ((1ull << lane) - 1ull));
+                        const int at = n - 1 - base_c - (int)__builtin_popcountll(culled & ((1ull << lane) - 1ull));
                         ws.rec[(size_t)b * N + at] = make_float4(pp[0], pp[1], pp[2], 0.0f);
                         ws.idx[(size_t)b * N + at] = a;
                         ws.alive[(size_t)b * N + a] = 0;

@@ -71,3 +71,35 @@ def test_vector_types(mg, B, N, T, D, spread, crowd):
     gc, gw = gm.mg_backward_vector_prepared(dev(w), ra, dev(G), ws)
     assert np.abs(gc.cpu().numpy() - wc).max() <= GRAD_RTOL * max(np.abs(wc).max(), 1e-30)
     assert np.abs(gw.cpu().numpy() - ww).max() <= GRAD_RTOL * max(np.abs(ww).max(), 1e-30)
+
+
+@pytest.mark.parametrize("B,N,keep", [(1, 8200, 64), (2, 9001, 2), (1, 16500, 5)])
+def test_vector_types_culled_among_live(mg, B, N, keep):
+    """Culled atoms between live ones in every pattern of lanes (the first lane of a wavefront live, the rest
+    culled, and the other way round): each is recorded once, and its gradients are zeros."""
+    rng = np.random.default_rng(N)
+    T, D, res = 3, 10, 0.75
+    dim = (D - 1) * res
+    coords = rng.uniform(-dim / 2, dim / 2, (B, N, 3)).astype(np.float32)
+    a = np.arange(N)
+    out = (a % keep != 0) ^ ((a // 1024) % 2 == 1)
+    coords[:, out] += 40.0
+    natoms = np.array([N, N - 77][:B], np.int32)
+    w = (rng.random((B, N, T)) * 0.05).astype(np.float32)
+    radii = rng.uniform(0.6, 1.5, T).astype(np.float32)
+    G = rng.standard_normal((B, T, D, D, D)).astype(np.float32)
+    gm = mg.GridMaker(res, dim, radius_type_indexed=True)
+    co, ra, dn = dev(coords), dev(radii), dev(natoms)
+    ref = oracle.forward_vector(coords, w, radii, res, dim, natoms=natoms)
+    wc, ww = oracle.backward_vector(coords, w, radii, res, dim, G, natoms=natoms)
+    for _ in range(2):
+        ws = gm.mg_prepare(co, None, ra, T, natoms=dn)
+        got = gm.mg_forward_vector_prepared(dev(w), ra, ws).cpu().numpy()
+        assert np.abs(got - ref).max() <= grid_tol(ref)
+        gc = torch.full((B, N, 3), float("nan"), device="cuda")
+        gw = torch.full((B, N, T), float("nan"), device="cuda")
+        gm.mg_backward_vector_prepared(dev(w), ra, dev(G), ws, grad_coords=gc, grad_weights=gw)
+        gc, gw = gc.cpu().numpy(), gw.cpu().numpy()
+        assert np.abs(gc - wc).max() <= GRAD_RTOL * np.abs(wc).max()
+        assert np.abs(gw - ww).max() <= GRAD_RTOL * np.abs(ww).max()
+        assert not gc[:, out].any() and not gw[:, out].any()
