@@ -103,6 +103,13 @@ __device__ inline void grid_center(const Subgrids &sub, const Xform &X, int b, i
     }
 }
 
+// Planes on each side of its own that an atom reaches, plus one (past the grid's own planes all are alike: the
+// bound keeps the bin numbers made from it within the grid's for any radius).
+__device__ inline int planes_reached(const GridSpec &gs, float reach)
+{
+    return (int)fminf(ceilf(reach * gs.inv_res + 1.0e-3f * gs.res), (float)(gs.D + 2)) + 1;
+}
+
 // Vector types: the reach of the widest channel (the lanes of a wavefront read the radii together).
 __device__ inline float widest_reach(const GridSpec &gs, const Batch &bt)
 {
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(NT) void prep_example_kernel(GridSpec gs, Batch bt,
         const int tg = e / D, i = e - tg * D;
         // plane i is reached from bins [i - Rv, i + Rv + 1]
         const float rmax = __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
-        const int Rv = (int)ceilf(rmax * gs.inv_res + 1.0e-3f * gs.res) + 1;
+        const int Rv = planes_reached(gs, rmax);
         const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
         ws.range[((size_t)b * T + tg) * D + i] = make_int2(s_pos[tg * nb + lo], s_pos[tg * nb + hi + 1]);
     }
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(kExThreads) void prep_example_vector_kernel(GridSpe
     }
     const int total = s_part[NW];
     if (tid == 0) ws.meta[(size_t)b * bt.T] = make_int4(0, s_cnt[(D + 2) * NW], total, 0);
-    const int Rv = (int)ceilf(reach * gs.inv_res + 1.0e-3f * gs.res) + 1;
+    const int Rv = planes_reached(gs, reach);
     for (int i = tid; i < D; i += NT) {             // plane i is reached from bins [i - Rv, i + Rv + 1]
         const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
         ws.range[(size_t)b * bt.T * D + i] = make_int2(s_cnt[lo * NW], s_cnt[(hi + 1) * NW]);
@@ -769,7 +776,7 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
             const int tg = e / D, i = e - tg * D;
             // plane i is reached from bins [i - Rv, i + Rv + 1]
             const float rmax = VECTOR ? vec_reach : __int_as_float(s_rmax[tg]) * (gs.binary ? 1.0f : gs.c);
-            const int Rv = (int)ceilf(rmax * gs.inv_res + 1.0e-3f * gs.res) + 1;
+            const int Rv = planes_reached(gs, rmax);
             const int lo = max(0, i - Rv), hi = min(D + 1, i + Rv + 1);
             ws.range[((size_t)b * T + tA + tg) * D + i] =
                 make_int2(first + s_pos[tg * nb + lo], first + s_pos[tg * nb + hi + 1]);

@@ -103,3 +103,24 @@ def test_vector_types_culled_among_live(mg, B, N, keep):
         assert np.abs(gc - wc).max() <= GRAD_RTOL * np.abs(wc).max()
         assert np.abs(gw - ww).max() <= GRAD_RTOL * np.abs(ww).max()
         assert not gc[:, out].any() and not gw[:, out].any()
+
+
+@pytest.mark.parametrize("N", [2, 5000, 9000])      # one workgroup's kernels; shares
+@pytest.mark.parametrize("radius", [3e9, 1e15])
+def test_radii_of_more_steps_than_an_integer_holds(mg, N, radius):
+    """Every voxel is inside every atom: occupancy is 1, densities are sums of weights."""
+    rng = np.random.default_rng(N)
+    T, D, res = 2, 6, 0.5
+    coords = rng.uniform(-3, 3, (1, N, 3)).astype(np.float32)
+    types = np.ones((1, N), np.int32)
+    w = (rng.random((1, N, T)) * (20.0 / N)).astype(np.float32)
+    ra = torch.full((T,), radius, device="cuda")
+    gmb = mg.GridMaker(res, (D - 1) * res, radius_type_indexed=True, binary=True)
+    ws = gmb.mg_prepare(dev(coords), dev(types), ra, T)
+    occ = gmb.mg_forward_index_prepared(1, N, T, ws)
+    assert float(occ[:, 0].abs().max()) == 0.0 and float(occ[:, 1].min()) == 1.0
+    gm = mg.GridMaker(res, (D - 1) * res, radius_type_indexed=True)
+    ws = gm.mg_prepare(dev(coords), None, ra, T)
+    out = gm.mg_forward_vector_prepared(dev(w), ra, ws).cpu().numpy()
+    want = w.astype(np.float64).sum(axis=1)[:, :, None, None, None]
+    assert np.abs(out - want).max() <= grid_tol(want)
