@@ -562,6 +562,7 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
     static_assert(kSlotCap == 64 * 16, "one 16-byte store per lane clears the marks");
     reinterpret_cast<int4 *>(marks)[lane] = make_int4(0, 0, 0, 0);
     lds_sync();
+    __shared__ float s_rot[4][9];       // (vector types, one launch)
     float4 a, gc, Ra, Rb;       // record, grid centre, rotation (rows, 9 values)
     float Rc;
     int ai, t_rec;
@@ -601,9 +602,14 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
             return;
         }
         a = make_float4(pos[0], pos[1], pos[2], r);
-        Ra = make_float4((float)X.R[0], (float)X.R[1], (float)X.R[2], (float)X.R[3]);
-        Rb = make_float4((float)X.R[4], (float)X.R[5], (float)X.R[6], (float)X.R[7]);
-        Rc = (float)X.R[8];
+        if (VECTOR) {           // past the loop over the slots, which needs all registers (or it spills some)
+            if (lane == 0)
+                for (int m = 0; m < 9; ++m) s_rot[threadIdx.x >> 6][m] = (float)X.R[m];
+        } else {
+            Ra = make_float4((float)X.R[0], (float)X.R[1], (float)X.R[2], (float)X.R[3]);
+            Rb = make_float4((float)X.R[4], (float)X.R[5], (float)X.R[6], (float)X.R[7]);
+            Rc = (float)X.R[8];
+        }
     } else {
         // Everything the wavefront needs first is requested in one go (one trip to memory, not
         // four in a row): the group table's last entry, the record and its atom index (slot
@@ -636,9 +642,12 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
     }
     const size_t D3 = (size_t)D * D * D;
     const int bs = source_example(p.subgrids, b);          // types and weights are the source example's
-    const float ox = gc.x - gs.half;
-    const float oy = gc.y - gs.half;
-    const float oz = gc.z - gs.half;
+    float ox = gc.x - gs.half, oy = gc.y - gs.half, oz = gc.z - gs.half;
+    if (FUSED && VECTOR) {
+        ox = uniform(ox);
+        oy = uniform(oy);
+        oz = uniform(oz);
+    }
 
     float tx = 0.0f, ty = 0.0f, tz = 0.0f;          // gradient in the transformed frame
     if (!VECTOR) {
@@ -729,6 +738,13 @@ __global__ __launch_bounds__(256, VECTOR ? (sizeof(GT) == 8 ? 5 : 6) : 1) void b
         tx = __int_as_float(bcast(__float_as_int(t), 0));
         ty = __int_as_float(bcast(__float_as_int(t), 1));
         tz = __int_as_float(bcast(__float_as_int(t), 2));
+    }
+    if (FUSED && VECTOR) {
+        lds_sync();
+        const float *R = s_rot[threadIdx.x >> 6];
+        Ra = make_float4(R[0], R[1], R[2], R[3]);
+        Rb = make_float4(R[4], R[5], R[6], R[7]);
+        Rc = R[8];
     }
     if (lane == 0 && p.grad_coords) {
         float *o = p.grad_coords + ((size_t)b * N + ai) * 3;
