@@ -483,8 +483,11 @@ __global__ __launch_bounds__(kExThreads) void prep_example_vector_kernel(GridSpe
 // atoms are placed once, to count the other bins).
 // The share's atoms are listed in LDS on the way.  Only those are placed after that, twice (which costs
 // less than keeping their positions in registers): for the counts, and in order of bins for the
-// records.  A share of more than kOwnAtoms atoms goes through all atoms again instead for the counts and for
-// the places, and its list in bin order sits in the workspace (rchan, whose final contents are written last).
+// records.  A share of more than kOwnAtoms atoms (one type of a large receptor) goes through all atoms again for
+// the counts and leaves atom, key and place within the bin where its records will be (index types; vector types
+// go through all atoms once more for the places), and its list in bin order sits in the workspace (rchan, whose
+// final contents are written last): one example of 20000 atoms in two channels 71 us, 94 with a second pass over
+// all atoms for the places, and 89 with two such passes and no list before them.
 // Bound: trips to memory one after the other, and placing atoms in double precision.  Two examples of
 // 20000 atoms and 18 channels as eight subgrids each: 27 us, 42 when all passes went through all
 // atoms; one of 20000, 28 channels 17 / 31; 12000 in two channels 34 / 57; vector types, two of 20000 28 / 56.
@@ -570,9 +573,10 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
         }
         return (t - tA) * nb + bin;
     };
-    // body(atom, type, Raw) for every atom of the share.  Index types: the share's atoms of a round (8192)
-    // are gathered in LDS first, so that all lanes place atoms.
+    // body(atom, type, Raw, number) for every atom of the share.  Index types: the share's atoms of a round (8192)
+    // are gathered in LDS first, so that all lanes place atoms, and numbered; vector types: for all atoms.
     auto for_mine = [&](auto body) {
+        int done = 0;
         for (int base = 0; base < N; base += NT * U) {
             int v[U], found = 0;
 #pragma unroll
@@ -616,7 +620,8 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
                 if (own_a[u] >= 0) w[u] = fetch(own_a[u], t[u]);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (own_a[u] >= 0) body(own_a[u], t[u], w[u]);
+                if (own_a[u] >= 0) body(own_a[u], t[u], w[u], done + u * NT + tid);
+            done += found;
             if (!VECTOR) __syncthreads();       // s_mine is free again
         }
     };
@@ -677,7 +682,8 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     }
     __syncthreads();
     const int found = s_found;
-    const bool kept = found <= kOwnAtoms;       // (else, rarely, three passes over all atoms)
+    const bool kept = found <= kOwnAtoms;
+    int4 *listed = VECTOR ? nullptr : reinterpret_cast<int4 *>(ws.rec + (size_t)b * N + s_less);       // (a share that is not kept)
 
     // ---- 1. atoms per key ----
     constexpr int kPer = kOwnAtoms / NT;
@@ -713,10 +719,11 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     } else {
         for (int k = tid; k < K; k += NT) s_cnt[k] = 0;
         __syncthreads();
-        for_mine([&](int a, int t, const Raw &w) {
+        for_mine([&](int a, int t, const Raw &w, int at) {
             float pp[3], r;
             const int key = place(w, t, pp, r);
-            atomicAdd(&s_cnt[key], 1);
+            if (VECTOR) atomicAdd(&s_cnt[key], 1);
+            else listed[at] = make_int4(a, key, atomicAdd(&s_cnt[key], 1), 0);
             if (!VECTOR && r > 0.0f) atomicMax(&s_rmax[t - tA], __float_as_int(r));
             if (key >= kA && key < kB) ws.alive[(size_t)b * N + a] = r > 0.0f ? 1 : 0;
         });
@@ -760,8 +767,17 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
 #pragma unroll
         for (int u = 0; u < kPer; ++u)
             if (my_a[u] >= 0) s_own[s_pos[my_slot[u] >> 14] - own0 + (my_slot[u] & 16383)] = my_a[u];
+    } else if (!VECTOR) {
+        for (int base = tid; base < found; base += 4 * NT) {
+            int4 e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = base + u * NT < found ? listed[base + u * NT] : make_int4(-1, 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (e[u].x >= 0) order[s_pos[e[u].y] + e[u].z] = e[u].x;
+        }
     } else {
-        for_mine([&](int a, int t, const Raw &w) {
+        for_mine([&](int a, int t, const Raw &w, int) {
             float pp[3], r;
             const int key = place(w, t, pp, r);
             if (key >= kA && key < kB) order[s_pos[key] + atomicAdd(&s_cnt[key], 1)] = a;

@@ -46,6 +46,27 @@ def test_index_types(mg, B, N, T, D, spread, skew):
     assert np.abs(got - want).max() <= GRAD_RTOL * np.abs(want).max()
 
 
+@pytest.mark.parametrize("main", [0, 4, 8])         # (64 examples: shares of three types each)
+def test_index_shares_longer_than_the_list(mg, main):
+    """More than 12288 atoms of one type beside two others in a share, with smaller and larger types in other shares."""
+    B, N, T, D = 64, 14000, 9, 8
+    rng, dim, coords, types, radii, pose, dpose = _inputs(B, N, T, D, 3.0, 0.0, main)
+    types[rng.random((B, N)) < 0.96] = main
+    types[:, ::1000] = -1 + (T + 1) * (np.arange(0, N, 1000) // 1000 % 2)       # no type's
+    co, ty, ra = dev(coords), dev(types), dev(radii)
+    gm = mg.GridMaker(0.75, dim, radius_type_indexed=True)
+    ref = oracle.forward_index(coords, types, radii, T, 0.75, dim, **pose)
+    outs = [gm.mg_forward_index(co, ty, ra, T, **dpose).cpu().numpy() for _ in range(2)]
+    assert np.abs(outs[0] - ref).max() <= grid_tol(ref)
+    assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+    G = rng.standard_normal(ref.shape).astype(np.float32)
+    want = oracle.backward_index(coords, types, radii, T, 0.75, dim, G, **pose)
+    ws = gm.mg_prepare(co, ty, ra, T, **dpose)
+    got = torch.full((B, N, 3), float("nan"), device="cuda")
+    gm.mg_backward_index_prepared(B, N, T, dev(G), ws, grad_coords=got)
+    assert np.abs(got.cpu().numpy() - want).max() <= GRAD_RTOL * np.abs(want).max()
+
+
 @pytest.mark.parametrize("B,N,T,D,spread,crowd", [
     (1, 1, 2, 9, 0.0, 0), (2, 63, 3, 9, 1.0, 0), (3, 2048, 5, 14, 2.0, 0), (2, 2049, 4, 14, 2.0, 0), (1, 4097, 3, 13, 4.0, 3000),
     (1, 8192, 70, 8, 6.0, 0), (1, 8193, 2, 13, 10.0, 0), (1, 20011, 3, 12, 2.0, 9000), (1, 500, 2, 130, 0.5, 0),
@@ -103,6 +124,44 @@ def test_vector_types_culled_among_live(mg, B, N, keep):
         assert np.abs(gc - wc).max() <= GRAD_RTOL * np.abs(wc).max()
         assert np.abs(gw - ww).max() <= GRAD_RTOL * np.abs(ww).max()
         assert not gc[:, out].any() and not gw[:, out].any()
+
+
+@pytest.mark.parametrize("B,N,D,planes,crowd", [
+    (1, 20011, 12, (4, 5), 13000),      # one bin, put in order by one wavefront
+    (64, 16000, 24, (6, 13), 13900),    # the seven bins of a share, put in order by counting
+    (64, 16000, 24, (20, 24), 13900),   # the share that also records the culled atoms
+])
+def test_vector_shares_longer_than_the_list(mg, B, N, D, planes, crowd):
+    """More than 12288 atoms in the planes of one workgroup, culled ones among them: counted and placed in passes
+    over all atoms.  (64 examples make shares of seven bins; all but the first two are short.)"""
+    rng = np.random.default_rng(crowd + D)
+    T, res = 2, 0.75
+    dim = (D - 1) * res
+    coords = rng.uniform(-dim / 2, dim / 2, (B, N, 3)).astype(np.float32)
+    coords[0, :, 0] = rng.uniform(-dim / 2 - 30.0, dim / 2 + 30.0, N)
+    at = rng.permutation(N)[:crowd]
+    lo, hi = planes
+    coords[0, at, 0] = ((lo + np.arange(crowd) % (hi - lo)) + rng.uniform(0.1, 0.8, crowd)) * res - dim / 2
+    if B > 1:
+        coords[1] = coords[0, ::-1]
+    natoms = np.full(B, 9, np.int32)
+    natoms[:2] = N
+    w = (rng.random((B, N, T)) * (60.0 / N)).astype(np.float32)
+    radii = rng.uniform(0.6, 1.5, T).astype(np.float32)
+    G = rng.standard_normal((B, T, D, D, D)).astype(np.float32)
+    ref = oracle.forward_vector(coords, w, radii, res, dim, natoms=natoms)
+    wc, ww = oracle.backward_vector(coords, w, radii, res, dim, G, natoms=natoms)
+    co, ra, dn, dw = dev(coords), dev(radii), dev(natoms), dev(w)
+    gm = mg.GridMaker(res, dim, radius_type_indexed=True)
+    ws = gm.mg_prepare(co, None, ra, T, natoms=dn)
+    outs = [gm.mg_forward_vector_prepared(dw, ra, ws).cpu().numpy(), gm.mg_forward_vector(co, dw, ra, natoms=dn).cpu().numpy()]
+    assert np.abs(outs[0] - ref).max() <= grid_tol(ref)
+    assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
+    gc = torch.full((B, N, 3), float("nan"), device="cuda")
+    gw = torch.full((B, N, T), float("nan"), device="cuda")
+    gm.mg_backward_vector_prepared(dw, ra, dev(G), ws, grad_coords=gc, grad_weights=gw)
+    assert np.abs(gc.cpu().numpy() - wc).max() <= GRAD_RTOL * np.abs(wc).max()
+    assert np.abs(gw.cpu().numpy() - ww).max() <= GRAD_RTOL * np.abs(ww).max()
 
 
 @pytest.mark.parametrize("N", [2, 5000, 9000])      # one workgroup's kernels; shares
