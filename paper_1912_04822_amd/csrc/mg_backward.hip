@@ -780,21 +780,30 @@ hipError_t launch_sum_subgrids(int subgrid_count, int B_source, size_t per_examp
 // Few atoms: no prep kernel, every atom's wavefront places its atom itself, in the caller's order.
 // What is lost is the order by channel and plane (neighbouring wavefronts then share fewer lines of
 // the gradient grid) and, per atom, the transform worked out by a whole wavefront; what is saved is
-// the prep kernel's 10 us and more.  Whole calls, one launch / prep kernel and backward kernel:
-// 2040 atoms and 28 channels of 48^3 per example, us: index types 10.4 / 17.1 for 1 example, 34.7 / 38.2
-// for 16, 47.1 / 50.2 for 24, 61.5 / 61.3 for 32, 92.1 / 87.7 for 50.
+// the prep kernel's 10 us and the gap behind it.  Whole calls, one launch / prep kernel and backward kernel, us;
+// atoms at 0.076 per cubic Angstrom about the grid's centre.
+// Index types, 2040 atoms and 28 channels of 48^3 per example: 9.4 / 14.7 for 1 example, 33.7 / 35.4
+// for 16, 46.2 / 46.4 for 24, 58.5 / 58.3 for 32, 90.9 / 85.0 for 50.
 // Vector types read every channel for every atom.  Four channels of a grid of 48^3 are 1.8 MB and stay in
 // an XCD's L2 whatever the order of the atoms; those of larger grids stay there only in the order of the
-// tables, so the line lies at a product of atoms, channels and points.  2040 atoms that fill the grid, us:
-// 28 x 48^3 48 / 63, two examples 81 / 86, three 135 / 111; 12 x 64^3 42 / 52, 28 x 64^3 91 / 89; 12 x 80^3
-// 80 / 75; 4 x 96^3 60 / 55, 28 x 96^3 329 / 205.  One example of more than 4096 atoms is sorted by one
-// workgroup in 50 us and more, so the line lies further out, and what counts is the atoms that such a
-// grid can hold (proteins: 0.08 per cubic Angstrom; 2 A for their reach): 8160 atoms, 28 x 96^3 at 0.25 A
-// (1750 in reach) 372 / 658, 28 x 64^3 at 0.5 A 158 / 178, 12 x 96^3 at 0.5 A 158 / 124.
+// tables, so the line lies at a product of atoms, channels and points.  2040 atoms, 28 x 48^3: one example 41.2 / 46.3,
+// two 66.9 / 67.1, three 104 / 89; 12 x 64^3 25.8 / 29.5, two 46.8 / 41.7; 28 x 64^3 51.9 / 48.5; 12 x 96^3 33.9 / 31.9;
+// 4 x 96^3 15.2 / 19.3, two 22.3 / 25.3; 28 x 96^3 at 0.25 A 228 / 191.
+// One example of more than 4096 atoms: the tables list the atoms out of the grid's reach last and each XCD takes an
+// eighth of the records, so that with a share f of the atoms within reach (what such a grid can hold: 0.08 atoms per
+// cubic Angstrom, 2 A for their reach) as large a share of the XCDs works; and spacings beyond 0.5 A have fewer rows in a
+// sphere.  Reads (atoms within reach x channels x points) x f^2 x min(1, (0.5 / spacing)^2) x sqrt(channels) tell the
+// two apart, 1e9: 40 x 96^3 at 0.25 A of 5000 atoms (49) 422 / 671, 28 x 96^3 of 8000 (11) 356 / 585, 28 x 64^3 of 8000 (32)
+// 121 / 125, 5 x 80^3 of 8000 (28) 41 / 51, 5 x 96^3 of 5000 (49) 40 / 41, 28 x 48^3 at 1 A of 8000 (33) 57 / 67, 40 x 48^3 (56)
+// 81 / 88, but 28 x 64^3 of 6000 (56) 117 / 100; of 4500 (100) 107 / 88; 20 x 72^3 of 8000 (70) 117 / 102; 28 x 64^3 at 1 A of
+// 8000 (78) 78 / 70; 28 x 80^3 at 0.375 A of 5000 (94) 196 / 158; 8 x 96^3 of 5000 (100) 60 / 47; 12 x 96^3 of 6000 (221) 109 / 65.
+// Up to four channels are one pass over each atom's rows: 2 x 128^3 of 8000 24 / 35, 3 x 120^3 33 / 38, 4 x 96^3 46 / 47,
+// 4 x 112^3 59 / 50.
 constexpr long long kSingleAtoms = 49152;           // index types
 constexpr long long kSingleAtomsVector = 8192;      // vector types, and ...
 constexpr double kSingleReads = 1.5e10;             // atoms x channels x points
-constexpr double kSingleReadsLong = 6.5e10;         // ... of one example of more than 4096, counting those it can hold
+constexpr double kSingleReadsLong = 5.7e10;         // ... of one example of more than 4096, weighted as above
+constexpr double kSingleReadsGroup = 6.5e10;        // ... and of no more than four channels: atoms within reach
 bool backward_takes_single_launch(const GridSpec &gs, const Batch &bt)
 {
     if (bt.sub.count != 1) return false;
@@ -803,8 +812,10 @@ bool backward_takes_single_launch(const GridSpec &gs, const Batch &bt)
     if (atoms > kSingleAtomsVector) return false;
     const double points = (double)bt.T * gs.D * gs.D * gs.D;
     if (bt.B > 1 || bt.N <= 4096) return atoms * points <= kSingleReads;
-    const double side = (double)gs.D * gs.res + 4.0;
-    return std::fmin((double)atoms, 0.08 * side * side * side) * points <= kSingleReadsLong;
+    const double side = (double)gs.D * gs.res + 4.0, held = std::fmin((double)atoms, 0.08 * side * side * side);
+    if (bt.T <= kChanGroup) return held * points <= kSingleReadsGroup;
+    const double f = held / (double)atoms, rows = std::fmin(1.0, 0.25 / ((double)gs.res * gs.res));
+    return held * points * f * f * rows * std::sqrt((double)bt.T) <= kSingleReadsLong;
 }
 
 hipError_t launch_backward(const GridSpec &gs, const Batch &bt, const Workspace &ws,

@@ -34,6 +34,10 @@ def route(mg, call, B, N, T, D, res):
     ("backward_vector", 1, 2040, 8, 96, 0.5, True), ("backward_vector", 1, 2040, 9, 96, 0.5, False),
     ("backward_vector", 1, 4096, 4, 100, 0.5, False), ("backward_vector", 1, 4097, 4, 100, 0.5, True),
     ("backward_vector", 1, 8192, 4, 128, 0.5, False), ("backward_vector", 1, 8192, 4, 128, 0.25, True),
+    ("backward_vector", 1, 6000, 12, 64, 0.5, True), ("backward_vector", 1, 4500, 28, 64, 0.5, False),
+    ("backward_vector", 1, 8000, 28, 56, 1.0, True), ("backward_vector", 1, 8000, 28, 64, 1.0, False),
+    ("backward_vector", 1, 5000, 20, 96, 0.25, True), ("backward_vector", 1, 5000, 5, 96, 0.5, True),
+    ("backward_vector", 1, 5000, 8, 96, 0.5, False),
     ("backward_vector", 2, 4096, 1, 12, 0.5, True), ("backward_vector", 2, 4097, 1, 12, 0.5, False),
     ("forward", 1, 2048, 28, 48, 0.5, True), ("forward", 1, 2049, 28, 48, 0.5, False),
     ("forward", 4, 2040, 28, 48, 0.5, False), ("forward", 100, 65, 8, 16, 1.0, True),
