@@ -42,10 +42,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0           # MI355X published HBM3E peak
-# 256 CUs x 4 SIMDs x 2.4 GHz, one 64-lane vector instruction per SIMD every 4 cycles, packed
-# FP32 switched off: 1024 x 2.4e9 / 4 x 64 lanes = 39.3e12 lane-instructions per second (the data
-# sheet's 157.3 TFLOP/s counts packed FMAs: two results per lane, two flops each)
-VALU_PEAK_TLANE = 39.3
+# 256 CUs x 4 SIMDs x 2.4 GHz x 64 lanes: lane-cycles per second, in units of 1e12.  An instruction takes a SIMD
+# several cycles (measured: floats and integer adds 2.3; maxima, comparisons, selects, lane exchanges 4.4 to 4.8;
+# roots and exponentials 8.5), so a kernel's limit is this over the mean of its own mix
+VALU_TLANE_CYCLES = 157.3
 SETTLE_GPU_MS = 30.0
 
 
@@ -159,16 +159,17 @@ def hbm_roofline(nbytes, kernel_ms, what):
             "frac": gbs / HBM_PEAK_GBS, "algorithmic_bytes": int(nbytes), "bytes_are": what}
 
 
-def alu_roofline(valu_key, kernel_ms):
-    insts, src = stored(valu_key)
-    if insts is None:
-        return {"bound": "alu", "achieved": None, "peak": VALU_PEAK_TLANE,
+def alu_roofline(kernel, kernel_ms):
+    insts, src = stored(kernel + "_valu_insts_per_launch")
+    cycles, _ = stored(kernel + "_issue_cycles_per_inst")
+    if insts is None or cycles is None:
+        return {"bound": "alu", "achieved": None, "peak": None,
                 "unit": "T lane-instructions/s", "frac": None}
-    rate = insts * 64 / (kernel_ms * 1e-3) / 1e12
-    return {"bound": "alu", "achieved": rate, "peak": VALU_PEAK_TLANE,
-            "unit": "T lane-instructions/s", "frac": rate / VALU_PEAK_TLANE,
-            "valu_insts_per_launch": insts,
-            "valu_insts_source": "%s (SQ_INSTS_VALU, stored from that profile, not measured in this run)" % src}
+    rate, peak = insts * 64 / (kernel_ms * 1e-3) / 1e12, VALU_TLANE_CYCLES / cycles
+    return {"bound": "alu", "achieved": rate, "peak": peak,
+            "unit": "T lane-instructions/s", "frac": rate / peak,
+            "valu_insts_per_launch": insts, "issue_cycles_per_inst": cycles,
+            "valu_insts_source": "%s (SQ_INSTS_VALU and the mix of the main loop, stored from that profile, not measured in this run)" % src}
 
 
 def main():
@@ -345,7 +346,7 @@ def main():
             coords, weights, radii, centers=centers, quats=quats, translations=trans, out=out,
             workspace=ws), n_slow)
         r["grids_per_s"] = w.B / (r["ms_per_call"] * 1e-3)
-        r["roofline"] = alu_roofline("forward_vector_valu_insts_per_launch", r["kernel_ms_avg"])
+        r["roofline"] = alu_roofline("forward_vector", r["kernel_ms_avg"])
         r["hbm_frac"] = w.out_bytes / (r["kernel_ms_avg"] * 1e-3) / 1e9 / HBM_PEAK_GBS
         rows["forward_vector"] = r
         distinct_vector = int(torch.count_nonzero(out))
@@ -389,7 +390,7 @@ def main():
             ev.close()
             return float(np.mean(k)), float(np.min(k))
 
-        def bwd_row(name, fn, steps, distinct, fetch_key, valu_key):
+        def bwd_row(name, fn, steps, distinct, fetch_key):
             r = row(fn, steps)
             warm = r["kernel_ms_avg"]
             k, kmin = kernel_after_forward(fn, min(steps, 30))
@@ -429,19 +430,19 @@ def main():
                              % lsrc) if lines is not None else
                             "the bytes the kernel fetches (see traffic): its distinct lines were not counted"}
             r["roofline"]["stream_whole_grid_frac"] = w.out_bytes / (kc * 1e-3) / 1e9 / HBM_PEAK_GBS
-            r["alu"] = alu_roofline(valu_key, warm)
+            r["alu"] = alu_roofline(name, warm)
             rows[name] = r
             return r
 
         bwd_row("backward_index", lambda: gm.mg_backward_index(
             coords, types, radii, w.T, G, centers=centers, quats=quats, translations=trans,
             grad_coords=gc, workspace=ws), n_fast, distinct_index,
-            "backward_index_fetch_bytes_per_launch", "backward_index_valu_insts_per_launch")
+            "backward_index_fetch_bytes_per_launch")
         gw = torch.empty((w.B, w.N, w.T), dtype=torch.float32, device="cuda")
         bwd_row("backward_vector", lambda: gm.mg_backward_vector(
             coords, weights, radii, G, centers=centers, quats=quats, translations=trans,
             grad_coords=gc, grad_weights=gw, workspace=ws), n_slow, distinct_vector,
-            "backward_vector_fetch_bytes_per_launch", "backward_vector_valu_insts_per_launch")
+            "backward_vector_fetch_bytes_per_launch")
 
         # forward + backward of one training step on the same inputs
         def train_step():

@@ -25,9 +25,9 @@
 // the lanes numbers the live slots, and slot s finds its row through a byte
 // array in LDS (the first slot of each lane's rows is marked with the lane, a
 // running maximum over the slots gives the owner) and one register exchange.
-// Index types are bound by vector instruction issue (50 x 2040 atoms, 28 x 48^3: three quarters of
-// the time; a third of the instructions the density, the rest finding rows and slots) and by the arrival of the
-// scattered lines (376 MB of 128-byte lines from HBM, 5.2 TB/s).  The three partial sums
+// Index types are bound by the arrival of the scattered lines (50 x 2040 atoms, 28 x 48^3: 372 MB of 128-byte
+// lines from HBM, 5.4 TB/s; wavefronts wait 59 % of their time) and by vector instruction issue (0.049 of
+// 0.069 ms; a third of the instructions the density, the rest finding rows and slots).  The three partial sums
 // are reduced across the wavefront together, in a fixed order (wave_sum4; with the slope as a
 // product instead of a select 76 instead of 78.6 us a call).  Records are grouped by
 // channel (and, within a channel, by x-plane), so neighbouring wavefronts read
@@ -131,15 +131,15 @@ typedef float Float4E __attribute__((ext_vector_type(4), aligned(4)));
 typedef double Double2E __attribute__((ext_vector_type(2), aligned(8)));
 
 // STREAM: the loads carry the non-temporal hint, so the lines they bring in do not settle in the
-// memory-side cache.  The index-type kernel reads each line of the gradient grid once (its reuse
-// is between neighbouring wavefronts, within microseconds, in L2), and the grid usually arrives
+// memory-side cache.  The index-type kernel's reuse of a line is between neighbouring wavefronts,
+// within microseconds, in L2 (1.38 reads from HBM per line), and the grid usually arrives
 // behind hundreds of MB that an earlier kernel has just written and that still sit dirty in
 // that cache: lines that settle there push those out, and the reads then wait behind the
-// write-backs.  Measured on the 48^3 batch: 74 against 100 us right after a forward call, 74
-// against 72 us after a read-only pass over another buffer, 71 against 62 us in a loop of
-// nothing but backward calls (where the lines of the call before would otherwise still be
-// cached).  The vector-typed kernel visits every line once per group of channels and atoms far
-// apart in time share lines: with the hint it took 1.55 instead of 0.98 ms, so it goes without.
+// write-backs.  Kernel on the 48^3 batch, with / without the hint: 70 / 100 us right after a forward call, 71 / 72
+// after a read-only pass over another buffer, 68 / 62 in a loop of nothing but backward calls (where the
+// lines of the call before would otherwise still be cached); without: as measured with an earlier body.
+// The vector-typed kernel visits every line once per group of channels and atoms far apart in time share
+// lines: 1.9 ms with the hint, 0.76 without.
 template <bool ALIGNED, bool STREAM, typename GT>
 __device__ inline void load_slot(const BwdParams &p, const GT *Gc, unsigned row_off, int k4,
                                  float ux, float uy, SlotData &d)
@@ -331,11 +331,12 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
 // kept by the lanes of their channels, so that an atom's weight gradients leave in one store.  Distances
 // are in Angstrom for all groups.  50 x 2040 atoms, 28 x 48^3: 778 instead of 907 us a call; 8 x 12 channels
 // 87 / 95; 2 x 100 channels of 32^3 126 / 165; few channels alike.
-// Bound by vector instruction issue and, as close, by the lines that the L2s deliver: the loads alone,
-// 128-byte lines for every 26 bytes of a chord, take 740 us (26 TB/s).
+// Bound by the lines that the L2s deliver, 128 bytes for every 26 of a chord (1.39e8 of them, 17.8 GB a launch,
+// 23.3 TB/s: the loads alone take 740 us; the L1s wait for L2 in two thirds of the kernel's 760 us) and by vector
+// instruction issue (0.55 of the 0.76 ms; wavefronts wait 29 % of their time for memory and 44 % for their turn to issue).
 // Measured and not kept: the slots of an atom listed once in LDS for all its channels, in shells of the
 // row's distance, so that rounds of far slots take the tail's half of the density only: 33 % fewer
-// loads issued and 20 % fewer instructions, and no faster (792 us; 0.25 A: 332 against 256; only 24^3
+// load instructions and 20 % fewer vector instructions, and no faster (792 us a call, lines and waits not counted; 0.25 A: 332 against 256; only 24^3
 // at 1 A gains, 225 against 255).
 // ---------------------------------------------------------------------------
 constexpr int kChanGroup = 4;

@@ -927,12 +927,13 @@ __global__ __launch_bounds__(64 * NW) void forward_kernel(FwdParams p)
 // error of weights of one and more 2.5 times as large (2.1e-7 -> 5.1e-7).
 // Bound by vector instruction issue: 38 instructions per step of 64 chords and four channels (some 137 cycles: 24
 // of them at 2.3, nine at 4.4, the five roots and exponentials at 8.5), with 54 % of the lanes inside the
-// sphere; 501 us a call on 50 x 2040 atoms, 28 x 48^3.  Measured and slower: chords cut into slots of four voxels and
+// sphere; issue is 0.45 of the kernel's 0.51 ms on 50 x 2040 atoms, 28 x 48^3.  Measured and slower, us a call against 501: chords cut into slots of four voxels and
 // queued in LDS (7 % fewer instructions, 12 instead of 16 wavefronts per CU: 612 us); tasks in order of the
 // row's distance from the atom (523 us); tile rows padded in LDS (half the bank conflicts, 509 us); no chords at
 // all, a voxel per lane in bricks of 4 x 4 x 4 that visit the atoms in reach one after the other, sums in
 // doubles, far visits with the tail's half of the density only (541 us: 30 % of the lanes are inside, a
-// visit of seven channels takes 290 cycles, 145 in the tail).
+// visit of seven channels takes 290 cycles, 145 in the tail).  A clamped multiply in place of a med3 was 1 %
+// faster, for one rounding more, and is not taken.
 // ---------------------------------------------------------------------------
 constexpr int kVecGroup = 4;
 
@@ -1472,14 +1473,17 @@ static hipError_t launch_forward_vector(const GridSpec &gs, const Batch &bt, con
 //     Tiles of about two x-planes, so that the atoms found need one round: 1024 (two wavefronts)
 //     below 37 points a side, else 4096 (four); 2048 where that leaves less than three workgroups
 //     per CU and a tile more than one plane.
-//     Listing and placing the atoms per tile costs 7 us per 3.1 M voxels at 2040 atoms against the
-//     10 us and more of the prep kernel: up to 8 M voxels, or 4096 of the small tiles (tiles, not
+//     Listing and placing the atoms per tile costs 3.5 us per 3.1 M voxels at 2040 atoms against the
+//     10 us of the prep kernel: up to 8 M voxels, or 4096 of the small tiles (tiles, not
 //     voxels: a channel of a few points a side is a tile all the same).
-// Whole calls, one launch / prep kernel and tables, us: 100 atoms, 4 x 24^3: 8.7 / 15 (one wavefront
-// that looks at all atoms: 13); 2040 atoms, 28 x 48^3: 11.9 / 17.7, 14 x 48^3 9.1 / 17.4, 4 x 48^3 13 / 30,
-// 1 x 48^3 20 / 44, 1 x 24^3 at 1 A 45 / 65; three of 24 x 48^3 18.2 / 22.9; 14 x 64^3 11.9 / 18.8; 20 x 28 x
-// 16^3 12.8 / 17.6, 50 x 28 x 12^3 19.8 / 20.3, 100 x 8 x 16^3 28.5 / 32, 500 x 14 x 8^3 48 / 35; 2000 x 200
-// atoms, 12 x 5^3 133 / 70.
+// Whole calls, one launch / prep kernel and tables, us, atoms at 0.076 per cubic Angstrom: 100 atoms, 4 x 24^3: 9.1 / 13.6;
+// 2040 atoms, 28 x 48^3: 12.0 / 15.7, 14 x 48^3 9.2 / 15.7, 4 x 48^3 13 / 26, 1 x 48^3 20 / 39, 1 x 24^3 at 1 A 45 / 59;
+// two of 28 x 48^3 14.7 / 18.7, three of 24 x 48^3 (8 M voxels) 17.4 / 21.1, four of 28 x 48^3 22.0 / 23.4; 14 x 64^3 11.6 / 17.2.
+// Small tiles: 2000 of them are quicker in one launch (62 x 8 x 16^3 of 500 atoms 14.8 / 17.1, 10 x 14 x 24^3 11.7 / 13.7,
+// 4 x 14 x 32^3 9.7 / 11.8; but 71 x 28 x 8^3 13.2 / 14.7, 142 x 14 x 8^3 of 2040 20.0 / 17.9), 3000 alike (93 x 8 x 16^3 of 500
+// 19.5 / 19.1, 15 x 14 x 24^3 15.6 / 15.2, 6 x 14 x 32^3 12.3 / 12.4; 53 x 28 x 12^3 of 2040 21.2 / 22.8), 4000 slower
+// (125 x 8 x 16^3 of 500 22.1 / 20.5, 20 x 14 x 24^3 18.6 / 16.3, 8 x 14 x 32^3 14.9 / 13.8; 71 x 28 x 12^3 of 2040 24.7 / 23.3).  The
+// line was drawn when a sort was slower; it would lie at 3000 now.
 constexpr int kSmallTotal = 2048;
 static int single_launch_tile(const GridSpec &gs, const Batch &bt, bool out_is_double)
 {
