@@ -978,9 +978,10 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     L.N = bt.N;
     const long long K = (long long)L.Tg * (gs.D + 3);
     // Index types of more than 4096 atoms: shares of the types for several workgroups while there are few
-    // examples, else one workgroup per example.  Kernel, us, shares / one workgroup: 16 x 8000 atoms, 28 channels 13 / 20,
-    // 1 x 8000 11 / 18, 32 x 8000 16 / 19, 48 x 8000 26 / 20, 64 x 8000 in eight channels 24 / 18, 12 x 8000 in one 29 / 37;
-    // below 4096 atoms alike for few examples (20 x 3000 11 / 11), worse for many (50 x 2040 18 / 10).
+    // examples, else one workgroup per example.  Kernel, us, shares / one workgroup: 16 x 8192 atoms, 28 channels 13.5 / 19.1,
+    // 1 x 8192 11.3 / 18.1, 32 x 8192 17.0 / 19.6, 48 x 8000 26 / 20, 64 x 8000 in eight channels 24 / 18, 12 x 8192 in two 34 / 49;
+    // 16 x 4100 11.5 / 12.7, 32 x 4100 13.5 / 13.1; below 4096 atoms alike for few examples (20 x 3000 11 / 11), worse for many
+    // (50 x 2040 18 / 10).
     const bool shared = bt.N > 4096 && bt.B <= 32;
     const bool fits = !vec && !shared && bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
     L.K = fits ? (int)K : 0;
@@ -1009,9 +1010,16 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
             hipLaunchKernelGGL((prep_example_kernel<8, kExThreads>), grd, dim3(kExThreads), lds_bytes, stream, gs, bt, ws, tag, stop);
         return hipGetLastError();
     }
-    // shares per example: enough workgroups for the chip, at most kRangeMaxKeys keys each
+    // Shares per example, at most kRangeMaxKeys keys each: as many workgroups as the chip holds at a time (one per
+    // CU).  A few more would run alone after the others: kernel, us, 256 / B shares at most / rounded up: index types, 28 examples of
+    // 4100 atoms and 28 channels 13.4 / 20.6 (one workgroup per example 13.1), 20 of 5000 and 25 channels 12.3 / 17.2, 40 of
+    // 9000 and 28 channels 22.3 / 30.1; vector types, 20 of 20000 31.6 / 54.4, 100 of 9000 27.0 / 43.6.  Where that leaves index types
+    // fewer than five shares (more than 51 examples) one is longer than the list, as types are uneven, and a
+    // second wave costs less: 60 of 20000 atoms, five channels 85.9 / 58.5, 86 of 9000, 28 channels 42.5 / 33.6.
     const int nb = gs.D + 3, units = vec ? nb : bt.T;
-    const int want = std::max(1, std::min(units, (256 + bt.B - 1) / bt.B));
+    int want = 256 / bt.B;
+    if (!vec && want < 5) want = (256 + bt.B - 1) / bt.B;
+    want = std::max(1, std::min(units, want));
     int per = (units + want - 1) / want;
     if (!vec) per = std::min(per, std::max(1, kRangeMaxKeys / nb));
     const int shares = (units + per - 1) / per;
