@@ -510,7 +510,7 @@ __global__ __launch_bounds__(kRangeThreads) void prep_range_kernel(GridSpec gs, 
     __shared__ int s_own[kOwnAtoms];            // the share's atoms, later in order of bins
     unsigned short *s_mine = reinterpret_cast<unsigned short *>(s_own);        // ... of a round
     static_assert(kOwnAtoms * sizeof(int) >= NT * U * sizeof(unsigned short), "a round's atoms");
-    const int p = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bs = source_example(bt.sub.count, b);       // whose atoms and pose this (virtual) example reads
     const int N = bt.N, T = bt.T, D = gs.D, nb = D + 3;   // bin D+2 holds the culled atoms
     if (MG_STOP_IS(stop, 1)) return;
@@ -1012,10 +1012,13 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     }
     // Shares per example, at most kRangeMaxKeys keys each: as many workgroups as the chip holds at a time (one per
     // CU).  A few more would run alone after the others: kernel, us, 256 / B shares at most / rounded up: index types, 28 examples of
-    // 4100 atoms and 28 channels 13.4 / 20.6 (one workgroup per example 13.1), 20 of 5000 and 25 channels 12.3 / 17.2, 40 of
-    // 9000 and 28 channels 22.3 / 30.1; vector types, 20 of 20000 31.6 / 54.4, 100 of 9000 27.0 / 43.6.  Where that leaves index types
+    // 4100 atoms and 28 channels 14.1 / 15.9, 20 of 5000 and 25 channels 13.8 / 15.2; vector types, 20 of 20000 32.3 / 53.6,
+    // 100 of 9000 28.1 / 42.7 (but index types, 40 of 9000 and 28 channels 21.8 / 20.8).  Where that leaves index types
     // fewer than five shares (more than 51 examples) one is longer than the list, as types are uneven, and a
-    // second wave costs less: 60 of 20000 atoms, five channels 85.9 / 58.5, 86 of 9000, 28 channels 42.5 / 33.6.
+    // second wave costs less: 60 of 20000 atoms, five channels 85.5 / 47.9, 86 of 9000, 28 channels 37.2 / 32.9.
+    // The grid runs over the examples first: the XCDs take workgroups in turn, and with the shares first the longest
+    // share of every example lay on the same ones (32 examples of 16000 atoms, all in one of two channels, 96 points a side, 129 us,
+    // 156 with the shares first; 24 of 20000 147 / 173; 70 of 20000 and 18 channels 52 / 104).
     const int nb = gs.D + 3, units = vec ? nb : bt.T;
     int want = 256 / bt.B;
     if (!vec && want < 5) want = (256 + bt.B - 1) / bt.B;
@@ -1025,7 +1028,7 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     const int shares = (units + per - 1) / per;
     const int keys = vec ? nb : per * nb;
     const size_t lds = (size_t)(2 * keys + 1 + (vec ? 1 : per)) * sizeof(int);
-    const dim3 grd(shares, bt.B), blk(kRangeThreads);
+    const dim3 grd(bt.B, shares), blk(kRangeThreads);       // (at most 65535 types)
     if (vec) hipLaunchKernelGGL(prep_range_kernel<true>, grd, blk, lds, stream, gs, bt, ws, tag, stop, per, keys);
     else hipLaunchKernelGGL(prep_range_kernel<false>, grd, blk, lds, stream, gs, bt, ws, tag, stop, per, keys);
     return hipGetLastError();

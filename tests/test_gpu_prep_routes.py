@@ -28,6 +28,7 @@ def _inputs(B, N, T, D, spread, skew, seed):
 @pytest.mark.parametrize("B,N,T,D,spread,skew", [
     (2, 4097, 3, 16, 2.0, 0.0), (1, 8192, 5, 16, 20.0, 0.0), (33, 4097, 2, 8, 3.0, 0.0), (28, 4200, 28, 6, 3.0, 0.0), (60, 8300, 7, 6, 3.0, 0.3),
     (1, 12288, 1, 16, 6.0, 0.0), (1, 12289, 1, 16, 6.0, 0.0), (1, 14000, 9, 12, 8.0, 0.95), (2, 9000, 4, 70, 1.0, 0.5),
+    (9, 8300, 2, 6, 3.0, 1.0),      # nine examples of two shares, one of them without atoms
 ])
 def test_index_types(mg, B, N, T, D, spread, skew):
     rng, dim, coords, types, radii, pose, dpose = _inputs(B, N, T, D, spread, skew, N + D)
