@@ -982,7 +982,16 @@ hipError_t launch_prep(const GridSpec &gs, const Batch &bt, const Workspace &ws,
     // 1 x 8192 11.3 / 18.1, 32 x 8192 17.0 / 19.6, 48 x 8000 26 / 20, 64 x 8000 in eight channels 24 / 18, 12 x 8192 in two 34 / 49;
     // 16 x 4100 11.5 / 12.7, 32 x 4100 13.5 / 13.1; below 4096 atoms alike for few examples (20 x 3000 11 / 11), worse for many
     // (50 x 2040 18 / 10).
-    const bool shared = bt.N > 4096 && bt.B <= 32;
+    // With few channels one share may hold nearly all atoms.  It sorts them in order of bins, which pays where atoms inside the
+    // grid and culled ones are mixed or bins are long; not where nearly all are culled (up to five channels, grids of up to 14 A),
+    // nor in up to three where all find room in the grid (0.08 per cubic Angstrom), up to 60 to a plane.  All atoms in one channel,
+    // points a side at 0.5 A, call, us, shares / one workgroup: 8192 atoms 16 27.4 / 18.7, 24 27.8 / 24.0, 32 28.7 / 29.0, 48 32.7 / 41.1,
+    // 96 47.2 / 48.7; eight of 5000 16 20.6 / 15.4, 48 26.2 / 33.2, 72 33.8 / 40.3, 96 32.0 / 28.7; 4100 24 19.0 / 14.5, 48 24.1 / 24.6,
+    // 72 26.0 / 21.5, 48 at 1 A 31.8 / 34.1; in two of five channels 8192 16 19.4 / 14.8, eight of 5000 72 20.4 / 24.8.
+    const float side = (float)gs.D * gs.res, room = side + 4.0f;        // 2 A on each side for the atoms' reach
+    const bool culled = bt.T <= 5 && side <= 14.0f;
+    const bool roomy = bt.T <= 3 && bt.N <= std::min(5500, 60 * gs.D) && 0.08f * room * room * room >= (float)bt.N;
+    const bool shared = bt.N > 4096 && bt.B <= 32 && !culled && !roomy;
     const bool fits = !vec && !shared && bt.N <= kExMaxAtoms && (size_t)K * 2 * sizeof(int) <= kExMaxLds;
     L.K = fits ? (int)K : 0;
     const size_t lds_bytes = (size_t)L.ints() * sizeof(int);

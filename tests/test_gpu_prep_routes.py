@@ -1,6 +1,6 @@
 """The kernels that sort the atoms, at the sizes where another one or another way through it takes over:
 vector types up to 2048, 4096 and 8192 atoms (two, four and eight per thread of one workgroup), index types up to
-4096 atoms or past 32 examples (one workgroup) and beyond (shares of the types, listed in LDS up to 12288
+4096 atoms, past 32 examples or in few channels of some grids (one workgroup) and beyond (shares of the types, listed in LDS up to 12288
 atoms), bins of thousands of atoms, planes of many bins.  Records have one order: every run gives the same bits."""
 import numpy as np
 import pytest
@@ -29,6 +29,9 @@ def _inputs(B, N, T, D, spread, skew, seed):
     (2, 4097, 3, 16, 2.0, 0.0), (1, 8192, 5, 16, 20.0, 0.0), (33, 4097, 2, 8, 3.0, 0.0), (28, 4200, 28, 6, 3.0, 0.0), (60, 8300, 7, 6, 3.0, 0.3),
     (1, 12288, 1, 16, 6.0, 0.0), (1, 12289, 1, 16, 6.0, 0.0), (1, 14000, 9, 12, 8.0, 0.95), (2, 9000, 4, 70, 1.0, 0.5),
     (9, 8300, 2, 6, 3.0, 1.0),      # nine examples of two shares, one of them without atoms
+    # few channels: one workgroup for grids of up to 14 A, and up to 60 atoms to a plane where all find room; else shares
+    (2, 4097, 5, 18, 4.0, 0.0), (2, 4097, 5, 19, 4.0, 0.0), (1, 8192, 1, 18, 9.0, 0.0), (1, 8192, 1, 19, 9.0, 0.0),
+    (1, 4200, 3, 70, 1.0, 0.9), (1, 4201, 3, 70, 1.0, 0.9), (1, 4200, 4, 70, 1.0, 0.9),
 ])
 def test_index_types(mg, B, N, T, D, spread, skew):
     rng, dim, coords, types, radii, pose, dpose = _inputs(B, N, T, D, spread, skew, N + D)
