@@ -330,7 +330,9 @@ __device__ inline void reduce_channel(const BwdParams &p, const GT *G, int t, si
 // group; the four weight sums of a group are reduced together (19 instructions instead of 52) and
 // kept by the lanes of their channels, so that an atom's weight gradients leave in one store.  Distances
 // are in Angstrom for all groups.  50 x 2040 atoms, 28 x 48^3: 778 instead of 907 us a call; 8 x 12 channels
-// 87 / 95; 2 x 100 channels of 32^3 126 / 165; few channels alike.
+// 87 / 95; 2 x 100 channels of 32^3 126 / 165; few channels alike.  Of 439 sizes 31 got slower, by 2 to 3 % at 0.25 A and few atoms
+// (30 x 100, 28 x 64^3 449 / 437), by 11 % at most (20 x 500, 40 x 48^3 at 0.375 A 494 / 446): the same lines are asked of
+// L2 by fewer instructions, but the wavefronts in flight spread over more groups and L2 misses more of them (2.34e7 / 1.91e7).
 // Bound by the lines that the L2s deliver, 128 bytes for every 26 of a chord (1.39e8 of them, 17.8 GB a launch,
 // 23.3 TB/s: the loads alone take 740 us; the L1s wait for L2 in two thirds of the kernel's 760 us) and by vector
 // instruction issue (0.55 of the 0.76 ms; wavefronts wait 29 % of their time for memory and 44 % for their turn to issue).
