@@ -50,6 +50,35 @@ def test_index_types(mg, B, N, T, D, spread, skew):
     assert np.abs(got - want).max() <= GRAD_RTOL * np.abs(want).max()
 
 
+@pytest.mark.parametrize("N,T,D,spread,skew", [
+    (4097, 5, 19, 4.0, 0.0), (8192, 1, 19, 9.0, 0.0), (8192, 28, 13, 1.0, 0.9), (4201, 3, 70, 1.0, 0.9), (6001, 2, 33, 6.0, 0.5),
+])
+@pytest.mark.parametrize("by_type", [True, False])
+def test_shares_and_one_workgroup_give_the_same_bits(mg, N, T, D, spread, skew, by_type):
+    """An example alone is sorted by shares, among 32 others by one workgroup."""
+    rng, dim, coords, types, radii, pose, _ = _inputs(1, N, T, D, spread, skew, N + T)
+    types[0, ::700] = -1
+    if not by_type:
+        radii = rng.uniform(0.6, 1.5, (1, N)).astype(np.float32)
+    G = rng.standard_normal((1, T, D, D, D)).astype(np.float32)
+    many = lambda v: dev(np.repeat(v, 33, axis=0))          # noqa: E731
+    got = []
+    for of, B in ((dev, 1), (many, 33)):
+        gm = mg.GridMaker(0.75, dim, radius_type_indexed=by_type)
+        co, ty, ra = of(coords), of(types), dev(radii) if by_type else of(radii)
+        ws = gm.mg_prepare(co, ty, ra, T, natoms=of(np.array([N - 5], np.int32)), quats=of(pose["quats"]))
+        grid = gm.mg_forward_index_prepared(B, N, T, ws)
+        grad = torch.full((B, N, 3), float("nan"), device="cuda")
+        gm.mg_backward_index_prepared(B, N, T, of(G), ws, grad_coords=grad)
+        got.append((grid, grad))
+    for one, all_of in zip(*got):
+        one = one.contiguous().view(torch.int32)
+        all_of = all_of.contiguous().view(torch.int32)
+        assert not torch.isnan(one.view(torch.float32)).any()
+        for b in (0, 15, 32):
+            assert torch.equal(one[0], all_of[b])
+
+
 @pytest.mark.parametrize("main", [0, 4, 8])         # (64 examples: shares of three types each)
 def test_index_shares_longer_than_the_list(mg, main):
     """More than 12288 atoms of one type beside two others in a share, with smaller and larger types in other shares."""
