@@ -274,7 +274,7 @@ def main():
         "vs_baseline": None,
         "dtype": "f32",
         "data": "synthetic",
-        "config": {"workload": "protein-ligand forward (configs[1]): B=50, N=2040 atoms, T=28, "
+        "config": {"workload": "protein-ligand forward: B=50, N=2040 atoms, T=28, "
                                "48^3 points @0.5A, random rotation + <=2A translation per example",
                    "out_bytes": w.out_bytes},
         "settle": dict(settled, what="the same forward call repeated, untimed, before the counted "
@@ -480,10 +480,10 @@ def main():
         r = fwd_row("forward_large_chunk", lambda: gmc.mg_forward_index(
             cc, tc, rc, wc.T, centers=cec, quats=qc, translations=trc, out=outc, workspace=wsc),
             n_slow, wc.out_bytes, wc.B)
-        r["workload"] = "configs[4], one chunk: B=16, N=8000, T=28, 96^3 @0.25A"
+        r["workload"] = "one chunk of a large-scale run: B=16, N=8000, T=28, 96^3 @0.25A"
         del outc
 
-        # the tiny configuration (configs[0]: one example, 100 atoms, 24^3): launch-bound, so a
+        # the tiny configuration (one example, 100 atoms, 24^3): launch-bound, so a
         # latency in microseconds and no roofline fraction (221 KB would take 0.03 us at the HBM
         # peak) -- called eagerly, and replayed from a HIP graph that holds the call's launches
         wt = workloads.tiny()
@@ -533,7 +533,7 @@ def main():
             "latency_us_eager_two_launches": r2["ms_per_call"] * 1e3,
             "latency_us_c_abi": r_raw["ms_per_call"] * 1e3,
             "roofline": None,
-            "workload": "configs[0]: B=1, N=100, T=4, 24^3 @0.5A (221 KB out): calls back to back, "
+            "workload": "tiny: B=1, N=100, T=4, 24^3 @0.5A (221 KB out): calls back to back, "
                         "one kernel launch per call (every tile looks at the 100 atoms itself); "
                         "launch-bound, so a latency and no roofline fraction"}
         result["rows"] = rows
